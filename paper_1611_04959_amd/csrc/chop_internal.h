@@ -111,6 +111,7 @@ struct KArgs {
 
 struct GatherArgs {
     const int16_t *raw;
+    int64_t n;  // samples
     int64_t stride;
     int32_t C;
     int32_t pad;
@@ -165,7 +166,7 @@ hipError_t launch_unpack12(const uint8_t *in, int64_t in_stride, int32_t C, int6
 #define DAQ_MAX_PARTS 4
 #endif
 constexpr int kMaxParts = DAQ_MAX_PARTS;
-hipError_t launch_gather(const GatherArgs &g, int grid, hipStream_t s);
+hipError_t launch_gather(const GatherArgs &g, int n_cu, hipStream_t s);
 
 // Island compression: one fill's packed rows and where its stream goes.
 struct ZFillDev {

@@ -1930,15 +1930,6 @@ struct ChunkInfo {
     int64_t tl, n_isl;
     int32_t i0, i1;
 };
-__device__ __forceinline__ ChunkInfo chunk_info(const FillDev &fd, int64_t k) {
-    ChunkInfo c;
-    c.tl = *gbl(&fd.counts->total_len);
-    c.n_isl = *gbl(&fd.counts->n_islands);
-    c.i0 = k * kCopyChunk < c.tl ? *gbl(fd.cmap + k) : 0;
-    c.i1 = (k + 1) * kCopyChunk < c.tl ? *gbl(fd.cmap + k + 1) : (int32_t)c.n_isl - 1;
-    return c;
-}
-
 // Chunk k of fill fd's packed rows (the fill's counts, run table and chunk
 // map complete; ci the same in every thread); L is a CopyLayout for
 // kCopyChunk + 1 runs. COHERENT: the run table is read with device-scope
@@ -2039,7 +2030,10 @@ __device__ __forceinline__ void copy_store(const FillDev &fd, int c, int c_hi, i
 
 // Packed positions [q0, q0 + m) of channels [c_lo, c_hi) of fill fd; the
 // segment's nrun runs are in st[] / d[] (d relative to q0, d[0] <= 0, end
-// marks at nrun and nrun + 1). Executed by one whole wave.
+// marks at nrun and nrun + 1). Executed by one whole wave. CHECK: the runs come
+// from a table of the caller's, which may not be one that the library wrote:
+// words whose 16-byte loads would leave the row go sample by sample.
+template <bool CHECK = false>
 __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int m, int c_lo, int c_hi,
                                              const int32_t *st, const int32_t *d, int32_t *slot, int nrun,
                                              int lane) {
@@ -2079,6 +2073,11 @@ __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int 
     const int src0 = st0 + (pos - d0);
     const int split = kind == 2 ? d1 - pos : kVec;
     const int src1 = st1 - split;
+    if (CHECK) {
+        const bool in0 = src0 >= 0 && (int64_t)src0 + kVec <= fd.n;
+        const bool in1 = src1 >= 0 && (int64_t)src1 + kVec <= fd.n;
+        if ((kind == 1 && !in0) || (kind == 2 && !(in0 && in1))) kind = 3;
+    }
     const int64_t o = q0 + pos;
     uint4 a0[kCopyU], a1[kCopyU], b0[kCopyU], b1[kCopyU];
 #pragma unroll
@@ -2556,9 +2555,46 @@ __global__ void __launch_bounds__(256) k_prepare(KArgs a) {
     }
 }
 
-// Two-pass gather: thread handles packed positions p0 + tid + 256 k.
-__global__ void __launch_bounds__(256) k_gather(GatherArgs g) {
-    constexpr int K = 8;
+// ---- two-call form: packed samples from an existing island table ------------------
+//
+// Work items as in the copy pass: one wave writes one segment of kCopyChunk
+// packed positions of a group of kCopyGroup channels, with the same 16-byte
+// loads and stores. There is no run table or chunk map here, so the wave finds
+// the segment's islands in the caller's table itself: a search with 64 probes
+// a step (two dependent loads for up to 4,096 islands), then the records up to
+// the segment's end, 64 at a time. What bounds it is that chain of loads, then
+// HBM. (One thread per packed position with a binary search and a loop over
+// all channels, 2,048 positions per work-group, took 126 us for a fill of
+// 54 x 300,001 at three times the nominal pulse rate, since it left most CUs
+// without work; find and gather together went from 148.3 to 37.3 us.)
+// The table is the caller's: a word whose 16-byte loads would leave the row
+// (records not in increasing start, or past the fill) goes sample by sample,
+// as does a segment touched by more than kSegRuns - 2 records (empty ones).
+
+// Last of the records [0, n) with offset <= q (0 if there is none); n >= 1.
+// Executed by one whole wave.
+__device__ __forceinline__ int64_t island_at(const daq_island *isl, int64_t n, int64_t q, int lane) {
+    int64_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + 63) >> 6;
+        const int64_t i = lo + lane * step;
+        const bool at_or_before = lane == 0 || (i < hi && *gbl(&isl[i].offset) <= q);
+        const int k = 63 - __clzll((long long)__ballot(at_or_before));
+        lo += k * step;
+        hi = hi < lo + step ? hi : lo + step;
+    }
+    return lo;
+}
+
+constexpr int kGatherThreads = 512;
+
+__global__ void __launch_bounds__(kGatherThreads) k_gather(GatherArgs g) {
+    constexpr int NW = kGatherThreads / 64;
+    __shared__ int32_t s_st[NW][kSegRuns];
+    __shared__ int32_t s_d[NW][kSegRuns];
+    __shared__ int32_t s_slot[NW][64];
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n_all = g.counts->n_islands;
     const int64_t n = n_all < g.cap ? n_all : g.cap;
     if (n <= 0) return;
@@ -2567,32 +2603,66 @@ __global__ void __launch_bounds__(256) k_gather(GatherArgs g) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && g.counts->total_len > g.out_stride)
         atomicOr(&g.counts->status, DAQ_STATUS_OUT_STRIDE);
     const int64_t lim = total < g.out_stride ? total : g.out_stride;
-    for (int64_t p0 = (int64_t)blockIdx.x * 256 * K; p0 < lim; p0 += (int64_t)gridDim.x * 256 * K) {
-        int64_t src[K];
-        int64_t dst[K];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const int64_t pos = p0 + threadIdx.x + 256 * k;
-            dst[k] = -1;
-            src[k] = 0;
-            if (pos < lim) {
-                int64_t lo = 0, hi = n - 1;  // last island whose offset <= pos
+    if (lim <= 0) return;
+    FillDev fd{};
+    fd.raw = g.raw;
+    fd.n = g.n;
+    fd.stride = g.stride;
+    fd.C = g.C;
+    fd.out = g.out;
+    fd.out_stride = g.out_stride;
+    const int groups = (g.C + kCopyGroup - 1) / kCopyGroup;
+    const int64_t items = (lim + kCopyChunk - 1) / kCopyChunk * groups;
+    int32_t *st = s_st[wid];
+    int32_t *dd = s_d[wid];
+    for (int64_t it = (int64_t)blockIdx.x * NW + wid; it < items; it += (int64_t)gridDim.x * NW) {
+        const int64_t k = it / groups;
+        const int c_lo = (int)(it - k * groups) * kCopyGroup;
+        const int c_hi = c_lo + kCopyGroup < g.C ? c_lo + kCopyGroup : g.C;
+        const int64_t q0 = k * kCopyChunk;
+        const int m = (int)(lim - q0 < kCopyChunk ? lim - q0 : kCopyChunk);
+        const int64_t i0 = island_at(g.isl, n, q0, lane);
+        int nrun = 0;
+        bool more = true;
+        while (more && nrun <= kSegRuns - 2) {
+            const int64_t i = i0 + nrun + lane;
+            int64_t off = q0 + m, start = 0;
+            if (i < n) {
+                off = *gbl(&g.isl[i].offset);
+                start = *gbl(&g.isl[i].start);
+            }
+            // the first record belongs to the segment whatever its offset
+            const uint64_t in = __ballot((i < n && off < q0 + m) || (nrun == 0 && lane == 0));
+            const int cnt = ~in == 0 ? 64 : __ffsll((unsigned long long)~in) - 1;
+            if (lane < cnt && nrun + lane < kSegRuns - 2) {
+                st[nrun + lane] = (int32_t)start;
+                dd[nrun + lane] = (int32_t)(off - q0);
+            }
+            nrun += cnt;
+            more = cnt == 64;
+        }
+        if (nrun <= kSegRuns - 2) {
+            if (lane < 2) {
+                st[nrun + lane] = 0;
+                dd[nrun + lane] = 1 << 30;
+            }
+            __builtin_amdgcn_wave_barrier();
+            copy_segment<true>(fd, q0, m, c_lo, c_hi, st, dd, s_slot[wid], nrun, lane);
+        } else {
+            for (int j = lane; j < m; j += 64) {
+                const int64_t pos = q0 + j;
+                int64_t lo = i0, hi = n - 1;
                 while (lo < hi) {
                     const int64_t mid = (lo + hi + 1) >> 1;
-                    if (g.isl[mid].offset <= pos) lo = mid;
+                    if (*gbl(&g.isl[mid].offset) <= pos) lo = mid;
                     else hi = mid - 1;
                 }
-                dst[k] = pos;
-                src[k] = g.isl[lo].start + (pos - g.isl[lo].offset);
+                const int64_t src = *gbl(&g.isl[lo].start) + (pos - *gbl(&g.isl[lo].offset));
+                for (int c = c_lo; c < c_hi; c++)
+                    *gbl(g.out + (int64_t)c * g.out_stride + pos) = *gbl(g.raw + (int64_t)c * g.stride + src);
             }
         }
-        for (int c = 0; c < g.C; c++) {
-            const int16_t *row = g.raw + (int64_t)c * g.stride;
-            int16_t *orow = g.out + (int64_t)c * g.out_stride;
-#pragma unroll
-            for (int k = 0; k < K; k++)
-                if (dst[k] >= 0) orow[dst[k]] = row[src[k]];
-        }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -2679,8 +2749,15 @@ hipError_t launch_unpack12(const uint8_t *in, int64_t in_stride, int32_t C, int6
     return hipGetLastError();
 }
 
-hipError_t launch_gather(const GatherArgs &g, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_gather, dim3(grid), dim3(256), 0, s, g);
+hipError_t launch_gather(const GatherArgs &g, int n_cu, hipStream_t s) {
+    // as many work-groups as the copy pass keeps on a CU, fewer for fills whose
+    // samples could not give each wave an item
+    const int64_t most = g.n < g.out_stride ? g.n : g.out_stride;
+    const int64_t items = (most + kCopyChunk - 1) / kCopyChunk * ((g.C + kCopyGroup - 1) / kCopyGroup);
+    const int64_t need = (items + kGatherThreads / 64 - 1) / (kGatherThreads / 64);
+    const int64_t wide = (int64_t)kCopyWgsPerCu * n_cu;
+    const int grid = (int)(need < 1 ? 1 : (need < wide ? need : wide));
+    hipLaunchKernelGGL(k_gather, dim3(grid), dim3(kGatherThreads), 0, s, g);
     return hipGetLastError();
 }
 

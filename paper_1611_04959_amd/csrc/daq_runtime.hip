@@ -1038,6 +1038,7 @@ int daq_gather_islands(daq_ctx *ctx, const daq_fill *fill, const daq_island *d_i
     DeviceGuard guard(ctx->device);
     GatherArgs g{};
     g.raw = fill->raw;
+    g.n = fill->n_samples;
     g.stride = fill->row_stride;
     g.C = fill->n_channels;
     g.isl = d_islands;
@@ -1045,9 +1046,7 @@ int daq_gather_islands(daq_ctx *ctx, const daq_fill *fill, const daq_island *d_i
     g.counts = d_counts;
     g.out = d_out;
     g.out_stride = out_stride;
-    const int64_t most = std::min<int64_t>(fill->n_samples, out_stride);
-    int grid = (int)std::min<int64_t>((int64_t)ctx->n_cu * 4, std::max<int64_t>(1, (most + 2047) / 2048));
-    HIP_TRY(daqk::launch_gather(g, grid, (hipStream_t)stream));
+    HIP_TRY(daqk::launch_gather(g, ctx->n_cu, (hipStream_t)stream));
     return DAQ_OK;
 }
 
