@@ -127,11 +127,14 @@ typedef struct daq_fill_out {
                                   two work-groups per CU (threads = 256)      */
 #define DAQ_VARIANT_RELOAD18 3 /* as RELOAD with 18 rows in flight (6 there) */
 #define DAQ_VARIANT_RELOAD27 4 /* as RELOAD with 27 rows in flight          */
-#define DAQ_VARIANT_SPLIT 5    /* a streaming scan that writes island-mask
-                                  bits and tile totals, an edge pass
-                                  (prefixes, records, run table, counts) and
+#define DAQ_VARIANT_SPLIT 5    /* a streaming scan that writes one flag bit
+                                  per sample and a summary of each 512, an
+                                  edge pass (records, run table, counts) and
                                   a copy pass that copies only the island
-                                  samples (threads = 256 or 512)             */
+                                  samples, or one pass that does both for
+                                  launches of few fills (threads = 256 or
+                                  512: the work-groups of the Q-method's
+                                  pass where it takes the scan's place)      */
 #define DAQ_VARIANT_PIPE 6     /* one persistent kernel: work-groups take scan
                                   tiles (each finds its islands and prefix at
                                   once) and copy chunks of fills whose tiles
@@ -140,7 +143,8 @@ typedef struct daq_fill_out {
 typedef struct daq_schedule {
     int32_t threads;     /* work-group size: 128, 256 or 512                    */
     int32_t wgs_per_cu;  /* persistent grid = wgs_per_cu x CUs (1..16); 0 =
-                            one work-group per tile                            */
+                            one work-group per tile, as the split variant's
+                            scan always has                                    */
     int32_t variant;     /* DAQ_VARIANT_*; under DAQ_VARIANT_LDS, fills it
                             cannot take (other channel counts, halos wider
                             than a quarter of its tile) use the re-read path
@@ -211,16 +215,17 @@ int daq_gather_islands(daq_ctx *ctx, const daq_fill *fill,
                        void *stream);
 
 /* Both calls at once, with the context's schedule: by default the split
- * schedule's scan, edge and copy passes; the fused schedules find the
+ * schedule's passes; the fused schedules find the
  * islands and write the packed samples in the same read of the raw data.
  * Same results as daq_find_islands followed by daq_gather_islands. */
 int daq_chop_fill(daq_ctx *ctx, const daq_fill *fill, const daq_fill_out *out,
                   void *stream);
 
 /* Many independent fills (uneven N, thresholds, windows) in one launch of
- * the context's schedule (by default the split schedule's three kernels over
- * every fill, with persistent grids), replayed from a captured HIP graph when
- * the context's graphs are on and launched plainly otherwise. Results per
+ * the context's schedule (by default the split schedule's kernels over every
+ * fill), replayed from a captured HIP graph when the context's graphs are on
+ * and launched plainly otherwise (and where the split schedule needs only two
+ * kernels, for few fills: a replay costs more than they do). Results per
  * fill are identical to daq_chop_fill whatever the schedule. The paper
  * chops each fill as it arrives (Section 3, fills in bursts at 12 Hz);
  * taking several in one launch is this library's addition, for throughput.
@@ -234,21 +239,20 @@ int daq_process_batch(daq_ctx *ctx, const daq_fill *fills,
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * results as daq_process_batch, computed with the split schedule (the
- * context's thread count and persistent grid when it holds a split schedule,
- * else 512 threads and 8 work-groups per CU) by plain kernel launches only:
+ * results as daq_process_batch, computed with the split schedule by plain
+ * kernel launches only:
  * no allocation, no graph, no event, no memset and no host staging. Every
- * scratch buffer of the call (look-back words, tile totals,
- * effective thresholds, the descriptor table, each fill's mask bits, run
- * table and chunk map) lives in one static device array of
- * DAQ_NOALLOC_SCRATCH_BYTES per GPU, which the library holds from the first
+ * scratch buffer of the call (effective thresholds, the descriptor table, each
+ * fill's flag bits and run table) lives in one static device array of
+ * DAQ_NOALLOC_SCRATCH_BYTES per GPU, and the tile summaries in three times as
+ * much behind it, which the library holds from the first
  * daq_ctx_create on that GPU until the process ends; the descriptors reach it
  * through kernel arguments. Calls on one GPU share that array: calls that
  * overlap in time on one GPU (other streams, other contexts or threads) race
  * and must be serialised by the caller; each call clears what it needs.
  * Needs daq_noalloc_scratch_bytes(fills, n) <= DAQ_NOALLOC_SCRATCH_BYTES
  * (DAQ_ERANGE otherwise, before anything is launched; 16 fills of
- * 54 x 560,000 need about 3.5 MB). Other errors as for daq_process_batch;
+ * 54 x 560,000 need about 3.2 MB). Other errors as for daq_process_batch;
  * the context's timing, graph and fill-group settings do not apply. */
 #define DAQ_NOALLOC_SCRATCH_BYTES ((int64_t)32 << 20)
 int64_t daq_noalloc_scratch_bytes(const daq_fill *fills, int32_t n);
@@ -292,10 +296,10 @@ int daq_qmethod_batch(daq_ctx *ctx, const daq_fill *fills,
 
 /* Both methods on one read (Section 3 and Table 2 run the T-method and the
  * Q-method on every fill): daq_process_batch's T-method results in outs and
- * the Q-method's in qouts (as daq_qmethod_batch computes them), the sums and
- * accumulator updates taken inside the chop's scan pass, so the raw samples
- * are read once for both. Runs the split schedule whatever the context's
- * (plain launches, no graph). The pedestals go to outs[i].ped or, when that
+ * the Q-method's in qouts (as daq_qmethod_batch computes them): the Q-method's
+ * pass also tests the threshold and takes the place of the chop's scan, so the
+ * raw samples are read once for both. Runs the split schedule whatever the
+ * context's (plain launches, no graph). The pedestals go to outs[i].ped or, when that
  * is NULL, to qouts[i].ped (DAQ_EINVAL if both are set). Errors as for both
  * calls. */
 int daq_process_batch_q(daq_ctx *ctx, const daq_fill *fills,
@@ -600,10 +604,11 @@ void daq_server_destroy(daq_server *srv);
 int daq_read_stream(const void *d_buf, int64_t bytes, unsigned int *d_sink,
                     int32_t blocks, int32_t layout, void *stream);
 
-/* The rate of the chop scan's own read pattern, with nothing else done:
+/* The rate of a scan that recomputes its tiles' halos (the read pattern of
+ * DAQ_VARIANT_PIPE), with nothing else done:
  * reads n_fills fills of `channels` rows of n_samples int16 each (row r of
- * fill f at d_raw + (f * channels + r) * n_samples, 16-byte aligned) in the
- * split scan's tiles at 512 threads (4,048 owned samples plus a 32-sample
+ * fill f at d_raw + (f * channels + r) * n_samples, 16-byte aligned) in
+ * tiles of 512 threads (4,048 owned samples plus a 32-sample
  * left and 16-sample right halo, every channel row, 9 rows in flight, 16-byte
  * non-temporal loads; groups of 8 outside a row are skipped), in a persistent
  * grid of `blocks` work-groups of 512 threads striding over the tiles.

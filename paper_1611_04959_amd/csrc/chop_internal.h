@@ -22,14 +22,12 @@ constexpr int kVariantResident = 1;  // rows kept in registers until written out
 constexpr int kVariantStream = 2;    // rows DMA'd into LDS; two work-groups per CU
 constexpr int kVariantReload18 = 3;  // as kVariantReload, 18 rows in flight per round (6 there)
 constexpr int kVariantReload27 = 4;  // as kVariantReload, 27 rows in flight per round
-constexpr int kVariantSplit = 5;     // scan pass (mask bits, tile totals), edge and copy passes
+constexpr int kVariantSplit = 5;     // scan pass (flag bits), edge and copy passes
 constexpr int kVariantPipe = 6;      // one persistent kernel: scan tiles and copy chunks from shared counters
 constexpr int kVariantLast = 6;
-// Guard bytes around each fill's island-mask bits (read as zero past the ends).
-constexpr int kMaskGuard = 16;
 // Packed positions per chunk of a row: the copy pass writes one chunk of a
-// channel group per wave (one 16-byte word per lane), and the edge pass
-// records the island holding every multiple of it.
+// channel group per wave (one 16-byte word per lane), and the persistent
+// schedule records the island holding every multiple of it.
 #ifndef DAQ_COPY_CHUNK
 #define DAQ_COPY_CHUNK 512
 #endif
@@ -41,6 +39,41 @@ constexpr int kStreamThreads = 256;
 constexpr int kModeChop = 0;
 constexpr int kModeStream = 1;
 
+// Samples of a tile of the split variant's scan (one wave's 16-byte loads).
+constexpr int kScanTile = 512;
+// Its work-groups: the rows of a tile are shared by their waves, each with
+// this many rows in flight (54 channels: 14 a wave, all at once).
+constexpr int kScanThreads = 256;
+constexpr int kScanRows = 14;
+// The scan computes its fill's pedestals itself up to this many pedestal
+// samples (16 lanes hold them, 8 each); k_prepare does for more.
+constexpr int kScanPed = 128;
+// Edge pass: a work-group takes a group of tiles, one 64-sample flag word per
+// thread; every fill's summaries start at a whole group.
+constexpr int kEdgeThreads = 256;
+constexpr int kGroupTiles = kEdgeThreads * 64 / kScanTile;
+// Tiles whose summaries one work-group adds up: a calorimeter fill of 560,000
+// samples is one such segment; longer fills have segment summaries too.
+constexpr int kSegGroups = 36;
+constexpr int kSegTiles = kSegGroups * kGroupTiles;
+// Emit pass: threads per work-group, and the most fills of a launch that takes
+// it in place of the edge and copy passes.
+constexpr int kEmitThreads = 512;
+#ifndef DAQ_EMIT_FILLS
+#define DAQ_EMIT_FILLS 8
+#endif
+constexpr int kEmitFills = DAQ_EMIT_FILLS;
+
+// Flags of a stretch of samples, as a fill's islands see them (gap = pre + post
+// + 1: windows of flags at most gap apart are one island). Stretches add up
+// from left to right.
+struct FlagSum {
+    int32_t first, last;  // first and last flag, or -1
+    int32_t begin;        // first flag of the island that holds `last`
+    int32_t len;          // sum over neighbouring flags of min(their distance, gap)
+    int32_t cnt;          // neighbouring flags more than gap apart
+};
+
 // Device-side view of one fill and where its results go.
 struct FillDev {
     const int16_t *raw;
@@ -50,6 +83,10 @@ struct FillDev {
     int32_t np;         // pedestal samples
     int32_t thr;
     int32_t pre;
+    uint64_t *flags;    // split variant: threshold flags, bit t % 64 of word t / 64; whole
+                        // words, zero past the last sample
+    int32_t *ped;       // may be null
+    int64_t tile_base;  // global index of the fill's first tile in the launch
     int32_t post;
     int32_t gl;         // halo groups of 8 samples left of a tile: ceil((post + 1) / 8)
     int32_t gr;         // halo groups right of a tile: ceil((pre + 1) / 8)
@@ -58,24 +95,20 @@ struct FillDev {
     int32_t mode;       // kModeChop or kModeStream
     int32_t pad1;
     int64_t tout;       // samples a tile owns (decides and writes)
-    int64_t tile_base;  // global index of the fill's first tile in the launch
     int64_t n_tiles;
+    int64_t sum_base;   // split variant: index of the fill's first tile summary, a multiple of kGroupTiles
     daq_island *isl;
     int64_t cap;
     daq_counts *counts;
-    int32_t *ped;       // may be null
     int16_t *out;       // may be null (find only)
     int64_t out_stride;
-    uint8_t *mbits;     // split variant: island-mask bits of the fill (bit t of
-                        // byte t / 8), kMaskGuard zero bytes on either side
-    int32_t *runs;      // split variant: (start, offset) of every island
+    int32_t *runs;      // split and pipe variants: (start, offset) of every island
                         // (room for the worst-case island count)
-    int32_t *cmap;      // split variant: island holding packed position
+    int32_t *cmap;      // pipe variant: island holding packed position
                         // k * kCopyChunk, for every such position < total_len
     int64_t *qsum;      // Q-method: decimated sums, or null
     int32_t *acc;       // Q-method: fill-by-fill accumulator rows, or null
     int64_t acc_stride;
-    int64_t pad2;
 };
 static_assert(sizeof(FillDev) % 16 == 0, "descriptors are read as 16-byte words");
 
@@ -85,7 +118,7 @@ struct BatchHdr {
     int32_t n_fills;
     int32_t stream_loads;  // 1: the scan reads raw rows non-temporally (batches larger than the caches)
     int64_t total_tiles;
-    int64_t copy_slots;  // split variant: n_fills x chunks of the longest fill
+    int64_t total_groups;  // split variant: groups of tiles of all fills
     int64_t pad2;
 };
 static_assert(sizeof(BatchHdr) % 16 == 0, "the descriptor table follows the header in one buffer");
@@ -96,16 +129,23 @@ struct KArgs {
     int32_t n_fills;
     int32_t stream_loads;
     int64_t total_tiles;
-    uint64_t *tile_state;  // one look-back word per tile (split variant: tile totals)
+    uint64_t *tile_state;  // one look-back word per tile (not the split variant)
     uint32_t *ticket;      // 16 words: tile dispenser; pipe variant: copy cursor, give-up flag
     int64_t *thr_eff;      // per fill: threshold + sum of pedestals
-    uint64_t *tile_pref;   // split variant: exclusive prefix of each tile; pipe variant:
-                           // finished tiles of each fill (one word per fill)
-    int64_t copy_slots;    // split variant, when hdr is null
+    uint64_t *tile_pref;   // pipe variant: finished tiles of each fill (one word per fill)
+    const int64_t *tile_bases;  // split variant: each fill's tile_base and sum_base, with table
+    const int64_t *sum_bases;
+    int4 *sums;            // split variant: packed FlagSum of every tile
+    FlagSum *seg_sums;     // split variant: the same of the segments of long fills
+    int64_t total_groups;  // split variant, when hdr is null
     int32_t part, parts;   // split variant: this launch covers fill group `part`
                            // of `parts` equal groups of the batch
-    int32_t q_fused;       // split variant: the scan pass also runs the Q-method
-    int32_t pad_q;
+    int32_t q_fused;       // split variant: the Q-method's pass takes the scan's place
+    int32_t split;         // 1: the split variant
+    int32_t ped_scan;      // split variant: the scan computes the pedestals
+    int32_t multi_seg;     // split variant: a fill has more than kSegTiles tiles
+    int32_t fused;         // split variant: the emit pass takes the edge and copy passes' place
+    int32_t copies;        // split variant: some fill has packed rows to write
     FillDev one;
 };
 
@@ -132,6 +172,12 @@ struct TileShape {
 };
 inline TileShape tile_shape(int32_t pre, int32_t post, int32_t channels, int threads, int variant) {
     TileShape t;
+    if (variant == kVariantSplit) {  // no halo: windows are the later passes' business
+        t.gl = t.gr = t.wide = 0;
+        t.mode = kModeChop;
+        t.tout = kScanTile;
+        return t;
+    }
     t.gl = (post + 1 + kVec - 1) / kVec;
     t.gr = (pre + 1 + kVec - 1) / kVec;
     if (variant == kVariantStream && channels == kResidentChannels && (t.gl + t.gr) * 4 <= kStreamGroups) {
@@ -150,8 +196,10 @@ hipError_t launch_prepare(const KArgs &a, int blocks, hipStream_t s);
 hipError_t launch_chop(const KArgs &a, int threads, int variant, int grid, hipStream_t s);
 // Split variant: the scan pass, then the edge and copy passes, over the fill
 // group a.part of a.parts.
-hipError_t launch_scan(const KArgs &a, int threads, int grid, hipStream_t s);
-hipError_t launch_emit(const KArgs &a, int threads, int edge_grid, int copy_grid, hipStream_t s);
+hipError_t launch_scan(const KArgs &a, int grid, hipStream_t s);
+hipError_t launch_emit(const KArgs &a, int edge_grid, int copy_grid, hipStream_t s);
+// Both in one kernel, for launches of few fills of at most kSegTiles tiles.
+hipError_t launch_emit_fused(const KArgs &a, int wgs_per_fill, hipStream_t s);
 // Work-groups per CU of the copy pass's persistent grid.
 #ifndef DAQ_COPY_WGS_PER_CU
 #define DAQ_COPY_WGS_PER_CU 4

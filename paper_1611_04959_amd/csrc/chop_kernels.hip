@@ -8,14 +8,15 @@
 //            threshold thr + sum(ped); clears the look-back words and counts
 //            (every schedule but the split one, which sums the pedestals in
 //            its scan).
-// k_scan_pass, k_edge_pass, k_copy_pass
+// k_scan_pass, k_edge_pass, k_copy_pass, k_emit_pass
 //            the split schedule (the default): a streaming scan that computes
-//            its fill's pedestals and writes one island-mask bit per sample
-//            and tile totals; an edge pass
-//            (one wave per tile: its prefix from the totals of the fill's
-//            earlier tiles, the island records, a run table, the counts);
-//            and a copy of the island samples in equal chunks of packed
-//            positions.
+//            its fill's pedestals and writes one threshold flag per sample
+//            and a summary of each tile's flags; an edge pass (the island
+//            records, a run table and the counts, from the flags and the
+//            summaries of the fill's earlier tiles; k_seg_pass sums these up
+//            for very long fills); and a copy of the island samples in equal
+//            chunks of packed positions. The emit pass is both in one, for
+//            launches of few fills.
 // k_pipe     one persistent kernel: scan tiles (steps 1-4a below) and copy
 //            chunks of finished fills, taken from shared counters.
 // k_chop     the fused pass. Each thread of a work-group takes 8 consecutive
@@ -126,42 +127,6 @@ __device__ __forceinline__ int64_t tile_base_at(const KArgs &a, int f) {
     return a.table ? gbl(a.table + f)->tile_base : a.one.tile_base;
 }
 
-// The edge pass copies the descriptors of batches of at most kFdLds fills
-// into LDS once per work-group, with the tile bases: a wave that meets a new
-// fill then reads its descriptor from LDS instead of waiting on a global
-// load. (The scan and copy passes do not: there the copy cost as much as
-// the load it saves, or more.)
-constexpr int kFdLds = 16;
-constexpr int kFdWords = (int)(sizeof(FillDev) / 16);
-
-// Copies the first nf descriptors of the table into s (call before the
-// barrier that publishes it); false when the batch is too large or has no table.
-template <int NT>
-__device__ __forceinline__ bool stage_fills(const KArgs &a, int nf, u32x4 *s) {
-    if (a.table == nullptr || nf > kFdLds) return false;
-    const DAQ_GLOBAL u32x4 *src = (const DAQ_GLOBAL u32x4 *)a.table;
-    for (int i = threadIdx.x; i < nf * kFdWords; i += NT) s[i] = src[i];
-    return true;
-}
-
-// Descriptor of fill f from the LDS copy (f the same in every lane).
-__device__ __forceinline__ FillDev fill_from_lds(const u32x4 *s, int f) {
-    f = __builtin_amdgcn_readfirstlane(f);
-    union {
-        FillDev d;
-        u32x4 v[kFdWords];
-    } u;
-#pragma unroll
-    for (int i = 0; i < kFdWords; i++) {
-        const u32x4 w = s[f * kFdWords + i];
-        u.v[i] = u32x4{(unsigned)__builtin_amdgcn_readfirstlane((int)w.x),
-                       (unsigned)__builtin_amdgcn_readfirstlane((int)w.y),
-                       (unsigned)__builtin_amdgcn_readfirstlane((int)w.z),
-                       (unsigned)__builtin_amdgcn_readfirstlane((int)w.w)};
-    }
-    return u.d;
-}
-
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 // Adds the eight int16 samples of one 16-byte row chunk to eight sums: one
@@ -226,97 +191,6 @@ __device__ __forceinline__ void store16_i32(int32_t *p, const uint4 v, bool stre
     w.w = v.w;
     if (stream) __builtin_nontemporal_store(w, (DAQ_GLOBAL u32x4 *)p);
     else *(DAQ_GLOBAL u32x4 *)p = w;
-}
-
-// The same with the Q-method on the read (Section 3, Q-method paragraph;
-// Table 2, decimation and fill-by-fill rows): an owner thread also adds
-// x - ped[c] to the fill's accumulator rows for its 8 samples and returns the
-// pedestal-subtracted calorimeter sum of its valid samples in *gsum. Every
-// load of a round (raw rows, pedestals, accumulator rows) is issued before
-// the round's first store.
-template <int R, bool STREAM>
-__device__ uint32_t group_flags_q(const FillDev &fd, int64_t p, int32_t thr_eff, int64_t valid, bool owner,
-                                  int64_t ped_total, int64_t *gsum) {
-    auto ld = [](const int16_t *q) { return STREAM ? load16_stream(q) : load16(q); };
-    const int16_t *xr = fd.raw + p;
-    int32_t *ar = (owner && fd.acc != nullptr) ? fd.acc + p : nullptr;
-    const bool full = valid >= kVec;
-    const int nv = full ? kVec : (int)valid;
-    int32_t s[kVec] = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto update = [&](int c, const uint4 v, const u32x4 a0, const u32x4 a1, int32_t pc) {
-        int32_t *row = ar + (int64_t)c * fd.acc_stride;
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        uint32_t d[kVec];
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            d[2 * k] = (uint32_t)((int32_t)(int16_t)(w[k] & 0xFFFFu) - pc);
-            d[2 * k + 1] = (uint32_t)((int32_t)(int16_t)(w[k] >> 16) - pc);
-        }
-        if (full) {
-            store16_i32(row, make_uint4(a0.x + d[0], a0.y + d[1], a0.z + d[2], a0.w + d[3]), STREAM);
-            store16_i32(row + 4, make_uint4(a1.x + d[4], a1.y + d[5], a1.z + d[6], a1.w + d[7]), STREAM);
-        } else {
-            for (int k = 0; k < nv; k++) gbl(row)[k] = (int32_t)((uint32_t)gbl(row)[k] + d[k]);
-        }
-    };
-    auto load_acc = [&](int c, u32x4 &a0, u32x4 &a1, int32_t &pc) {
-        pc = *gbl(fd.ped + c);
-        if (full) {
-            const int32_t *row = ar + (int64_t)c * fd.acc_stride;
-            a0 = *(const DAQ_GLOBAL u32x4 *)row;
-            a1 = *(const DAQ_GLOBAL u32x4 *)(row + 4);
-        } else {
-            a0 = a1 = u32x4{0u, 0u, 0u, 0u};
-        }
-    };
-    int c = 0;
-    for (; c + R <= fd.C; c += R) {
-        uint4 v[R];
-        u32x4 a0[R], a1[R];
-        int32_t pc[R];
-#pragma unroll
-        for (int u = 0; u < R; u++) v[u] = ld(xr + (int64_t)(c + u) * fd.stride);
-        if (ar != nullptr) {
-#pragma unroll
-            for (int u = 0; u < R; u++) load_acc(c + u, a0[u], a1[u], pc[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < R; u++) {
-            add8(s, v[u]);
-            if (ar != nullptr) update(c + u, v[u], a0[u], a1[u], pc[u]);
-        }
-    }
-    for (; c < fd.C; c++) {
-        const uint4 v = ld(xr + (int64_t)c * fd.stride);
-        add8(s, v);
-        if (ar != nullptr) {
-            u32x4 a0, a1;
-            int32_t pc;
-            load_acc(c, a0, a1, pc);
-            update(c, v, a0, a1, pc);
-        }
-    }
-    if (owner) {
-#pragma unroll
-        for (int k = 0; k < kVec; k++) *gsum += k < nv ? (int64_t)s[k] - ped_total : 0;
-    }
-    return flags8(s, thr_eff, valid);
-}
-
-// Adds the lanes' group sums (8-sample groups at p) into the decimated sums
-// of their kQBin-sample bins: the first lane of each bin within the wave sums
-// the bin's next lanes and makes one atomic add. Executed by whole waves.
-__device__ __forceinline__ void q_bin_add(const FillDev &fd, int64_t p, int64_t gsum) {
-    const int lane = threadIdx.x & 63;
-    const int k = (int)((p >> 3) & (kQBin / kVec - 1));  // group index within its bin
-    int64_t acc = gsum;
-#pragma unroll
-    for (int d = 1; d < kQBin / kVec; d++) {
-        const int64_t t = __shfl_down(gsum, d, 64);
-        if (lane + d < 64 && k + d < kQBin / kVec) acc += t;
-    }
-    if (fd.qsum != nullptr && (k == 0 || lane == 0) && acc != 0 && p >= 0 && p < fd.n)
-        atomicAdd(reinterpret_cast<unsigned long long *>(fd.qsum + (p >> 5)), (unsigned long long)acc);
 }
 
 // Flags of 8 samples starting at p (all C rows read, nothing kept); R rows
@@ -1079,9 +953,9 @@ struct ChopGeom {
 // Step 1 for a tile of NT groups: flags of this thread's 8 samples from all
 // channel rows (Table 2 waveform-sum and threshold rows), R rows in flight,
 // halo groups of wide windows loaded apart; bitmap zero padding; barrier.
-template <int NT, int R, bool Q = false>
+template <int NT, int R>
 __device__ __forceinline__ void chop_flags(const FillDev &fd, const ChopGeom<NT> &q, int32_t thr_eff,
-                                           uint8_t *s_bits, bool stream = false, int64_t ped_total = 0) {
+                                           uint8_t *s_bits, bool stream = false) {
     const int tid = threadIdx.x;
     const int64_t N = fd.n;
     uint32_t fb = 0;
@@ -1090,17 +964,9 @@ __device__ __forceinline__ void chop_flags(const FillDev &fd, const ChopGeom<NT>
     const int w = tid >> 6;
     const bool halo_wave = !fd.wide && (w == 0 || w == NT / 64 - 1);
     const bool nt = stream && !halo_wave;
-    if constexpr (Q) {
-        int64_t gsum = 0;
-        if (q.p >= 0 && q.p < N)
-            fb = nt ? group_flags_q<R, true>(fd, q.p, thr_eff, N - q.p, q.owner, ped_total, &gsum)
-                    : group_flags_q<R, false>(fd, q.p, thr_eff, N - q.p, q.owner, ped_total, &gsum);
-        q_bin_add(fd, q.p, gsum);
-    } else {
-        if (q.p >= 0 && q.p < N)
-            fb = nt ? group_flags<R, true>(fd.raw + q.p, fd.stride, fd.C, thr_eff, N - q.p)
-                    : group_flags<R, false>(fd.raw + q.p, fd.stride, fd.C, thr_eff, N - q.p);
-    }
+    if (q.p >= 0 && q.p < N)
+        fb = nt ? group_flags<R, true>(fd.raw + q.p, fd.stride, fd.C, thr_eff, N - q.p)
+                : group_flags<R, false>(fd.raw + q.p, fd.stride, fd.C, thr_eff, N - q.p);
     s_bits[q.g] = (uint8_t)fb;
     if (fd.wide) {
         for (int h = tid; h < fd.gl + fd.gr; h += NT) {
@@ -1499,13 +1365,12 @@ __global__ void __launch_bounds__(NT) k_chop(KArgs a) {
 
 // ---- variant 5: scan pass, edge pass, copy pass -------------------------------------
 //
-// The scan pass streams the raw rows once and keeps nothing: per tile it
-// writes the island-mask bits of the samples it owns and the tile's totals.
-// The edge pass sums the totals of each tile's predecessors into its
-// exclusive prefix and writes the island records, a run table and the
-// fill's counts; the copy pass copies only the island samples. No tile
-// waits for another, so the streaming pass keeps as many loads in flight as
-// the CU holds.
+// The scan pass streams the raw rows once and keeps one flag bit per sample and
+// a 16-byte summary of the flags of every 512. The edge pass turns them into
+// the island records, a run table and the fill's counts; the copy pass copies
+// only the island samples; launches of few fills do both in one kernel (the
+// emit pass). No work-group waits for another, so the streaming pass keeps as
+// many loads in flight as the CU holds.
 
 // Fills [lo, hi) and their tiles [tile_lo, tile_hi) of the launch's part of
 // the batch (the whole batch when parts <= 1).
@@ -1524,26 +1389,23 @@ __device__ __forceinline__ PartRange part_range(const KArgs &a, int nf, int64_t 
     return r;
 }
 
-#ifndef DAQ_Q_SCAN_ROWS
-#define DAQ_Q_SCAN_ROWS 4  // the same with the Q-method fused (three loads per row)
-#endif
 #ifndef DAQ_SCAN_ROWS
-#define DAQ_SCAN_ROWS 9  // channel rows each thread has in flight
+#define DAQ_SCAN_ROWS 9  // channel rows each thread of the persistent schedule has in flight
 #endif
 
 // Flags and dilation of one tile (Table 2 threshold and pre/post rows): the
 // island-mask bits of samples p - 1 .. p + 8 of the calling thread (zero for
 // threads that own no samples).
-template <int NT, int R, bool Q = false>
+template <int NT, int R>
 __device__ __forceinline__ uint32_t tile_mask10(const FillDev &fd, const ChopGeom<NT> &q, int32_t thr_eff,
-                                                uint8_t *lds, bool stream, int64_t ped_total = 0) {
+                                                uint8_t *lds, bool stream) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wid = tid >> 6;
     const int64_t N = fd.n;
     uint8_t *s_bits = lds;
     uint32_t *s_pc = reinterpret_cast<uint32_t *>(lds + ChopLds<NT>::kWords * 8);
-    chop_flags<NT, R, Q>(fd, q, thr_eff, s_bits, stream, ped_total);
+    chop_flags<NT, R>(fd, q, thr_eff, s_bits, stream);
     const int Wn = (q.G + 7) >> 3;
     const uint64_t *words = reinterpret_cast<const uint64_t *>(s_bits);
     // windows of at most 55 samples: the flags around a group fit one 64-bit
@@ -1648,101 +1510,333 @@ __device__ int64_t fill_pedestals(const FillDev &fd, bool write, long long *s_ac
     return sum;
 }
 
-// Scan pass, one tile: flags, dilation, mask bits, totals. Each wave leaves
-// its totals (island samples, islands begun) in s_part; thread 0 adds them up
-// and stores the tile's word after the next tile's first barrier (or after
-// the work-group's last tile), so a tile ends without a barrier of its own
-// and tile_state needs no clearing. Before that, thread 0 stores the word of
-// the previous tile (prev_tile >= 0) from s_prev.
-template <int NT>
-__device__ __forceinline__ void put_tile_total(const KArgs &a, int64_t tile, const uint32_t *part) {
-    uint64_t m = 0, i = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; w++) {
-        m += part[w] >> 16;
-        i += part[w] & 0xFFFFu;
-    }
-    *gbl(a.tile_state + tile) = (m << 31) | i;
+// Scan pass (Table 2 waveform-sum and threshold rows): one flag bit per
+// sample, and the FlagSum of every tile. A work-group takes a tile of
+// kScanTile = 512 samples of every channel: each wave sums the rows of its slice
+// of ceil(C / 4) channels, 8 samples per lane, the slices meet in LDS, and each
+// wave's ballot is one 64-bit flag word. Nothing outside the tile is read
+// (windows are the later passes' business), tiles start on whole 128-byte lines
+// when the rows do, and a wave has up to kScanRows rows in flight at once.
+//
+// PED: the work-group computes its fill's pedestals too (fills with at most
+// kScanPed pedestal samples), each wave those of its own slice, loaded ahead
+// of the rows so that they cost no wait of their own; the fill's first tile
+// writes them out. Otherwise k_prepare has done both. STREAM: non-temporal row
+// loads.
+//
+// Bound by HBM: 2 C bytes a sample, each read once. 16 fills of 54 x 560,000
+// (967.7 MB): 141.9 us, 6.8 TB/s; one fill: 13.3 us. Tiles of 4,096 samples
+// with a halo, every wave summing all rows with 9 in flight, took 156 and 17.0
+// us (139 work-groups for a fill, 1.05 times the bytes). Eight waves of 7 rows:
+// 138.9 and 12.6 us with the pedestals in a kernel of their own, which takes 5
+// to 6.6 us, but 183 and 16.8 us with them (the waves need 86 registers then,
+// and two work-groups of eight fill a CU).
+
+// Constant-memory view of a descriptor: uniform reads become scalar loads.
+#define DAQ_CONST __attribute__((address_space(4)))
+__device__ __forceinline__ const DAQ_CONST FillDev *fill_const(const KArgs &a, int f) {
+    return (const DAQ_CONST FillDev *)(a.table + f);
 }
 
-template <int NT, int R, bool Q = false>
-__device__ __forceinline__ void scan_pass_tile(const KArgs &a, const FillDev &fd, int32_t thr_eff, int64_t tile,
-                                               uint8_t *lds, int64_t ped_total, uint32_t *s_part,
-                                               int64_t prev_tile, const uint32_t *s_prev) {
+// The last fill whose base is <= x: 64 bases per load, no chain of loads.
+// Executed by whole waves, x the same in every lane.
+__device__ __forceinline__ int fill_of(const int64_t *bases, int nf, int64_t x) {
     const int lane = threadIdx.x & 63;
-    const ChopGeom<NT> q(fd, tile);
-    const uint32_t m10 = tile_mask10<NT, R, Q>(fd, q, thr_eff, lds, stream_loads(a), ped_total);
-    if (threadIdx.x == 0 && prev_tile >= 0) put_tile_total<NT>(a, prev_tile, s_prev);
-    if (q.owner) {
-        // the owned samples' mask byte: t0 is a multiple of 8
-        const int64_t byte = (q.t0 >> 3) + (q.g - fd.gl);
-        *gbl(fd.mbits + byte) = (uint8_t)((m10 >> 1) & 0xFFu);
+    int before = 0;
+    for (int f0 = 0; f0 < nf; f0 += 64) {
+        const bool le = f0 + lane < nf && *gbl(bases + f0 + lane) <= x;
+        const uint64_t b = __ballot(le);
+        before += __popcll(b);
+        if (~b) break;
     }
-    const uint32_t mm = (m10 >> 1) & 0xFFu;
-    const uint32_t rise = mm & ~(((mm << 1) | (m10 & 1u)) & 0xFFu);
-    // the wave's totals (island samples, islands begun)
-    uint32_t mine = ((uint32_t)__popc(mm) << 16) | (uint32_t)__popc(rise);
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) mine += __shfl_xor(mine, d, 64);
-    if (lane == 0) s_part[threadIdx.x >> 6] = mine;
+    return __builtin_amdgcn_readfirstlane(before - 1);
 }
 
-// PED: the work-group computes the pedestals of each fill it meets (the
-// first min(Np, N) samples of every row, from L2 after the first reader) and
-// the tile-0 work-group writes them out; the mask guards are cleared by the
-// fill's first and last tiles. Otherwise k_prepare has done both.
-template <int NT, int R, bool Q = false, bool PED = false>
-__global__ void __launch_bounds__(NT) k_scan_pass(KArgs a) {
-    // two bitmaps, used by alternate tiles: a wave still reading one tile's
-    // bitmap never meets the next tile's writes, so tiles need no closing
-    // barrier (the next-but-one tile's writes come after a barrier every
-    // wave has passed)
-    __shared__ __align__(16) uint8_t s_lds[2][ChopLds<NT>::kBitsBytes];
-    __shared__ int64_t s_base[kLdsFills];
-    __shared__ uint32_t s_part[2][NT / 64];
-    __shared__ long long s_acc[kPedChannels];
-    __shared__ long long s_ped;
+// x smeared upwards by `up` samples (0 .. 63).
+__device__ __forceinline__ uint64_t smear_up(uint64_t x, int up) {
+    int have = 1;  // shifts 0 .. have - 1 are in
+    while (2 * have <= up + 1) {
+        x |= x << have;
+        have *= 2;
+    }
+    if (have < up + 1) x |= x << (up + 1 - have);
+    return x;
+}
+
+// What a flag word's neighbours see: `y` marks the samples less than gap after
+// one of the word's flags, `start` the flags with none of the word's flags in
+// the gap samples before them.
+struct WordEdges {
+    uint64_t y, start;
+};
+__device__ __forceinline__ WordEdges word_edges(uint64_t x, int32_t gap) {
+    WordEdges e;
+    e.y = smear_up(x, gap - 1 < 63 ? gap - 1 : 63);
+    e.start = x & ~(e.y << 1);
+    return e;
+}
+
+// The FlagSum of flag word x whose first sample is ws.
+__device__ __forceinline__ FlagSum word_sum(uint64_t x, int32_t ws, int32_t gap) {
+    FlagSum s{-1, -1, -1, 0, 0};
+    if (x) {
+        const WordEdges e = word_edges(x, gap);
+        const int hi = 63 - __clzll((long long)x);
+        s.first = ws + __ffsll((unsigned long long)x) - 1;
+        s.last = ws + hi;
+        s.begin = ws + 63 - __clzll((long long)e.start);
+        s.len = __popcll(e.y & ((1ull << hi) - 1ull));
+        s.cnt = __popcll(e.start) - 1;
+    }
+    return s;
+}
+
+// a, then b to its right.
+__device__ __forceinline__ FlagSum add_sums(const FlagSum a, const FlagSum b, int32_t gap) {
+    const bool ea = a.first < 0, eb = b.first < 0;
+    const int32_t dist = b.first - a.last;
+    const bool apart = dist > gap;
+    FlagSum r;
+    r.first = ea ? b.first : a.first;
+    r.last = eb ? a.last : b.last;
+    r.begin = (ea || (!eb && (b.cnt > 0 || apart))) ? b.begin : a.begin;
+    r.len = a.len + b.len + (ea || eb ? 0 : (apart ? gap : dist));
+    r.cnt = a.cnt + b.cnt + (!ea && !eb && apart ? 1 : 0);
+    return r;
+}
+
+// Lane moves in the vector ALU (DPP), `none` where a lane has no source. The
+// empty asm keeps the move apart from the arithmetic that uses it: a row shift
+// folded into a reverse subtract gave wrong differences on gfx950.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int32_t dpp_move(int32_t v, int32_t none) {
+    int32_t r = __builtin_amdgcn_update_dpp(none, v, CTRL, ROWS, 0xF, false);
+    asm("" : "+v"(r));
+    return r;
+}
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ FlagSum dpp_sum(const FlagSum s) {
+    return FlagSum{dpp_move<CTRL, ROWS>(s.first, -1), dpp_move<CTRL, ROWS>(s.last, -1),
+                   dpp_move<CTRL, ROWS>(s.begin, -1), dpp_move<CTRL, ROWS>(s.len, 0), dpp_move<CTRL, ROWS>(s.cnt, 0)};
+}
+constexpr int kDppShr = 0x110, kDppShl = 0x100;  // + lanes, within rows of 16
+constexpr int kDppPrev = 0x138;                  // the lane before, over the whole wave
+constexpr int kDppRow = 0x142, kDppHalf = 0x143;  // last lane of the row, of the half before
+
+// Inclusive scan over the wave's lanes.
+__device__ __forceinline__ FlagSum scan_sums(FlagSum s, int32_t gap) {
+    s = add_sums(dpp_sum<kDppShr + 1>(s), s, gap);
+    s = add_sums(dpp_sum<kDppShr + 2>(s), s, gap);
+    s = add_sums(dpp_sum<kDppShr + 4>(s), s, gap);
+    s = add_sums(dpp_sum<kDppShr + 8>(s), s, gap);
+    s = add_sums(dpp_sum<kDppRow, 0xA>(s), s, gap);
+    s = add_sums(dpp_sum<kDppHalf, 0xC>(s), s, gap);
+    return s;
+}
+
+// Inclusive scan within each 8 lanes.
+__device__ __forceinline__ FlagSum scan8_sums(FlagSum s, int32_t gap, int lane) {
+    FlagSum o = dpp_sum<kDppShr + 1>(s);
+    if ((lane & 7) >= 1) s = add_sums(o, s, gap);
+    o = dpp_sum<kDppShr + 2>(s);
+    if ((lane & 7) >= 2) s = add_sums(o, s, gap);
+    o = dpp_sum<kDppShr + 4>(s);
+    if ((lane & 7) >= 4) s = add_sums(o, s, gap);
+    return s;
+}
+
+__device__ __forceinline__ FlagSum lane_sum(const FlagSum s, int lane) {
+    return FlagSum{__builtin_amdgcn_readlane(s.first, lane), __builtin_amdgcn_readlane(s.last, lane),
+                   __builtin_amdgcn_readlane(s.begin, lane), __builtin_amdgcn_readlane(s.len, lane),
+                   __builtin_amdgcn_readlane(s.cnt, lane)};
+}
+
+constexpr FlagSum kNoFlags{-1, -1, -1, 0, 0};
+
+// The FlagSum of eight consecutive flag words, held by lanes 0 .. 7 of a wave
+// (lane 0 gets it; the other lanes hold zeros).
+__device__ __forceinline__ FlagSum tile_sum(uint64_t x, int32_t ws, int32_t gap) {
+    FlagSum s = word_sum(x, ws, gap);
+    s = add_sums(s, dpp_sum<kDppShl + 1>(s), gap);
+    s = add_sums(s, dpp_sum<kDppShl + 2>(s), gap);
+    return add_sums(s, dpp_sum<kDppShl + 4>(s), gap);
+}
+
+// A tile's FlagSum in 16 bytes (len < 512, cnt < 256).
+__device__ __forceinline__ void store_sum(int4 *p, const FlagSum s) {
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    *(DAQ_GLOBAL i32x4 *)p = i32x4{s.first, s.last, s.begin, (s.len << 16) | s.cnt};
+}
+__device__ __forceinline__ FlagSum load_sum(const int4 *p) {
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    const i32x4 v = *(const DAQ_GLOBAL i32x4 *)p;
+    return FlagSum{v.x, v.y, v.z, v.w >> 16, v.w & 0xFFFF};
+}
+
+// What the scan needs of a fill.
+struct ScanFill {
+    const int16_t *raw;
+    int64_t n, stride;
+    int32_t C, np, thr, gap;  // gap: pre + post + 1
+    uint64_t *flags;
+    int32_t *ped;
+    int64_t tile_base;
+};
+
+// The sum over the 16 lanes of a DPP row (every lane gets it).
+__device__ __forceinline__ int32_t row16_sum(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);   // lanes 1 0 3 2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);   // lanes 2 3 0 1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);  // 7 - i within 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);  // 15 - i within 16
+    return v;
+}
+
+// Pedestal sums of 16 rows at a time: 16 lanes per row, 8 samples per lane,
+// four rows per load.
+struct PedLoads {
+    uint4 v[4];
+};
+__device__ __forceinline__ PedLoads ped_load(const ScanFill &fd, int r0, int r1, int nch, int lane) {
+    PedLoads p;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int r = r0 + 4 * u + (lane >> 4);
+        p.v[u] = make_uint4(0, 0, 0, 0);
+        if (r < r1 && (lane & 15) < nch) p.v[u] = load16(fd.raw + (int64_t)r * fd.stride + (lane & 15) * kVec);
+    }
+    return p;
+}
+
+// The sum of the pedestals of rows [r0, min(r0 + 16, r1)), spread over the
+// lanes (n <= kScanPed samples each, half-up means); writes them when `write`.
+__device__ __forceinline__ int32_t ped_add(const ScanFill &fd, const PedLoads &p, int r0, int r1, int n, bool write,
+                                           int lane) {
+    const int t = (lane & 15) * kVec;
+    int32_t sum = 0;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int r = r0 + 4 * u + (lane >> 4);
+        int32_t s[kVec] = {0, 0, 0, 0, 0, 0, 0, 0};
+        add8(s, p.v[u]);
+        int32_t part = 0;
+#pragma unroll
+        for (int k = 0; k < kVec; k++) part += (t + k < n) ? s[k] : 0;
+        const int32_t num = 2 * row16_sum(part) + n, den = 2 * n;
+        int32_t q = num / den;
+        if (num - q * den < 0) q--;
+        if ((lane & 15) == 0 && r < r1) {
+            sum += q;
+            if (write) *gbl(fd.ped + r) = q;
+        }
+    }
+    return sum;
+}
+
+template <bool PED, bool STREAM>
+__global__ void __launch_bounds__(kScanThreads) k_scan_pass(KArgs a) {
+    constexpr int NW = kScanThreads / 64, R = kScanRows;
+    static_assert(kScanTile == 64 * kVec, "one wave covers a tile");
+    __shared__ __align__(16) int32_t s_sum[NW][kScanTile];
+    __shared__ int32_t s_ped[NW];
+    __shared__ uint64_t s_word[kScanTile / 64];
     const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
     const int64_t total = a.hdr ? a.hdr->total_tiles : a.total_tiles;
-    const bool lds_fills = nf <= kLdsFills;
-    if (lds_fills)
-        for (int i = threadIdx.x; i < nf; i += NT) s_base[i] = tile_base_at(a, i);
-    lds_barrier();
-    FillDev fd{};
-    int cur = -1;
-    int32_t thr_eff = 0;
-    int64_t ped_total = 0;  // Q: the sum of the fill's pedestals
-    int buf = 0;
-    int64_t prev_tile = -1;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto ld = [](const int16_t *q) { return STREAM ? load16_stream(q) : load16(q); };
     const PartRange pr = part_range(a, nf, total);
     for (int64_t tile = pr.tile_lo + blockIdx.x; tile < pr.tile_hi; tile += gridDim.x) {
-        if (cur < 0 || tile < fd.tile_base || tile >= fd.tile_base + fd.n_tiles) {
-            int lo = 0, hi = nf - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if ((lds_fills ? s_base[mid] : tile_base_at(a, mid)) <= tile) lo = mid;
-                else hi = mid - 1;
+        ScanFill fd;
+        int64_t te = 0;
+        if (a.table) {
+            const int f = fill_of(a.tile_bases, nf, tile);
+            const DAQ_CONST FillDev *d = fill_const(a, f);
+            fd = ScanFill{d->raw, d->n, d->stride, d->C, d->np, d->thr, d->pre + d->post + 1, d->flags, d->ped,
+                          d->tile_base};
+            if (!PED) te = *gbl(a.thr_eff + f);
+        } else {
+            fd = ScanFill{a.one.raw, a.one.n, a.one.stride, a.one.C, a.one.np, a.one.thr, a.one.pre + a.one.post + 1,
+                          a.one.flags, a.one.ped, 0};
+            if (!PED) te = *gbl(a.thr_eff);
+        }
+        const int64_t lt = tile - fd.tile_base;
+        if (lt * kScanTile >= fd.n) continue;  // padding up to a whole group of tiles
+        const int64_t p = lt * kScanTile + lane * kVec;  // this lane's first sample
+        const int slice = (fd.C + NW - 1) / NW;
+        const int c0 = wid * slice;
+        const int c1 = c0 + slice < fd.C ? c0 + slice : fd.C;
+        const int n_ped = fd.n < (int64_t)fd.np ? (int)fd.n : fd.np;
+        const int nch = (n_ped + kVec - 1) / kVec;
+        PedLoads pl;
+        if constexpr (PED) pl = ped_load(fd, c0, c1, nch, lane);
+        // the rows of the slice, R in flight
+        int32_t s[kVec] = {0, 0, 0, 0, 0, 0, 0, 0};
+        const int16_t *x = fd.raw + p;
+        uint4 v[R];
+        auto load_round = [&](int c) {
+            if (c + R <= c1) {
+#pragma unroll
+                for (int u = 0; u < R; u++) v[u] = ld(x + (int64_t)(c + u) * fd.stride);
+            } else {
+#pragma unroll
+                for (int u = 0; u < R; u++) {
+                    v[u] = make_uint4(0, 0, 0, 0);
+                    if (c + u < c1) v[u] = ld(x + (int64_t)(c + u) * fd.stride);
+                }
             }
-            fd = fill_at(a, lo);
-            int64_t te;
-            if constexpr (PED) te = (int64_t)fd.thr + fill_pedestals<NT>(fd, tile == fd.tile_base, s_acc, &s_ped);
-            else te = *gbl(a.thr_eff + lo);
-            thr_eff = clamp_thr(te);
-            ped_total = te - (int64_t)fd.thr;
-            cur = lo;
-        }
+        };
+        const bool in = p < fd.n;
+        if (in) load_round(c0);
         if constexpr (PED) {
-            const int64_t lt = tile - fd.tile_base;
-            const int i = (int)threadIdx.x;
-            if (i < kMaskGuard && lt == 0) fd.mbits[i - kMaskGuard] = 0;
-            if (i < kMaskGuard && lt == fd.n_tiles - 1) fd.mbits[fd.n_tiles * fd.tout / kVec + i] = 0;
+            const bool write = lt == 0 && fd.ped != nullptr;
+            int32_t ps = ped_add(fd, pl, c0, c1, n_ped, write, lane);
+            for (int r0 = c0 + 16; r0 < c1; r0 += 16)
+                ps += ped_add(fd, ped_load(fd, r0, c1, nch, lane), r0, c1, n_ped, write, lane);
+            ps += __shfl_xor(ps, 16, 64);
+            ps += __shfl_xor(ps, 32, 64);
+            if (lane == 0) s_ped[wid] = ps;
         }
-        scan_pass_tile<NT, R, Q>(a, fd, thr_eff, tile, s_lds[buf], ped_total, s_part[buf], prev_tile, s_part[buf ^ 1]);
-        prev_tile = tile;
-        buf ^= 1;
+        if (in) {
+#pragma unroll
+            for (int u = 0; u < R; u++) add8(s, v[u]);
+            for (int c = c0 + R; c < c1; c += R) {
+                load_round(c);
+#pragma unroll
+                for (int u = 0; u < R; u++) add8(s, v[u]);
+            }
+        }
+        // lane l's samples 8 l .. 8 l + 3 in the first half of the wave's
+        // row, 8 l + 4 .. 8 l + 7 in the second: 16-byte stores side by side
+        *reinterpret_cast<int4 *>(&s_sum[wid][4 * lane]) = make_int4(s[0], s[1], s[2], s[3]);
+        *reinterpret_cast<int4 *>(&s_sum[wid][kScanTile / 2 + 4 * lane]) = make_int4(s[4], s[5], s[6], s[7]);
+        lds_barrier();
+        if constexpr (PED) {
+            te = fd.thr;
+#pragma unroll
+            for (int w = 0; w < NW; w++) te += s_ped[w];
+        }
+        const int32_t thr_eff = clamp_thr(te);
+#pragma unroll
+        for (int q = (int)threadIdx.x; q < kScanTile; q += NW * 64) {
+            const int i = (q & 4) * (kScanTile / 8) + 4 * (q >> 3) + (q & 3);
+            int32_t sum = 0;
+#pragma unroll
+            for (int w = 0; w < NW; w++) sum += s_sum[w][i];
+            const uint64_t word = __ballot(sum < thr_eff && lt * kScanTile + q < fd.n);
+            if (lane == 0) s_word[q >> 6] = word;
+        }
+        lds_barrier();
+        if (wid == 0) {
+            constexpr int kWords = kScanTile / 64;
+            const int64_t w = lt * kWords + lane;
+            const uint64_t x = lane < kWords ? s_word[lane] : 0ull;
+            if (lane < kWords) *gbl(fd.flags + w) = x;
+            const FlagSum sum = tile_sum(x, (int32_t)((uint32_t)w << 6), fd.gap);
+            if (lane == 0) store_sum(a.sums + tile, sum);
+        }
+        // (the next tile's LDS writes come after barriers that the readers above have passed)
     }
-    lds_barrier();
-    if (threadIdx.x == 0 && prev_tile >= 0) put_tile_total<NT>(a, prev_tile, s_part[buf ^ 1]);
 }
 
 // The run table entries (start, packed offset) of the islands the calling
@@ -1778,149 +1872,216 @@ __device__ __forceinline__ void write_runs(const FillDev &fd, const TileScan &r,
     }
 }
 
-// Edge pass, one tile per wave: the tile's exclusive prefix (the sum of the
-// totals the scan pass wrote for the fill's earlier tiles), island edges from
-// the mask bits, the island records (capacity-limited), the fill's run table
-// (start, offset of every island), for every multiple k of kCopyChunk among
-// the tile's packed positions the island holding packed position k, and, from
-// the fill's last tile, the fill's counts. Lane l takes the tile's
-// owned mask bytes 8l .. 8l + 7 (64 samples); a tile owns at most 512 bytes.
-// Only wave-level scans: no barrier, and a work-group handles NT / 64 tiles
-// at once.
-__device__ __forceinline__ void edge_wave_tile(const KArgs &a, const FillDev &fd, int64_t tile, int lane) {
-    const int64_t lt = tile - fd.tile_base;
-    const int64_t t0 = lt * fd.tout;
-    const int own = (int)(fd.tout / kVec);  // owned mask bytes
-    const uint8_t *mb = fd.mbits + (t0 >> 3);
-    const int b0 = lane * 8;
-    const int nb = own - b0 < 0 ? 0 : (own - b0 < 8 ? own - b0 : 8);  // this lane's bytes
-    // bytes b0 - 2 .. b0 + 13 in one 16-byte load (2-byte aligned: mbits is
-    // 16-byte aligned and a tile owns an even number of bytes). It stays
-    // inside the fill's mask: byte -2 and bytes up to 12 past the last tile's
-    // owned bytes fall in the 16 guard bytes on either side. Byte b0 - 1 is
-    // zero before the fill's first sample, byte b0 + nb after its last.
-    u32x4 w = u32x4{0, 0, 0, 0};
-    if (nb > 0) __builtin_memcpy(&w, (const DAQ_GLOBAL int16_t *)(mb + b0 - 2), 16);
-    // the tile's exclusive prefix: the totals of the fill's earlier tiles
-    // (written by the scan pass), summed by the wave; these loads are issued
-    // with the mask load above, so the two wait together
-    uint64_t pref = 0;
-#pragma unroll 4
-    for (int64_t j = lane; j < lt; j += 64) pref += *gbl(a.tile_state + fd.tile_base + j);
-    pref = wave_sum_u64(pref);
-    uint64_t m = 0;
-    uint32_t prv = 0, nxt = 0;
-    if (nb > 0) {
-        const uint64_t lo = ((uint64_t)w.y << 32) | w.x;   // bytes -2 .. 5
-        const uint64_t hi = ((uint64_t)w.w << 32) | w.z;   // bytes 6 .. 13
-        m = (lo >> 16) | (hi << 48);                       // bytes 0 .. 7
-        if (nb < 8) m &= (1ull << (8 * nb)) - 1ull;
-        prv = (uint32_t)(lo >> 15) & 1u;                   // top bit of byte -1
-        const int nx = nb + 2;                             // byte b0 + nb, 2 .. 10 of the load
-        nxt = (uint32_t)((nx < 8 ? (lo >> (8 * nx)) : (hi >> (8 * (nx - 8)))) & 1u);
-    }
-    const uint64_t rise = m & ~((m << 1) | (uint64_t)prv);
-    const uint64_t fall = nb > 0 ? (m & ~((m >> 1) | ((uint64_t)nxt << (8 * nb - 1)))) : 0ull;
-    const uint32_t cm = (uint32_t)__popcll(m), ci = (uint32_t)__popcll(rise);
-    const uint32_t mine = (cm << 16) | ci;
-    const uint32_t excl = wave_incl_scan_u32(mine, lane) - mine;
-    if (lt == fd.n_tiles - 1 && lane == 0 && fd.counts != nullptr) {
-        // the fill's last tile writes the counts
-        const uint64_t all = pref + *gbl(a.tile_state + tile);
-        const int64_t n_isl = (int64_t)(all & kField);
-        const int64_t tl = (int64_t)((all >> 31) & kField);
-        int32_t status = (n_isl > fd.cap) ? DAQ_STATUS_CAPACITY : 0;
-        if (fd.out != nullptr && tl > fd.out_stride) status |= DAQ_STATUS_OUT_STRIDE;
-        DAQ_GLOBAL daq_counts *cnt = gbl(fd.counts);
-        cnt->n_islands = n_isl;
-        cnt->total_len = tl;
-        cnt->status = status;
-        cnt->reserved = 0;
-    }
-    const int64_t mbase = (int64_t)((pref >> 31) & kField) + (int64_t)(excl >> 16);
-    const int64_t ibase = (int64_t)(pref & kField) + (int64_t)(excl & 0xFFFFu);
-    const int64_t p = t0 + (int64_t)b0 * 8;  // this lane's first sample
-    DAQ_GLOBAL daq_island *isl = gbl(fd.isl);
-    DAQ_GLOBAL int32_t *runs = gbl(fd.runs);
-    const bool copy = fd.out != nullptr;
-    for (uint64_t r = rise; r; r &= r - 1) {
-        const int k = __ffsll((unsigned long long)r) - 1;
-        const uint64_t below = (1ull << k) - 1ull;
-        const int64_t idx = ibase + __popcll(rise & below);
-        const int64_t off = mbase + __popcll(m & below);
-        if (idx < fd.cap) {
-            isl[idx].start = p + k;
-            isl[idx].offset = off;
+// Edge pass (Table 2 pre/post, merge-check and island-array rows): the island
+// records (capacity-limited), the fill's run table (start, offset of every
+// island) and the fill's counts, from the flags and the tiles' FlagSums.
+//
+// Windows never have to be laid over the samples: a flag more than gap = pre +
+// post + 1 after the one before it begins an island, pre samples before
+// itself; the island before it ends post samples after that flag; and the
+// packed samples up to a flag are the sum over the flags before it of min(their
+// distance to the next, gap). Only the fill's ends clip, the first island's
+// window at sample 0 and the last one's at the last sample. So all that a word
+// of flags needs is the FlagSum of what precedes it, and windows of any width
+// cost the same.
+//
+// A work-group takes kGroupTiles tiles, a flag word per thread: its threads add
+// up the summaries of the earlier tiles (at most kSegTiles, a few per thread),
+// then scan their own words. Bound by the latency of one round of loads and
+// two short scans.
+
+// What the later passes need of a fill.
+struct EdgeFill {
+    const uint64_t *flags;
+    int64_t n;
+    int32_t pre, post, C;
+    int64_t sum_base;
+    daq_island *isl;
+    int64_t cap;
+    daq_counts *counts;
+    int32_t *ped;
+    int16_t *out;
+    int64_t out_stride;
+    int32_t *runs;
+};
+template <class D>
+__device__ __forceinline__ EdgeFill edge_fill_of(const D &d) {
+    return EdgeFill{d.flags, d.n, d.pre, d.post, d.C, d.sum_base, d.isl, d.cap, d.counts, d.ped, d.out, d.out_stride,
+                    d.runs};
+}
+__device__ __forceinline__ EdgeFill edge_fill(const KArgs &a, int f) {
+    return a.table ? edge_fill_of(*fill_const(a, f)) : edge_fill_of(a.one);
+}
+
+// The islands that begin in flag word x (first sample ws), with `p` the FlagSum
+// of the fill's earlier flags: begin(index, start, offset, end of the island
+// before it).
+template <class F>
+__device__ __forceinline__ void word_islands(uint64_t x, int32_t ws, const FlagSum &p, int32_t pre, int32_t post,
+                                             F begin) {
+    if (x == 0) return;
+    const int32_t gap = pre + post + 1;
+    const WordEdges e = word_edges(x, gap);
+    const int32_t first = ws + __ffsll((unsigned long long)x) - 1;
+    const bool any = p.first >= 0;
+    const int32_t dist = first - p.last;
+    uint64_t start = e.start;
+    if (any && dist <= gap) start &= start - 1;  // the word's first flag goes on with an island
+    const int32_t at_first = any ? p.len + (dist < gap ? dist : gap) : 0;  // packed samples up to it, unclipped
+    const int32_t f0 = any ? p.first : first;
+    const int32_t clip = pre > f0 ? pre - f0 : 0;
+    int32_t idx = any ? p.cnt + 1 : 0;
+    for (uint64_t r = start; r; r &= r - 1, idx++) {
+        const int b = __ffsll((unsigned long long)r) - 1;
+        const uint64_t below = x & ((1ull << b) - 1ull);
+        int32_t prev = p.last, at = at_first;
+        if (below) {
+            const int pb = 63 - __clzll((long long)below);
+            prev = ws + pb;
+            at += __popcll(e.y & ((1ull << pb) - 1ull)) + gap;
         }
-        if (copy) {
-            runs[2 * idx] = (int32_t)(p + k);
-            runs[2 * idx + 1] = (int32_t)off;
-        }
-    }
-    for (uint64_t f = fall; f; f &= f - 1) {
-        const int k = __ffsll((unsigned long long)f) - 1;
-        const uint64_t upto = k == 63 ? ~0ull : ((2ull << k) - 1ull);
-        const int64_t idx = ibase + __popcll(rise & upto) - 1;
-        if (idx >= 0 && idx < fd.cap) isl[idx].stop = p + k + 1;
-    }
-    if (!copy || cm == 0) return;
-    // at most one multiple of the chunk size among this lane's packed positions
-    const int64_t q = (mbase + kCopyChunk - 1) / kCopyChunk * kCopyChunk;
-    if (q < mbase + cm) {
-        uint64_t bits = m;
-        for (int64_t skip = q - mbase; skip > 0; skip--) bits &= bits - 1;  // drop the lowest set bits
-        const int b = __ffsll((unsigned long long)bits) - 1;
-        const uint64_t upto = b == 63 ? ~0ull : ((2ull << b) - 1ull);
-        *gbl(fd.cmap + q / kCopyChunk) = (int32_t)(ibase + __popcll(rise & upto) - 1);
+        const int32_t s = ws + b - pre;
+        begin(idx, s > 0 ? s : 0, idx ? at - clip : 0, prev + post + 1);
     }
 }
 
-template <int NT>
-__global__ void __launch_bounds__(NT) k_edge_pass(KArgs a) {
-    constexpr int NW = NT / 64;
-    __shared__ int64_t s_base[kLdsFills];
-    __shared__ u32x4 s_fd[kFdLds * kFdWords];
+// Islands and island samples of a fill with FlagSum t.
+struct FillTotals {
+    int64_t n_isl, len;
+};
+__device__ __forceinline__ FillTotals fill_totals(const FlagSum &t, int64_t n, int32_t pre, int32_t post) {
+    if (t.first < 0) return FillTotals{0, 0};
+    const int64_t left = pre > t.first ? pre - t.first : 0;
+    const int64_t over = (int64_t)t.last + post - (n - 1);
+    return FillTotals{(int64_t)t.cnt + 1, (int64_t)t.len + pre + post + 1 - left - (over > 0 ? over : 0)};
+}
+
+// The fill's counts and the end of its last island (one thread).
+__device__ __forceinline__ void put_totals(const EdgeFill &fd, const FlagSum &t) {
+    const FillTotals r = fill_totals(t, fd.n, fd.pre, fd.post);
+    if (r.n_isl > 0 && r.n_isl <= fd.cap) {
+        const int64_t stop = (int64_t)t.last + fd.post + 1;
+        gbl(fd.isl)[r.n_isl - 1].stop = stop < fd.n ? stop : fd.n;
+    }
+    if (fd.counts == nullptr) return;
+    int32_t status = (r.n_isl > fd.cap) ? DAQ_STATUS_CAPACITY : 0;
+    if (fd.out != nullptr && r.len > fd.out_stride) status |= DAQ_STATUS_OUT_STRIDE;
+    DAQ_GLOBAL daq_counts *cnt = gbl(fd.counts);
+    cnt->n_islands = r.n_isl;
+    cnt->total_len = r.len;
+    cnt->status = status;
+    cnt->reserved = 0;
+}
+
+// The record fields known where island idx begins.
+__device__ __forceinline__ void put_begin(const EdgeFill &fd, int32_t idx, int32_t start, int32_t off, int32_t prev_stop) {
+    DAQ_GLOBAL daq_island *isl = gbl(fd.isl);
+    if (idx < fd.cap) {
+        isl[idx].start = start;
+        isl[idx].offset = off;
+    }
+    if (idx > 0 && idx <= fd.cap) isl[idx - 1].stop = prev_stop;
+}
+
+// The FlagSum of m consecutive tiles (packed) or segments, in order: each
+// thread of the NT adds up its share of them, and lane 63 of each wave ends up
+// with the wave's.
+template <int NT, class T>
+__device__ __forceinline__ FlagSum sum_range(const T *p, int m, int32_t gap) {
+    const int c = (m + NT - 1) / NT;
+    const int i0 = (int)threadIdx.x * c;
+    FlagSum s = kNoFlags;
+    for (int i = i0; i < i0 + c && i < m; i++) {
+        if constexpr (sizeof(T) == sizeof(int4)) s = add_sums(s, load_sum(p + i), gap);
+        else s = add_sums(s, FlagSum{p[i].first, p[i].last, p[i].begin, p[i].len, p[i].cnt}, gap);
+    }
+    return m > 0 ? scan_sums(s, gap) : s;
+}
+
+// Where the segment summaries of a fill start: fills share no entry, whatever
+// their lengths.
+__device__ __forceinline__ int64_t seg_at(int64_t sum_base, int f) { return sum_base / kSegTiles + f; }
+
+// FlagSums of the segments of fills of more than kSegTiles tiles.
+__global__ void __launch_bounds__(kEdgeThreads) k_seg_pass(KArgs a) {
+    constexpr int NW = kEdgeThreads / 64;
+    __shared__ FlagSum s_w[NW];
     const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
-    const int64_t total = a.hdr ? a.hdr->total_tiles : a.total_tiles;
-    const bool lds_fills = nf <= kLdsFills;
-    if (lds_fills)
-        for (int i = threadIdx.x; i < nf; i += NT) s_base[i] = tile_base_at(a, i);
-    const bool fd_lds = stage_fills<NT>(a, nf, s_fd);
-    lds_barrier();
+    const int64_t groups = a.hdr ? a.hdr->total_groups : a.total_groups;
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        const int f = a.table ? fill_of(a.sum_bases, nf, g * kGroupTiles) : 0;
+        const EdgeFill fd = edge_fill(a, f);
+        const int64_t t0 = g * kGroupTiles - fd.sum_base;
+        const int64_t tiles = (fd.n + kScanTile - 1) / kScanTile;
+        if (tiles <= kSegTiles || t0 % kSegTiles != 0) continue;
+        const int m = (int)(tiles - t0 < kSegTiles ? tiles - t0 : kSegTiles);
+        const int32_t gap = fd.pre + fd.post + 1;
+        const FlagSum s = sum_range<kEdgeThreads>(a.sums + fd.sum_base + t0, m, gap);
+        if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = s;
+        lds_barrier();
+        if (threadIdx.x == 0) {
+            FlagSum t = kNoFlags;
+            for (int w = 0; w < NW; w++) t = add_sums(t, s_w[w], gap);
+            a.seg_sums[seg_at(fd.sum_base, f) + t0 / kSegTiles] = t;
+        }
+        lds_barrier();
+    }
+}
+
+__global__ void __launch_bounds__(kEdgeThreads) k_edge_pass(KArgs a) {
+    constexpr int NW = kEdgeThreads / 64;
+    __shared__ FlagSum s_seg[NW], s_tiles[NW], s_words[NW];
+    const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
+    const int64_t groups = a.hdr ? a.hdr->total_groups : a.total_groups;
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    FillDev fd{};
-    int cur = -1;
-    const PartRange pr = part_range(a, nf, total);
-    // fills without samples have no tile: their counts and pedestals (all
-    // zero) come from here, each work-group taking some of the fills
-    for (int f = pr.lo + (int)blockIdx.x; f < pr.hi; f += (int)gridDim.x) {
-        const FillDev *fp = a.table ? a.table + f : &a.one;
-        if (fp->n_tiles != 0) continue;
-        daq_counts *cnt = fp->counts;
-        if (threadIdx.x == 0 && cnt != nullptr) {
-            cnt->n_islands = 0;
-            cnt->total_len = 0;
-            cnt->status = 0;
-            cnt->reserved = 0;
+    const PartRange pr = part_range(a, nf, 0);
+    const int64_t lo = pr.lo == 0 ? 0 : (pr.lo < nf ? *gbl(a.sum_bases + pr.lo) / kGroupTiles : groups);
+    const int64_t hi = pr.hi < nf ? *gbl(a.sum_bases + pr.hi) / kGroupTiles : groups;
+    for (int64_t g = lo + blockIdx.x; g < hi; g += gridDim.x) {
+        const int f = a.table ? fill_of(a.sum_bases, nf, g * kGroupTiles) : 0;
+        const EdgeFill fd = edge_fill(a, f);
+        const int64_t t0 = g * kGroupTiles - fd.sum_base;  // the group's first tile in the fill
+        const int64_t tiles = (fd.n + kScanTile - 1) / kScanTile;
+        const int32_t gap = fd.pre + fd.post + 1;
+        const int64_t w = t0 * (kScanTile / 64) + threadIdx.x;
+        const uint64_t x = w < (fd.n + 63) >> 6 ? *gbl(fd.flags + w) : 0ull;
+        const int32_t ws = (int32_t)((uint32_t)w << 6);
+        const int64_t seg = t0 / kSegTiles;
+        const FlagSum before = sum_range<kEdgeThreads>(a.sums + fd.sum_base + seg * kSegTiles, (int)(t0 - seg * kSegTiles), gap);
+        FlagSum segs = kNoFlags;
+        if (seg > 0) segs = sum_range<kEdgeThreads>(a.seg_sums + seg_at(fd.sum_base, f), (int)seg, gap);
+        const FlagSum s = scan_sums(word_sum(x, ws, gap), gap);
+        if (lane == 63) {
+            s_tiles[wid] = before;
+            s_seg[wid] = segs;
+            s_words[wid] = s;
         }
-        int32_t *ped = fp->ped;
-        if (ped != nullptr)
-            for (int c = (int)threadIdx.x; c < fp->C; c += NT) ped[c] = 0;
-    }
-    for (int64_t tile = pr.tile_lo + (int64_t)blockIdx.x * NW + wid; tile < pr.tile_hi;
-         tile += (int64_t)gridDim.x * NW) {
-        if (cur < 0 || tile < fd.tile_base || tile >= fd.tile_base + fd.n_tiles) {
-            int lo = 0, hi = nf - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if ((lds_fills ? s_base[mid] : tile_base_at(a, mid)) <= tile) lo = mid;
-                else hi = mid - 1;
+        lds_barrier();
+        FlagSum p = kNoFlags;
+        if (seg > 0)
+            for (int v = 0; v < NW; v++) p = add_sums(p, s_seg[v], gap);
+#pragma unroll
+        for (int v = 0; v < NW; v++) p = add_sums(p, s_tiles[v], gap);
+        FlagSum all = p;
+#pragma unroll
+        for (int v = 0; v < NW; v++) {
+            if (v == wid) p = all;
+            all = add_sums(all, s_words[v], gap);
+        }
+        p = add_sums(p, dpp_sum<kDppPrev>(s), gap);
+        const bool copy = fd.out != nullptr;
+        word_islands(x, ws, p, fd.pre, fd.post, [&](int32_t idx, int32_t start, int32_t off, int32_t prev_stop) {
+            put_begin(fd, idx, start, off, prev_stop);
+            if (copy) {
+                gbl(fd.runs)[2 * (int64_t)idx] = start;
+                gbl(fd.runs)[2 * (int64_t)idx + 1] = off;
             }
-            fd = fd_lds ? fill_from_lds(s_fd, lo) : fill_at(a, lo);
-            cur = lo;
-        }
-        edge_wave_tile(a, fd, tile, lane);
+        });
+        if (t0 + kGroupTiles >= tiles && threadIdx.x == 0) put_totals(fd, all);
+        if (fd.n == 0 && fd.ped != nullptr)  // no tile wrote them
+            for (int c = (int)threadIdx.x; c < fd.C; c += kEdgeThreads) *gbl(fd.ped + c) = 0;
+        if (g + gridDim.x < hi) lds_barrier();
     }
 }
 
@@ -1963,7 +2124,7 @@ __device__ __forceinline__ void copy_chunk(const FillDev &fd, int64_t k, const C
 // ---- copy pass of the split schedule ----------------------------------------------
 //
 // Writes the packed rows (the chopped islands of every channel) from the run
-// table and chunk map of the edge pass. A work item is one wave's: a fill, a
+// table of the edge pass. A work item is one wave's: a fill, a
 // segment of kCopyChunk = 512 packed positions (one 16-byte word per lane)
 // and a group of kCopyGroup channels. Items are numbered fill by fill; every
 // work-group first computes the items of each fill from its counts (a prefix
@@ -1990,7 +2151,7 @@ __device__ __forceinline__ void copy_chunk(const FillDev &fd, int64_t k, const C
 #endif
 constexpr int kCopyGroup = DAQ_COPY_GROUP;
 constexpr int kCopyU = DAQ_COPY_U;
-constexpr int kSegRuns = kCopyChunk + 3;  // runs touching one segment, and two end marks
+constexpr int kSegRuns = kCopyChunk + 3;  // runs touching one segment, and two words to spare
 static_assert(kCopyChunk == 64 * kVec, "a segment is one 16-byte word per lane");
 
 // Eight consecutive int16 samples from any element address (2-byte
@@ -2000,6 +2161,17 @@ __device__ __forceinline__ uint4 load16u(const int16_t *p) {
     u32x4 v;
     __builtin_memcpy(&v, (const DAQ_GLOBAL int16_t *)p, 16);
     return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// Inclusive maximum over the lanes up to this one (values of at least -1).
+__device__ __forceinline__ int scan_max(int v) {
+    auto up = [](int x, int o) { return x > o ? x : o; };
+    v = up(v, dpp_move<kDppShr + 1>(v, -1));
+    v = up(v, dpp_move<kDppShr + 2>(v, -1));
+    v = up(v, dpp_move<kDppShr + 4>(v, -1));
+    v = up(v, dpp_move<kDppShr + 8>(v, -1));
+    v = up(v, dpp_move<kDppRow, 0xA>(v, -1));
+    return up(v, dpp_move<kDppHalf, 0xC>(v, -1));
 }
 
 // One round of the copy: the source samples of kCopyU channels starting at
@@ -2029,32 +2201,30 @@ __device__ __forceinline__ void copy_store(const FillDev &fd, int c, int c_hi, i
 }
 
 // Packed positions [q0, q0 + m) of channels [c_lo, c_hi) of fill fd; the
-// segment's nrun runs are in st[] / d[] (d relative to q0, d[0] <= 0, end
-// marks at nrun and nrun + 1). Executed by one whole wave. CHECK: the runs come
+// nrun runs that cover it are in st[] / d[] (packed starts d relative to dq,
+// the first one at or before q0; two more words of either may be read).
+// Executed by one whole wave. CHECK: the runs come
 // from a table of the caller's, which may not be one that the library wrote:
 // words whose 16-byte loads would leave the row go sample by sample.
 template <bool CHECK = false>
 __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int m, int c_lo, int c_hi,
-                                             const int32_t *st, const int32_t *d, int32_t *slot, int nrun,
-                                             int lane) {
+                                             const int32_t *st, const int32_t *d, int64_t dq, int32_t *slot,
+                                             int nrun, int lane) {
+    const int rel = (int)(q0 - dq);
     // run of each word's first position
     slot[lane] = -1;
     __builtin_amdgcn_wave_barrier();
     for (int j = lane; j < nrun; j += 64) {
-        const int dj = d[j];
+        const int dj = d[j] - rel;
         const int w = dj <= 0 ? 0 : (dj + kVec - 1) / kVec;
         if (w < 64) atomicMax(&slot[w], j);
     }
     __builtin_amdgcn_wave_barrier();
-    int R = slot[lane];
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-        const int u = __shfl_up(R, s, 64);
-        if (lane >= s) R = R > u ? R : u;
-    }
+    const int R = scan_max(slot[lane]);
     const int pos = kVec * lane;                       // first packed position of this lane's word
     const int valid = m - pos < kVec ? m - pos : kVec;  // positions of the word inside the segment
-    const int d0 = d[R], d1 = d[R + 1], d2 = d[R + 2];
+    const int d0 = d[R] - rel;
+    const int d1 = R + 1 < nrun ? d[R + 1] - rel : 1 << 30, d2 = R + 2 < nrun ? d[R + 2] - rel : 1 << 30;
     const int st0 = st[R], st1 = st[R + 1];
     const bool uniform = (fd.out_stride & 7) == 0 && ((uintptr_t)fd.out & 15u) == 0;
     // kind 0: nothing; 1: one run; 2: two runs; 3: sample by sample
@@ -2100,21 +2270,54 @@ __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int 
             int r = R;
             for (int e = 0; e < valid; e++) {
                 const int q = pos + e;
-                while (r + 1 < nrun && d[r + 1] <= q) r++;
-                orow[q] = *gbl(row + st[r] + (q - d[r]));
+                while (r + 1 < nrun && d[r + 1] - rel <= q) r++;
+                orow[q] = *gbl(row + st[r] + (q - (d[r] - rel)));
             }
         }
     }
 }
 
-constexpr int kCopyFills = kLdsFills;  // fills per window of the item prefix
-
-// Two consecutive int32 words (4-byte aligned) in one 8-byte load.
-__device__ __forceinline__ uint64_t load8_pair(const int32_t *p) {
-    uint64_t v;
-    __builtin_memcpy(&v, (const DAQ_GLOBAL int32_t *)p, 8);
-    return v;
+// The runs of the fill's run table that cover packed positions [q0, q0 + m),
+// into st[] (source start) and d[] (packed start relative to q0); returns their
+// number (at most kSegRuns - 2). 64 probes narrow the
+// table down to 64 entries (once per 4,096 islands), one more load brings
+// these. Executed by one whole wave; n_isl >= 1.
+__device__ __forceinline__ int load_runs(const int32_t *runs, int64_t n_isl, int64_t q0, int m, int32_t *st,
+                                         int32_t *d, int lane) {
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    const DAQ_GLOBAL i32x2 *tab = (const DAQ_GLOBAL i32x2 *)runs;
+    int64_t lo = 0, hi = n_isl;
+    while (hi - lo > 64) {
+        const int64_t step = (hi - lo + 63) >> 6;
+        const int64_t i = lo + lane * step;
+        const bool le = lane == 0 || (i < hi && tab[i].y <= q0);
+        lo += (63 - __clzll((long long)__ballot(le))) * step;
+        hi = hi < lo + step ? hi : lo + step;
+    }
+    int nrun = 0;
+    bool first = true;
+    for (int64_t i0 = lo;; i0 += 64) {
+        const int64_t i = i0 + lane;
+        const bool in = i < n_isl;
+        i32x2 e{0, 0};
+        if (in) e = tab[i];
+        int skip = 0;  // entries before the run that holds q0
+        if (first) skip = 63 - __clzll((long long)__ballot(lane == 0 || (in && e.y <= q0)));
+        const uint64_t upto = __ballot(in && ((first && lane <= skip) || e.y < q0 + m));
+        const int cnt = ~upto == 0 ? 64 : __ffsll((unsigned long long)~upto) - 1;
+        const int j = nrun + lane - skip;
+        if (lane >= skip && lane < cnt && j < kSegRuns - 2) {
+            st[j] = e.x;
+            d[j] = (int32_t)(e.y - q0);
+        }
+        nrun += cnt - skip;
+        first = false;
+        if (cnt < 64 || nrun >= kSegRuns - 2) break;
+    }
+    return nrun < 1 ? 1 : (nrun > kSegRuns - 2 ? kSegRuns - 2 : nrun);
 }
+
+constexpr int kCopyFills = kLdsFills;  // fills per window of the item prefix
 
 template <int NT>
 __global__ void __launch_bounds__(NT) k_copy_pass(KArgs a) {
@@ -2187,32 +2390,201 @@ __global__ void __launch_bounds__(NT) k_copy_pass(KArgs a) {
             const int64_t L = tl < fd.out_stride ? tl : fd.out_stride;
             const int64_t q0 = k * kCopyChunk;
             const int m = (int)(L - q0 < kCopyChunk ? L - q0 : kCopyChunk);
-            // both chunk-map words in one 8-byte load (entry k + 1 exists: the
-            // map has two spare words; 4-byte alignment is enough for it)
-            const uint64_t e = load8_pair(fd.cmap + k);
-            const int i0 = __builtin_amdgcn_readfirstlane((int)(uint32_t)e);
-            const int i1 = q0 + kCopyChunk < tl ? __builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32))
-                                                : (int)n_isl - 1;
-            int nrun = i1 - i0 + 1;  // at most kCopyChunk + 1
-            nrun = nrun < 1 ? 1 : (nrun > kSegRuns - 2 ? kSegRuns - 2 : nrun);
             int32_t *st = s_st[wid];
             int32_t *dd = s_d[wid];
-            for (int j = lane; j < nrun; j += 64) {
-                const DAQ_GLOBAL int32_t *e = gbl(fd.runs + 2 * (int64_t)(i0 + j));
-                st[j] = e[0];
-                dd[j] = (int32_t)((int64_t)e[1] - q0);
-            }
-            if (lane < 2) {
-                st[nrun + lane] = 0;
-                dd[nrun + lane] = 1 << 30;
-            }
+            const int nrun = load_runs(fd.runs, n_isl, q0, m, st, dd, lane);
             __builtin_amdgcn_wave_barrier();
             const int c_lo = cg * kCopyGroup;
             const int c_hi = c_lo + kCopyGroup < fd.C ? c_lo + kCopyGroup : fd.C;
-            copy_segment(fd, q0, m, c_lo, c_hi, st, dd, s_slot[wid], nrun, lane);
+            copy_segment(fd, q0, m, c_lo, c_hi, st, dd, q0, s_slot[wid], nrun, lane);
             __builtin_amdgcn_wave_barrier();
         }
         lds_barrier();  // the next window rewrites s_item
+    }
+}
+
+// ---- edge and copy pass in one, for launches of few fills -------------------------
+//
+// gridDim / n_fills work-groups per fill. Each scans the summaries of all the
+// fill's tiles (at most kSegTiles; a few loads per thread), which gives it the
+// fill's totals and what precedes every tile; takes an equal share of the copy
+// items (segment of 512 packed positions x group of channels); expands the
+// flag words that its segments need into a run table in LDS; writes the records
+// of the islands that begin in segments whose first item is its own; and
+// copies. The run table never goes through memory, and a single fill takes two
+// kernels in place of three: what bounds such a launch is the chain of
+// dependent loads and the kernels' starts and ends, not HBM. Shares are equal
+// per fill, so launches of many fills (of any mix of lengths and islands) are
+// better off with the copy pass's items.
+constexpr int kEmitSegs = 6;  // segments expanded at a time
+constexpr int kEmitRuns = kEmitSegs * kCopyChunk + kScanTile / 2 + 4;  // their runs, those of one tile before them, end marks
+#ifndef DAQ_EMIT_GROUP
+#define DAQ_EMIT_GROUP 3  // channels per item: a lone fill has few segments to share out
+#endif
+constexpr int kEmitGroup = DAQ_EMIT_GROUP;
+
+__global__ void __launch_bounds__(kEmitThreads) k_emit_pass(KArgs a) {
+    constexpr int NT = kEmitThreads, NW = NT / 64;
+    constexpr int kPer = (kSegTiles + NT - 1) / NT;  // tiles per thread
+    __shared__ FlagSum s_wave[NW];
+    __shared__ int32_t s_before[5][kSegTiles];  // the FlagSum of what precedes each tile
+    __shared__ int32_t s_st[kEmitRuns], s_d[kEmitRuns];
+    __shared__ int32_t s_slot[NW][64];
+    __shared__ int32_t s_ta, s_tb, s_nrun;
+    const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W = gridDim.x / nf;
+    const int f = blockIdx.x / W;
+    const int me = blockIdx.x - f * W;
+    const EdgeFill fd = edge_fill(a, f);
+    const int32_t gap = fd.pre + fd.post + 1;
+    const int tiles = (int)((fd.n + kScanTile - 1) / kScanTile);
+    const int per = (tiles + NT - 1) / NT;
+    const int4 *sums = a.sums + fd.sum_base;
+    FlagSum t[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; i++) {
+        const int k = tid * per + i;
+        t[i] = i < per && k < tiles ? load_sum(sums + k) : kNoFlags;
+    }
+    FlagSum s = t[0];
+#pragma unroll
+    for (int i = 1; i < kPer; i++) s = add_sums(s, t[i], gap);
+    s = scan_sums(s, gap);
+    if (lane == 63) s_wave[wid] = s;
+    if (tid == 0) {
+        s_ta = tiles;
+        s_tb = -1;
+        s_nrun = 0;
+    }
+    lds_barrier();
+    static_assert(NW == 8, "the waves' sums are scanned in 8 lanes");
+    const FlagSum waves = scan8_sums(lane < NW ? s_wave[lane] : kNoFlags, gap, lane);
+    const FlagSum all = lane_sum(waves, NW - 1);
+    FlagSum p = wid ? lane_sum(waves, wid - 1) : kNoFlags;
+    p = add_sums(p, dpp_sum<kDppPrev>(s), gap);
+    if (me == 0) {
+        if (tid == 0) put_totals(fd, all);
+        if (fd.n == 0 && fd.ped != nullptr)  // no tile wrote them
+            for (int c = tid; c < fd.C; c += NT) *gbl(fd.ped + c) = 0;
+    }
+    if (all.first < 0) return;
+    // this work-group's items, and the segments they lie in
+    const int32_t len = (int32_t)fill_totals(all, fd.n, fd.pre, fd.post).len;
+    const int32_t clip = fd.pre > all.first ? fd.pre - all.first : 0;
+    const int groups = fd.out != nullptr ? (fd.C + kEmitGroup - 1) / kEmitGroup : 1;
+    const uint32_t items = (uint32_t)((len + kCopyChunk - 1) / kCopyChunk) * (uint32_t)groups;
+    const uint32_t share = (items + W - 1) / W;
+    const uint32_t i_lo = me * share;
+    const uint32_t i_hi = i_lo + share < items ? i_lo + share : items;
+    if (i_lo >= i_hi) return;
+    const int s_lo = (int)(i_lo / (uint32_t)groups), s_hi = (int)((i_hi - 1) / (uint32_t)groups);
+    // first packed position whose records are written here: that of the first
+    // segment that begins among the items
+    const int32_t own_lo = (s_lo + (i_lo > (uint32_t)s_lo * groups ? 1 : 0)) * kCopyChunk;
+    const int32_t L = fd.out == nullptr ? 0 : (len < fd.out_stride ? len : (int32_t)fd.out_stride);
+    FillDev cd{};
+    cd.raw = a.table ? fill_const(a, f)->raw : a.one.raw;
+    cd.stride = a.table ? fill_const(a, f)->stride : a.one.stride;
+    cd.n = fd.n;
+    cd.C = fd.C;
+    cd.out = fd.out;
+    cd.out_stride = fd.out_stride;
+    for (int sw = s_lo; sw <= s_hi; sw += kEmitSegs) {
+        const int se = sw + kEmitSegs - 1 < s_hi ? sw + kEmitSegs - 1 : s_hi;
+        const int32_t q_lo = sw * kCopyChunk, q_hi = (se + 1) * kCopyChunk;
+        // tiles whose flags lie at packed positions q_lo .. q_hi, and what
+        // precedes each tile, for the threads that expand it
+        {
+            FlagSum q = p;
+            int ta = tiles, tb = -1;
+#pragma unroll
+            for (int i = 0; i < kPer; i++) {
+                const int k = tid * per + i;
+                if (i < per && k < tiles && sw == s_lo) {
+                    s_before[0][k] = q.first;
+                    s_before[1][k] = q.last;
+                    s_before[2][k] = q.begin;
+                    s_before[3][k] = q.len;
+                    s_before[4][k] = q.cnt;
+                }
+                if (t[i].first >= 0) {
+                    const int32_t dist = t[i].first - q.last;
+                    const int32_t at = q.first < 0 ? 0 : q.len + (dist < gap ? dist : gap);
+                    q = add_sums(q, t[i], gap);
+                    if ((q_lo == 0 || q.len - clip >= q_lo) && ta == tiles) ta = k;
+                    if (at - clip < q_hi) tb = k;
+                }
+            }
+            const uint64_t ba = __ballot(ta < tiles), bb = __ballot(tb >= 0);
+            if (ba) ta = __builtin_amdgcn_readlane(ta, __ffsll((unsigned long long)ba) - 1);
+            if (bb) tb = __builtin_amdgcn_readlane(tb, 63 - __clzll((long long)bb));
+            if (lane == 0 && ba) atomicMin(&s_ta, ta);
+            if (lane == 0 && bb) atomicMax(&s_tb, tb);
+        }
+        lds_barrier();
+        const int ta = __builtin_amdgcn_readfirstlane(s_ta), tb = __builtin_amdgcn_readfirstlane(s_tb);
+        auto before = [&](int k) {
+            return FlagSum{s_before[0][k], s_before[1][k], s_before[2][k], s_before[3][k], s_before[4][k]};
+        };
+        // the run that is open before them
+        const FlagSum b = ta < tiles ? before(ta) : all;
+        const int32_t idx0 = b.first >= 0 ? b.cnt : 0;
+        if (tid == 0 && b.first >= 0) {
+            const int32_t off = b.len - (b.last - b.begin) - clip;
+            s_st[0] = b.begin > fd.pre ? b.begin - fd.pre : 0;
+            s_d[0] = off > 0 ? off : 0;
+            atomicMax(&s_nrun, 1);
+        }
+        const int words = (tb - ta + 1) * (kScanTile / 64);
+        for (int w0 = 0; w0 < words; w0 += NT) {
+            const int64_t w = (int64_t)ta * (kScanTile / 64) + w0 + tid;
+            const uint64_t x = w0 + tid < words && w < (fd.n + 63) >> 6 ? *gbl(fd.flags + w) : 0ull;
+            const int32_t ws = (int32_t)((uint32_t)w << 6);
+            // the tile's 8 words up to this one, then what precedes the tile
+            const FlagSum o = dpp_sum<kDppPrev>(scan8_sums(word_sum(x, ws, gap), gap, lane));
+            if (x) {
+                FlagSum q = before((int)(w >> 3));
+                if (lane & 7) q = add_sums(q, o, gap);
+                word_islands(x, ws, q, fd.pre, fd.post, [&](int32_t idx, int32_t start, int32_t off, int32_t prev_stop) {
+                    if (off >= q_hi) return;
+                    if (off >= own_lo && off >= q_lo) put_begin(fd, idx, start, off, prev_stop);
+                    const int j = idx - idx0;
+                    if (j < kEmitRuns - 2) {
+                        s_st[j] = start;
+                        s_d[j] = off;
+                        atomicMax(&s_nrun, j + 1);
+                    }
+                });
+            }
+        }
+        lds_barrier();
+        const int nrun = __builtin_amdgcn_readfirstlane(s_nrun);
+        if (fd.out != nullptr) {
+            const uint32_t a_lo = (uint32_t)sw * groups > i_lo ? (uint32_t)sw * groups : i_lo;
+            const uint32_t a_hi = (uint32_t)(se + 1) * groups < i_hi ? (uint32_t)(se + 1) * groups : i_hi;
+            for (uint32_t it = a_lo + wid; it < a_hi; it += NW) {
+                const uint32_t k = it / (uint32_t)groups;
+                const int32_t q0 = (int32_t)k * kCopyChunk;
+                if (q0 >= L) continue;
+                const int m = L - q0 < kCopyChunk ? L - q0 : kCopyChunk;
+                const int c_lo = (int)(it - k * groups) * kEmitGroup;
+                const int c_hi = c_lo + kEmitGroup < fd.C ? c_lo + kEmitGroup : fd.C;
+                copy_segment(cd, q0, m, c_lo, c_hi, s_st, s_d, 0, s_slot[wid], nrun, lane);
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        if (se < s_hi) {  // the next segments
+            lds_barrier();
+            if (tid == 0) {
+                s_ta = tiles;
+                s_tb = -1;
+                s_nrun = 0;
+            }
+            lds_barrier();
+        }
     }
 }
 
@@ -2394,6 +2766,9 @@ __global__ void __launch_bounds__(NT) k_pipe(KArgs a) {
 // fill has an accumulator, to the channel's eight accumulator words minus
 // the channel pedestal (one 32-byte read-modify-write). The pedestal-
 // subtracted column sums of four consecutive threads make one 32-sample bin.
+// When both methods run on one read, the column sums are also compared with
+// the threshold and the flags written for the edge pass, in place of the scan
+// pass.
 
 template <int NT>
 __global__ void __launch_bounds__(NT) k_q_pass(KArgs a) {
@@ -2411,7 +2786,9 @@ __global__ void __launch_bounds__(NT) k_q_pass(KArgs a) {
     FillDev fd{};
     int cur = -1;
     int64_t ped_total = 0;
-    for (int64_t tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    int32_t thr_eff = 0;
+    const PartRange pr = part_range(a, nf, total);
+    for (int64_t tile = pr.tile_lo + blockIdx.x; tile < pr.tile_hi; tile += gridDim.x) {
         if (cur < 0 || tile < fd.tile_base || tile >= fd.tile_base + fd.n_tiles) {
             int lo = 0, hi = nf - 1;
             while (lo < hi) {
@@ -2420,12 +2797,15 @@ __global__ void __launch_bounds__(NT) k_q_pass(KArgs a) {
                 else hi = mid - 1;
             }
             fd = fill_at(a, lo);
-            ped_total = *gbl(a.thr_eff + lo) - (int64_t)fd.thr;  // thr + sum of pedestals
+            const int64_t te = *gbl(a.thr_eff + lo);  // thr + sum of pedestals
+            ped_total = te - (int64_t)fd.thr;
+            thr_eff = clamp_thr(te);
             cur = lo;
         }
         const int64_t p = (tile - fd.tile_base) * fd.tout + (int64_t)tid * kVec;
         const int64_t valid = fd.n - p;  // samples of this thread's group inside the fill
         int64_t gsum = 0;
+        uint32_t fb = 0;
         if (valid > 0) {
             const int nv = valid < kVec ? (int)valid : kVec;
             int32_t s[kVec] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -2472,6 +2852,27 @@ __global__ void __launch_bounds__(NT) k_q_pass(KArgs a) {
             }
 #pragma unroll
             for (int k = 0; k < kVec; k++) gsum += k < nv ? (int64_t)s[k] - ped_total : 0;
+            fb = flags8(s, thr_eff, valid);
+        }
+        // with the T-method on the same read: the group's threshold flags
+        if (fd.flags != nullptr) {
+            // the 8 lanes of a flag word put their bytes together; a wave holds one summary tile
+            const uint32_t sh = 8 * (tid & 3);
+            uint32_t lo = (tid & 4) ? 0u : fb << sh, hi = (tid & 4) ? fb << sh : 0u;
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) {
+                lo |= __shfl_xor(lo, d, 64);
+                hi |= __shfl_xor(hi, d, 64);
+            }
+            const int64_t w = (p >> 6);
+            const uint64_t x = ((uint64_t)hi << 32) | lo;
+            if ((tid & 7) == 0 && p < ((fd.n + 63) & ~63ll)) *gbl(fd.flags + w) = x;
+            const int64_t t512 = __builtin_amdgcn_readfirstlane((int)(p >> 9));
+            // word j from lane 8 j to lane j
+            const uint32_t xl = __shfl((int)lo, 8 * (tid & 7), 64), xh = __shfl((int)hi, 8 * (tid & 7), 64);
+            const uint64_t xs = (tid & 63) < 8 ? ((uint64_t)xh << 32) | xl : 0ull;
+            const FlagSum sum = tile_sum(xs, (int32_t)((uint32_t)(8 * t512 + (tid & 7)) << 6), fd.pre + fd.post + 1);
+            if ((tid & 63) == 0 && t512 * kScanTile < fd.n) store_sum(a.sums + fd.sum_base + t512, sum);
         }
         // one bin = kGroupsPerBin consecutive threads (within one wave)
 #pragma unroll
@@ -2528,19 +2929,13 @@ __global__ void __launch_bounds__(256) k_prepare(KArgs a) {
     __shared__ long long s_ped;
     const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
     const int64_t total = a.hdr ? a.hdr->total_tiles : a.total_tiles;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256)
-        a.tile_state[i] = 0;
+    if (!a.split)  // look-back words
+        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256)
+            a.tile_state[i] = 0;
     if (blockIdx.x == 0 && threadIdx.x < 8) a.ticket[threadIdx.x] = 0;  // dispenser, copy cursor, flags
     for (int f = blockIdx.x; f < nf; f += gridDim.x) {
         const FillDev fd = fill_at(a, f);
         const int64_t ped_sum = fill_pedestals<256>(fd, true, s_acc, &s_ped);
-        if (fd.qsum != nullptr)  // decimated sums built by atomic adds (fused Q-method)
-            for (int64_t i = threadIdx.x; i < (fd.n + kQBin - 1) / kQBin; i += 256) fd.qsum[i] = 0;
-        if (fd.mbits != nullptr && threadIdx.x < 2 * kMaskGuard) {
-            const int64_t nbytes = fd.n_tiles * fd.tout / kVec;
-            const int i = threadIdx.x;
-            fd.mbits[i < kMaskGuard ? i - kMaskGuard : nbytes + (i - kMaskGuard)] = 0;
-        }
         if (threadIdx.x == 0) {
             a.thr_eff[f] = (int64_t)fd.thr + ped_sum;
             if (a.tile_pref) a.tile_pref[f] = 0;  // finished tiles (pipe variant)
@@ -2642,12 +3037,8 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather(GatherArgs g) {
             more = cnt == 64;
         }
         if (nrun <= kSegRuns - 2) {
-            if (lane < 2) {
-                st[nrun + lane] = 0;
-                dd[nrun + lane] = 1 << 30;
-            }
             __builtin_amdgcn_wave_barrier();
-            copy_segment<true>(fd, q0, m, c_lo, c_hi, st, dd, s_slot[wid], nrun, lane);
+            copy_segment<true>(fd, q0, m, c_lo, c_hi, st, dd, q0, s_slot[wid], nrun, lane);
         } else {
             for (int j = lane; j < m; j += 64) {
                 const int64_t pos = q0 + j;
@@ -2698,34 +3089,29 @@ hipError_t launch_chop(const KArgs &a, int threads, int variant, int grid, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const KArgs &a, int threads, int grid, hipStream_t s) {
-    if (a.q_fused) {
-        if (threads == 256) hipLaunchKernelGGL((k_scan_pass<256, DAQ_Q_SCAN_ROWS, true>), dim3(grid), dim3(256), 0, s, a);
-        else if (threads == 512) hipLaunchKernelGGL((k_scan_pass<512, DAQ_Q_SCAN_ROWS, true>), dim3(grid), dim3(512), 0, s, a);
-        else return hipErrorInvalidValue;
-        return hipGetLastError();
-    }
-    // without the Q-method the scan computes the pedestals itself (no k_prepare)
-    if (threads == 256) hipLaunchKernelGGL((k_scan_pass<256, DAQ_SCAN_ROWS, false, true>), dim3(grid), dim3(256), 0, s, a);
-    else if (threads == 512) hipLaunchKernelGGL((k_scan_pass<512, DAQ_SCAN_ROWS, false, true>), dim3(grid), dim3(512), 0, s, a);
-    else return hipErrorInvalidValue;
+hipError_t launch_scan(const KArgs &a, int grid, hipStream_t s) {
+    if (grid < 1) return hipErrorInvalidValue;
+    if (a.ped_scan && a.stream_loads) hipLaunchKernelGGL((k_scan_pass<true, true>), dim3(grid), dim3(kScanThreads), 0, s, a);
+    else if (a.ped_scan) hipLaunchKernelGGL((k_scan_pass<true, false>), dim3(grid), dim3(kScanThreads), 0, s, a);
+    else if (a.stream_loads) hipLaunchKernelGGL((k_scan_pass<false, true>), dim3(grid), dim3(kScanThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_scan_pass<false, false>), dim3(grid), dim3(kScanThreads), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_emit(const KArgs &a, int threads, int edge_grid, int copy_grid, hipStream_t s) {
-    // both passes stride over their work (tiles, copy items), so any grid of
-    // at least one work-group covers the launch
+hipError_t launch_emit(const KArgs &a, int edge_grid, int copy_grid, hipStream_t s) {
+    // both passes stride over their work (groups of tiles, copy items), so any
+    // grid of at least one work-group covers the launch
     const int eg = edge_grid < 1 ? 1 : edge_grid;
     const int cg = copy_grid < 1 ? 1 : copy_grid;
-    if (threads == 256) {
-        hipLaunchKernelGGL((k_edge_pass<256>), dim3(eg), dim3(256), 0, s, a);
-        hipLaunchKernelGGL((k_copy_pass<256>), dim3((int)cg), dim3(256), 0, s, a);
-    } else if (threads == 512) {
-        hipLaunchKernelGGL((k_edge_pass<512>), dim3(eg), dim3(512), 0, s, a);
-        hipLaunchKernelGGL((k_copy_pass<512>), dim3((int)cg), dim3(512), 0, s, a);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    if (a.multi_seg) hipLaunchKernelGGL(k_seg_pass, dim3(eg), dim3(kEdgeThreads), 0, s, a);
+    hipLaunchKernelGGL(k_edge_pass, dim3(eg), dim3(kEdgeThreads), 0, s, a);
+    hipLaunchKernelGGL((k_copy_pass<512>), dim3(cg), dim3(512), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_emit_fused(const KArgs &a, int wgs_per_fill, hipStream_t s) {
+    if (a.n_fills < 1 || a.multi_seg || wgs_per_fill < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_emit_pass, dim3(a.n_fills * wgs_per_fill), dim3(kEmitThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -58,9 +58,14 @@ struct GraphKey {
     int threads = 0, wgs = 0, variant = 0, parts = 0;
     const void *table = nullptr;
     const void *state = nullptr;
+    // split variant: what else the captured launches depend on
+    int64_t tiles = 0;  // the scan's grid
+    const void *sums = nullptr;
+    int stream_loads = 0, ped_scan = 0, multi_seg = 0;
     bool operator==(const GraphKey &o) const {
         return threads == o.threads && wgs == o.wgs && variant == o.variant && parts == o.parts &&
-               table == o.table && state == o.state;
+               table == o.table && state == o.state && tiles == o.tiles && sums == o.sums &&
+               stream_loads == o.stream_loads && ped_scan == o.ped_scan && multi_seg == o.multi_seg;
     }
 };
 
@@ -81,8 +86,12 @@ struct Scratch {
     hipGraphExec_t g_prep = nullptr, g_chop = nullptr;  // the two halves (timed launches)
     hipGraphExec_t g_all = nullptr;                     // both in one graph (untimed launches)
     GraphKey key;
-    uint64_t *tile_pref = nullptr;  // split variant: tile prefixes (tile_cap)
-    uint8_t *mask = nullptr;        // split variant: island-mask bits of all fills
+    uint64_t *tile_pref = nullptr;  // pipe variant: per-fill words (tile_cap)
+    int64_t *bases = nullptr;       // device, inside the hdr allocation: fill_cap tile bases, as many summary bases
+    int4 *sums = nullptr;           // split variant: tile summaries (sum_cap) ..
+    daqk::FlagSum *seg_sums = nullptr;  // .. and segment summaries, in one allocation
+    int64_t sum_cap = 0;
+    uint8_t *mask = nullptr;        // split and pipe variants: flags, run tables and chunk maps of all fills
     int64_t mask_cap = 0;
     int32_t *q_ped = nullptr;       // Q-method: pedestals of fills that have no ped output
     int64_t q_ped_cap = 0;
@@ -176,6 +185,7 @@ void free_scratch(Scratch *s) {
     (void)hipFree(s->thr_eff);
     (void)hipFree(s->hdr);
     (void)hipFree(s->tile_pref);
+    (void)hipFree(s->sums);
     (void)hipFree(s->mask);
     (void)hipFree(s->q_ped);
     (void)hipFree(s->z_gofs);
@@ -195,11 +205,23 @@ Scratch *scratch_for(daq_ctx *ctx, hipStream_t stream) {
     return s;
 }
 
+// Segment summaries that the fills of `groups` groups of tiles can need (a fill
+// takes at least one group).
+int64_t seg_entries(int64_t groups) { return groups / daqk::kSegGroups + groups + 2; }
+
+// Bytes of a descriptor image: the header, the tile and summary bases of `cap`
+// fills, n descriptors.
+size_t desc_bytes(int32_t cap, int32_t n) {
+    return sizeof(BatchHdr) + 2 * (size_t)cap * sizeof(int64_t) + (size_t)n * sizeof(FillDev);
+}
+
 // Grows the scratch of one stream; waits for that stream first because the
 // old buffers may still be in use by queued work or captured graphs.
-int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes) {
+int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes, int64_t groups) {
     if (!s->ticket) HIP_TRY(hipMalloc(&s->ticket, 64));
-    if (tiles <= s->tile_cap && fills <= s->fill_cap && s->ring_host[0] && mask_bytes <= s->mask_cap)
+    const int64_t sums = groups * daqk::kGroupTiles;
+    if (tiles <= s->tile_cap && fills <= s->fill_cap && s->ring_host[0] && mask_bytes <= s->mask_cap &&
+        sums <= s->sum_cap)
         return DAQ_OK;
     HIP_TRY(hipStreamSynchronize(s->stream));
     free_graphs(s);
@@ -216,6 +238,17 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes)
         HIP_TRY(hipMalloc(&s->tile_pref, (size_t)cap * sizeof(uint64_t)));
         s->tile_cap = cap;
     }
+    if (sums > s->sum_cap) {
+        const int64_t cap = std::max<int64_t>(groups + groups / 2, 256);
+        (void)hipFree(s->sums);
+        s->sums = nullptr;
+        s->seg_sums = nullptr;
+        s->sum_cap = 0;
+        HIP_TRY(hipMalloc(&s->sums, (size_t)cap * daqk::kGroupTiles * sizeof(int4) +
+                                        (size_t)seg_entries(cap) * sizeof(daqk::FlagSum)));
+        s->seg_sums = reinterpret_cast<daqk::FlagSum *>(s->sums + cap * daqk::kGroupTiles);
+        s->sum_cap = cap * daqk::kGroupTiles;
+    }
     if (mask_bytes > s->mask_cap) {
         const int64_t cap = std::max<int64_t>(mask_bytes + mask_bytes / 2, 1 << 20);
         (void)hipFree(s->mask);
@@ -225,7 +258,7 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes)
         s->mask_cap = cap;
     }
     if (fills > s->fill_cap || !s->ring_host[0]) {
-        int32_t cap = std::max<int32_t>(fills + fills / 2, 64);
+        int32_t cap = (std::max<int32_t>(fills + fills / 2, 64) + 1) / 2 * 2;
         (void)hipFree(s->thr_eff);
         (void)hipFree(s->hdr);
         s->thr_eff = nullptr;
@@ -233,16 +266,17 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes)
         s->hdr = nullptr;
         s->fill_cap = 0;
         HIP_TRY(hipMalloc(&s->thr_eff, (size_t)cap * sizeof(int64_t)));
-        HIP_TRY(hipMalloc(&s->hdr, sizeof(BatchHdr) + (size_t)cap * sizeof(FillDev)));
-        s->table = reinterpret_cast<FillDev *>(s->hdr + 1);
+        HIP_TRY(hipMalloc(&s->hdr, desc_bytes(cap, cap)));
+        s->bases = reinterpret_cast<int64_t *>(s->hdr + 1);
+        s->table = reinterpret_cast<FillDev *>(s->bases + 2 * (size_t)cap);
         s->last_desc.clear();
         for (int i = 0; i < kRing; i++) {
             if (s->ring_used[i]) HIP_TRY(hipEventSynchronize(s->ring_ev[i]));
             if (s->ring_host[i]) (void)hipHostFree(s->ring_host[i]);
             s->ring_host[i] = nullptr;
             s->ring_used[i] = false;
-            HIP_TRY(hipHostMalloc(&s->ring_host[i], sizeof(BatchHdr) + (size_t)cap * sizeof(FillDev),
-                                  hipHostMallocDefault));
+            HIP_TRY(hipHostMalloc(&s->ring_host[i], desc_bytes(cap, cap), hipHostMallocDefault));
+            std::memset(s->ring_host[i], 0, desc_bytes(cap, cap));  // whole images are compared
             if (!s->ring_ev[i]) HIP_TRY(hipEventCreateWithFlags(&s->ring_ev[i], hipEventDisableTiming));
         }
         s->fill_cap = cap;
@@ -278,22 +312,41 @@ int64_t tiles_of(const daq_fill &f, const daq_schedule &sc) {
     return (f.n_samples + T - 1) / T;
 }
 
-// Scratch of one fill under the split variant: island-mask bits (with
-// guards), the (start, offset) run table for the worst-case island count and
-// the island of every chunk start, each part 16-byte aligned.
+// Tiles of the Q-method's pass: no halo.
+int64_t q_tiles_of(const daq_fill &f, int threads) {
+    const int64_t T = (int64_t)threads * daqk::kVec;
+    return (f.n_samples + T - 1) / T;
+}
+
+// Tile summaries of a fill (split variant), in whole groups; a fill without
+// samples takes a group too (its counts are written there).
+int64_t groups_of(const daq_fill &f) {
+    constexpr int64_t T = (int64_t)daqk::kScanTile * daqk::kGroupTiles;
+    return std::max<int64_t>(1, (f.n_samples + T - 1) / T);
+}
+
+// Scratch of one fill under the split and pipe variants: threshold flags in
+// whole tiles of `tile` samples, the (start, offset) run table for the
+// worst-case island count and, for the pipe variant, the island of every
+// chunk start, each part 16-byte aligned.
 struct SplitLayout {
     int64_t runs = 0, cmap = 0, bytes = 0;
 };
-SplitLayout split_layout_of(const daq_fill &f, const daq_schedule &sc) {
-    const int64_t tout = daqk::tile_shape(f.pre, f.post, f.n_channels, sc.threads, sc.variant).tout;
-    const int64_t data = tiles_of(f, sc) * tout / daqk::kVec;
+SplitLayout split_layout_of(const daq_fill &f, bool pipe) {
     SplitLayout L;
-    L.runs = (data + 2 * daqk::kMaskGuard + 15) / 16 * 16;
+    L.runs = (f.n_samples + daqk::kScanTile - 1) / daqk::kScanTile * daqk::kScanTile / 8;
     const int64_t isl = std::max<int64_t>(daq_max_islands(f.n_samples, f.pre, f.post), 0);
     L.cmap = L.runs + (8 * isl + 15) / 16 * 16;
     const int64_t chunks = (f.n_samples + daqk::kCopyChunk - 1) / daqk::kCopyChunk + 2;
-    L.bytes = L.cmap + (4 * chunks + 15) / 16 * 16;
+    L.bytes = L.cmap + (pipe ? (4 * chunks + 15) / 16 * 16 : 0);
     return L;
+}
+
+// Whether the split variant's scan can compute the pedestals of every fill.
+bool scan_pedestals(const daq_fill *fills, int32_t n) {
+    for (int32_t i = 0; i < n; i++)
+        if (std::min<int64_t>(fills[i].ped_samples, fills[i].n_samples) > daqk::kScanPed) return false;
+    return true;
 }
 
 FillDev make_desc(const daq_fill &f, const daq_fill_out &o, int64_t tile_base, const daq_schedule &sc) {
@@ -346,30 +399,58 @@ int ensure_parts(Scratch *sc, int parts) {
     return DAQ_OK;
 }
 
-// Work-groups of the edge pass: one wave per tile, so no more than the
-// tiles need (tiles < 0: not known, as in a captured graph that may be
-// replayed for any batch its scratch holds), and at most the scan's grid.
-int edge_grid(int grid, int64_t tiles, int threads) {
-    if (tiles < 0) return grid;
-    const int64_t waves = threads / 64;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(grid, (tiles + waves - 1) / waves));
+// Work-groups of the split variant's scan (one per tile) and edge pass (one
+// per group). Both stride over their work, so smaller grids are right too.
+int scan_grid(int64_t tiles) { return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 1 << 22); }
+int edge_grid(int64_t groups) { return (int)std::min<int64_t>(std::max<int64_t>(groups, 1), 1 << 20); }
+
+// A captured launch serves batches of other sizes too (smaller grids stride,
+// the work-groups of larger ones find nothing to do): its grids cover the
+// tiles rounded up to 1, 1.5 or 2 times a power of two.
+int64_t graph_tiles(int64_t tiles) {
+    int64_t p = 1;
+    while (2 * p <= tiles) p *= 2;
+    return tiles == p ? p : (2 * tiles <= 3 * p ? 3 * p / 2 : 2 * p);
+}
+
+// Whether a split launch takes the emit pass in place of the edge and copy
+// passes (the kernel's comment says when that is faster).
+bool emit_fused(const KArgs &a, int32_t n, int parts, int64_t longest) {
+    return a.split && n <= daqk::kEmitFills && parts <= 1 &&
+           longest <= (int64_t)daqk::kSegTiles * daqk::kScanTile;
+}
+
+// The scan of a split launch, or the Q-method's pass in its place.
+int launch_scan_or_q(const daq_ctx *ctx, const KArgs &a, int threads, int64_t tiles, hipStream_t stream) {
+    if (a.q_fused)
+        HIP_TRY(daqk::launch_q(a, threads, (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 8 * (int64_t)ctx->n_cu), stream));
+    else
+        HIP_TRY(daqk::launch_scan(a, scan_grid(tiles), stream));
+    return DAQ_OK;
 }
 
 int launch_main(const daq_ctx *ctx, Scratch *sc, const KArgs &a, const daq_schedule &s, int grid,
-                int64_t tiles, hipStream_t stream) {
+                int64_t tiles, int64_t groups, hipStream_t stream) {
     if (s.variant == daqk::kVariantPipe) {
         HIP_TRY(daqk::launch_pipe(a, s.threads, grid, stream));
         return DAQ_OK;
     }
     if (s.variant == daqk::kVariantSplit) {
         const int parts = (a.table && s.parts > 1) ? std::min(s.parts, daqk::kMaxParts) : 1;
-        const int eg = edge_grid(grid, tiles, s.threads);
+        const int copy_grid = daqk::kCopyWgsPerCu * ctx->n_cu;
         if (parts == 1) {
             KArgs a1 = a;
             a1.part = 0;
             a1.parts = 1;
-            HIP_TRY(daqk::launch_scan(a1, s.threads, grid, stream));
-            HIP_TRY(daqk::launch_emit(a1, s.threads, eg, daqk::kCopyWgsPerCu * ctx->n_cu, stream));
+            const int rc = launch_scan_or_q(ctx, a1, s.threads, tiles, stream);
+            if (rc) return rc;
+            if (a1.fused) {
+                // two work-groups per CU, shared by the fills; fewer where only records are written
+                const int per = a1.copies ? std::max(1, 2 * ctx->n_cu / a1.n_fills) : 16;
+                HIP_TRY(daqk::launch_emit_fused(a1, per, stream));
+                return DAQ_OK;
+            }
+            HIP_TRY(daqk::launch_emit(a1, edge_grid(groups), copy_grid, stream));
             return DAQ_OK;
         }
         // fill group k runs on its own stream; its scan starts when group
@@ -387,25 +468,24 @@ int launch_main(const daq_ctx *ctx, Scratch *sc, const KArgs &a, const daq_sched
                 HIP_TRY(hipStreamWaitEvent(sk, sc->ev_fork, 0));
                 HIP_TRY(hipStreamWaitEvent(sk, sc->ev_scan[k - 1], 0));
             }
-            HIP_TRY(daqk::launch_scan(ak, s.threads, grid, sk));
+            rc = launch_scan_or_q(ctx, ak, s.threads, tiles, sk);
+            if (rc) return rc;
             HIP_TRY(hipEventRecord(sc->ev_scan[k], sk));
-            HIP_TRY(daqk::launch_emit(ak, s.threads, eg, daqk::kCopyWgsPerCu * ctx->n_cu, sk));
+            HIP_TRY(daqk::launch_emit(ak, edge_grid(groups), copy_grid, sk));
             if (k > 0) HIP_TRY(hipEventRecord(sc->ev_join[k], sk));
         }
         for (int k = 1; k < parts; k++) HIP_TRY(hipStreamWaitEvent(stream, sc->ev_join[k], 0));
         return DAQ_OK;
     }
-    (void)ctx;
-    (void)sc;
     HIP_TRY(daqk::launch_chop(a, s.threads, s.variant, grid, stream));
     return DAQ_OK;
 }
 
 // Whether a launch needs k_prepare first: the split schedule's scan computes
-// the pedestals itself unless the Q-method rides along (its bins are cleared
-// by k_prepare).
+// the pedestals itself unless they take too many samples or the Q-method's
+// pass, which needs them in memory, takes its place.
 bool needs_prepare(const daq_schedule &s, const KArgs &a) {
-    return s.variant != daqk::kVariantSplit || a.q_fused != 0;
+    return s.variant != daqk::kVariantSplit || !a.ped_scan;
 }
 
 int prepare_blocks(const KArgs &a, int64_t total_tiles) {
@@ -424,7 +504,7 @@ int launch_pair(daq_ctx *ctx, Scratch *sc, const KArgs &a, int64_t total_tiles, 
         int rc = timing_begin(ctx, stream, &slot);
         if (rc) return rc;
     }
-    int rc = launch_main(ctx, sc, a, s, chop_grid(ctx, s, total_tiles), total_tiles, stream);
+    int rc = launch_main(ctx, sc, a, s, chop_grid(ctx, s, total_tiles), total_tiles, a.total_groups, stream);
     if (rc) return rc;
     if (ctx->timing) return timing_end(ctx, stream, slot);
     return DAQ_OK;
@@ -432,7 +512,7 @@ int launch_pair(daq_ctx *ctx, Scratch *sc, const KArgs &a, int64_t total_tiles, 
 
 // Captures the two kernels of a table-driven launch (sizes read from the
 // device header) into two graph execs bound to this scratch.
-int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc) {
+int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc, const GraphKey &key) {
     free_graphs(s);
     if (!ctx->capture) HIP_TRY(hipStreamCreateWithFlags(&ctx->capture, hipStreamNonBlocking));
     KArgs a{};
@@ -442,6 +522,15 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc) {
     a.ticket = s->ticket;
     a.thr_eff = s->thr_eff;
     a.tile_pref = s->tile_pref;
+    a.tile_bases = s->bases;
+    a.sum_bases = s->bases + s->fill_cap;
+    a.sums = s->sums;
+    a.seg_sums = s->seg_sums;
+    a.split = sc.variant == daqk::kVariantSplit ? 1 : 0;
+    a.stream_loads = key.stream_loads;
+    a.ped_scan = key.ped_scan;
+    a.multi_seg = key.multi_seg;
+    const int64_t groups = (key.tiles + daqk::kGroupTiles - 1) / daqk::kGroupTiles;
     hipGraph_t g = nullptr;
     // graphs never carry the Q-method: only schedules other than the split
     // one need k_prepare
@@ -459,7 +548,7 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc) {
         if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
     }
     HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
-    const int rc0 = launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, -1, ctx->capture);
+    const int rc0 = launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, key.tiles, groups, ctx->capture);
     e2 = hipStreamEndCapture(ctx->capture, &g);
     if (rc0) return rc0;
     if (e2 != hipSuccess) return hip_fail(e2, "hipStreamEndCapture");
@@ -469,7 +558,7 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc) {
     // prepare (if any) and main pass in one graph: one launch, no gap between the two
     HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
     e = prep ? daqk::launch_prepare(a, kPrepareBlocks, ctx->capture) : hipSuccess;
-    const int rc1 = e == hipSuccess ? launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, -1, ctx->capture) : DAQ_OK;
+    const int rc1 = e == hipSuccess ? launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, key.tiles, groups, ctx->capture) : DAQ_OK;
     e2 = hipStreamEndCapture(ctx->capture, &g);
     if (e != hipSuccess) return hip_fail(e, "launch_prepare (capture)");
     if (rc1) return rc1;
@@ -477,27 +566,23 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc) {
     e = hipGraphInstantiate(&s->g_all, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
-    s->key.threads = sc.threads;
-    s->key.wgs = sc.wgs_per_cu;
-    s->key.variant = sc.variant;
-    s->key.parts = sc.parts;
-    s->key.table = s->table;
-    s->key.state = s->tile_state;
+    s->key = key;
     daqlog::say(2, "graphs captured for schedule %d/%d/%d/%d on stream %p", sc.threads, sc.wgs_per_cu, sc.variant,
                 sc.parts, (void *)s->stream);
     return DAQ_OK;
 }
 
-// The fused pass over n fills. n == 1 without `force_table` passes the one
-// descriptor in the kernel arguments; otherwise the descriptors go through a
-// pinned staging slot into the device table (and graphs may be replayed).
+// The chop of n fills. A single fill's descriptor goes in the kernel arguments
+// (batch calls: with the split variant only); otherwise, or with `force_table`,
+// the descriptors go through a pinned staging slot into the device table (and
+// graphs may be replayed).
 int check_q_out(const daq_fill &f, const daq_q_out &o);
 bool q_acc_overlap(const daq_fill *fills, const daq_q_out *outs, int32_t n);
 
 // qouts (optional): the Q-method runs inside the split schedule's scan pass,
 // on the same read of the raw samples (plain launches, no graph).
 int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int32_t n,
-              hipStream_t stream, bool force_table, const daq_q_out *qouts = nullptr) {
+              hipStream_t stream, bool batch, const daq_q_out *qouts = nullptr, bool force_table = false) {
     if (!ctx || n < 0 || (n > 0 && (!fills || !outs))) return DAQ_EINVAL;
     for (int32_t i = 0; i < n; i++) {
         int rc = check_fill(&fills[i]);
@@ -518,27 +603,35 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     // the register variant keeps exactly 54 rows per thread: calls with other
     // channel counts run the re-read variant
     if (sc.variant == daqk::kVariantResident && !all_calorimeters(fills, n)) sc.variant = daqk::kVariantReload;
-    int64_t total = 0, mask_total = 0, max_chunks = 0;
-    std::vector<int64_t> base((size_t)n), moff((size_t)n, -1);
+    int64_t total = 0, mask_total = 0, groups = 0, longest = 0;
+    std::vector<int64_t> base((size_t)n), sbase((size_t)n), moff((size_t)n, -1);
     std::vector<SplitLayout> lay((size_t)n);
+    const int q_threads = sc.threads;  // work-group size of the Q-method's pass
     // the pipe variant uses the split variant's run table and chunk map
     const bool split = sc.variant == daqk::kVariantSplit || sc.variant == daqk::kVariantPipe;
     int64_t raw_bytes = 0;
+    bool copies = false;
     for (int32_t i = 0; i < n; i++) {
+        sbase[(size_t)i] = groups * daqk::kGroupTiles;
+        groups += groups_of(fills[i]);
+        // the split variant's scan numbers its tiles as their summaries
+        if (sc.variant == daqk::kVariantSplit && !qouts) total = sbase[(size_t)i];
         base[(size_t)i] = total;
-        total += tiles_of(fills[i], sc);
+        total += qouts ? q_tiles_of(fills[i], q_threads) : tiles_of(fills[i], sc);
+        longest = std::max(longest, fills[i].n_samples);
+        copies = copies || outs[i].out != nullptr;
         raw_bytes += 2 * (int64_t)fills[i].n_channels * fills[i].n_samples;
         if (split) {
             moff[(size_t)i] = mask_total;
-            lay[(size_t)i] = split_layout_of(fills[i], sc);
+            lay[(size_t)i] = split_layout_of(fills[i], sc.variant == daqk::kVariantPipe);
             mask_total += lay[(size_t)i].bytes;
-            max_chunks = std::max<int64_t>(max_chunks, (fills[i].n_samples + daqk::kCopyChunk - 1) /
-                                                           daqk::kCopyChunk);
         }
     }
     Scratch *s = scratch_for(ctx, stream);
-    // tile words double as per-fill words (pipe variant): at least one per fill
-    int rc = ensure_scratch(s, std::max<int64_t>(total, n), n, mask_total);
+    // one look-back word per tile; they double as per-fill words (pipe
+    // variant): at least one per fill
+    const bool is_split = sc.variant == daqk::kVariantSplit;
+    int rc = ensure_scratch(s, std::max<int64_t>(is_split ? 0 : total, n), n, mask_total, is_split ? groups : 0);
     if (rc) return rc;
     // fused Q-method: the accumulator update needs the pedestals in memory
     std::vector<int64_t> poff((size_t)n, -1);
@@ -561,11 +654,14 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     }
     auto desc = [&](int32_t i) {
         FillDev d = make_desc(fills[i], outs[i], base[(size_t)i], sc);
-        d.mbits = split ? s->mask + moff[(size_t)i] + daqk::kMaskGuard : nullptr;
+        d.sum_base = sbase[(size_t)i];
+        d.flags = split ? reinterpret_cast<uint64_t *>(s->mask + moff[(size_t)i]) : nullptr;
         d.runs = split ? reinterpret_cast<int32_t *>(s->mask + moff[(size_t)i] + lay[(size_t)i].runs) : nullptr;
         d.cmap = split ? reinterpret_cast<int32_t *>(s->mask + moff[(size_t)i] + lay[(size_t)i].cmap) : nullptr;
         if (qouts) {
             const daq_q_out &q = qouts[i];
+            d.tout = (int64_t)q_threads * daqk::kVec;
+            d.n_tiles = q_tiles_of(fills[i], q_threads);
             if (!d.ped) d.ped = q.ped ? q.ped : s->q_ped + poff[(size_t)i];
             d.qsum = q.qsum;
             d.acc = q.acc;
@@ -581,9 +677,16 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     a.n_fills = n;
     a.total_tiles = total;
     a.stream_loads = raw_bytes > kStreamLoadBytes ? 1 : 0;
-    a.copy_slots = split ? max_chunks * n : 0;
+    a.total_groups = groups;
+    a.sums = s->sums;
+    a.seg_sums = s->seg_sums;
     a.q_fused = qouts ? 1 : 0;
-    if (n == 1 && !force_table) {
+    a.split = is_split ? 1 : 0;
+    a.ped_scan = is_split && !qouts && scan_pedestals(fills, n) ? 1 : 0;
+    a.multi_seg = longest > (int64_t)daqk::kSegTiles * daqk::kScanTile ? 1 : 0;
+    a.fused = emit_fused(a, n, sc.parts, longest) ? 1 : 0;
+    a.copies = copies ? 1 : 0;
+    if (n == 1 && !force_table && (!batch || is_split)) {
         a.one = desc(0);
         return launch_pair(ctx, s, a, total, stream, sc);
     }
@@ -592,16 +695,21 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     s->ring_pos = (s->ring_pos + 1) % kRing;
     if (s->ring_used[rs]) HIP_TRY(hipEventSynchronize(s->ring_ev[rs]));
     BatchHdr *h = reinterpret_cast<BatchHdr *>(s->ring_host[rs]);
-    FillDev *tab = reinterpret_cast<FillDev *>(h + 1);
+    int64_t *bases = reinterpret_cast<int64_t *>(h + 1);
+    FillDev *tab = reinterpret_cast<FillDev *>(bases + 2 * (size_t)s->fill_cap);
     h->n_fills = n;
     h->stream_loads = a.stream_loads;
     h->total_tiles = total;
-    h->copy_slots = a.copy_slots;
+    h->total_groups = groups;
     h->pad2 = 0;
-    for (int32_t i = 0; i < n; i++) tab[i] = desc(i);
+    for (int32_t i = 0; i < n; i++) {
+        tab[i] = desc(i);
+        bases[i] = tab[i].tile_base;
+        bases[s->fill_cap + i] = tab[i].sum_base;
+    }
     // one upload of header and table, skipped when the device already holds
     // exactly these bytes (the same batch launched again)
-    const size_t bytes = sizeof(BatchHdr) + (size_t)n * sizeof(FillDev);
+    const size_t bytes = desc_bytes(s->fill_cap, n);
     const uint8_t *img = reinterpret_cast<const uint8_t *>(h);
     if (s->last_desc.size() != bytes || std::memcmp(s->last_desc.data(), img, bytes) != 0) {
         HIP_TRY(hipMemcpyAsync(s->hdr, h, bytes, hipMemcpyHostToDevice, stream));
@@ -611,7 +719,10 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     }
     a.table = s->table;
     a.hdr = s->hdr;
-    const bool use_graph = ctx->graphs && sc.wgs_per_cu > 0 && !qouts;
+    a.tile_bases = s->bases;
+    a.sum_bases = s->bases + s->fill_cap;
+    // two kernels (the emit pass) are cheaper launched than replayed
+    const bool use_graph = ctx->graphs && sc.wgs_per_cu > 0 && !qouts && !a.fused;
     if (!use_graph) return launch_pair(ctx, s, a, total, stream, sc);
     GraphKey want;
     want.threads = sc.threads;
@@ -620,8 +731,15 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     want.parts = sc.parts;
     want.table = s->table;
     want.state = s->tile_state;
+    if (a.split) {
+        want.tiles = graph_tiles(total);
+        want.sums = s->sums;
+        want.stream_loads = a.stream_loads;
+        want.ped_scan = a.ped_scan;
+        want.multi_seg = a.multi_seg;
+    }
     if (!s->g_chop || !(s->key == want)) {
-        rc = capture_graphs(ctx, s, sc);
+        rc = capture_graphs(ctx, s, sc, want);
         if (rc) return rc;
     }
     if (!ctx->timing) {
@@ -821,7 +939,14 @@ std::string shape_key(const daq_ctx *ctx, const daq_fill *fills, int32_t n) {
 // the host that name is only a stand-in for the symbol. Its device address is
 // looked up once per device, at the first daq_ctx_create on it, and kept in
 // g_noalloc_ptr.
-static __device__ __align__(256) uint8_t scratch[DAQ_NOALLOC_SCRATCH_BYTES];
+//
+// The tile summaries have a part of their own behind the documented bytes,
+// three times as large: a call that fits these never needs more. (A group of
+// 16,384 samples takes at most 533 bytes of summaries; a fill takes at least
+// 216 bytes of the rest for its descriptor and words, and over 2,048 for each
+// group after its first.)
+constexpr int64_t kNoAllocSumBytes = DAQ_NOALLOC_SCRATCH_BYTES * 3;
+static __device__ __align__(256) uint8_t scratch[DAQ_NOALLOC_SCRATCH_BYTES + kNoAllocSumBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_noalloc_mu;
@@ -876,6 +1001,7 @@ struct PutDescArgs {
     FillDev d[kPutFills];
     BatchHdr hdr;
     FillDev *dst;      // table entry of d[0]
+    int64_t *tile_bases, *sum_bases;  // entries of d[0]
     BatchHdr *dst_hdr; // written when write_hdr
     int32_t count, write_hdr;
 };
@@ -888,13 +1014,19 @@ __global__ void k_put_descs(PutDescArgs a) {
         const uint4 *src = reinterpret_cast<const uint4 *>(&a.d[0]);
         reinterpret_cast<uint4 *>(a.dst)[i] = src[i];
     }
+    if (i < a.count) {
+        a.tile_bases[i] = a.d[i].tile_base;
+        a.sum_bases[i] = a.d[i].sum_base;
+    }
     if (a.write_hdr && i == 0) *a.dst_hdr = a.hdr;
 }
 
 // Layout of one no-allocation call inside the scratch array (byte offsets).
 struct NoAllocLayout {
-    int64_t ticket = 0, thr_eff = 0, hdr = 0, tile_state = 0, tile_pref = 0, fills = 0, bytes = 0;
-    int64_t total_tiles = 0, max_chunks = 0;
+    int64_t ticket = 0, thr_eff = 0, hdr = 0, fills = 0, bytes = 0;
+    int64_t bases = 0;  // tile bases, then summary bases of the n fills
+    int64_t sums = 0, seg_sums = 0, sum_bytes = 0;  // in the summaries' own part
+    int64_t total_tiles = 0, total_groups = 0;
 };
 
 int64_t up16(int64_t b) { return (b + 15) / 16 * 16; }
@@ -902,13 +1034,15 @@ int64_t up16(int64_t b) { return (b + 15) / 16 * 16; }
 // Validated fills only.
 NoAllocLayout noalloc_layout(const daq_fill *fills, int32_t n, const daq_schedule &sc) {
     NoAllocLayout L;
-    int64_t tiles = 0, per_fill = 0;
+    int64_t groups = 0, per_fill = 0;
     for (int32_t i = 0; i < n; i++) {
-        tiles += tiles_of(fills[i], sc);
-        per_fill += up16(split_layout_of(fills[i], sc).bytes);
-        L.max_chunks = std::max<int64_t>(L.max_chunks, (fills[i].n_samples + daqk::kCopyChunk - 1) / daqk::kCopyChunk);
+        L.total_tiles = groups * daqk::kGroupTiles + tiles_of(fills[i], sc);
+        groups += groups_of(fills[i]);
+        per_fill += up16(split_layout_of(fills[i], false).bytes);
     }
-    L.total_tiles = tiles;
+    L.total_groups = groups;
+    L.seg_sums = groups * daqk::kGroupTiles * (int64_t)sizeof(int4);
+    L.sum_bytes = L.seg_sums + seg_entries(groups) * (int64_t)sizeof(daqk::FlagSum);
     int64_t o = 0;
     L.ticket = o;
     o += 256;
@@ -916,10 +1050,8 @@ NoAllocLayout noalloc_layout(const daq_fill *fills, int32_t n, const daq_schedul
     o = up256(o + 8 * (int64_t)std::max(n, 1));
     L.hdr = o;
     o = up256(o + (int64_t)sizeof(BatchHdr) + (int64_t)n * (int64_t)sizeof(FillDev));
-    L.tile_state = o;
-    o = up256(o + 8 * std::max<int64_t>(tiles, n));
-    L.tile_pref = o;
-    o = up256(o + 8 * std::max<int64_t>(tiles, n));
+    L.bases = o;
+    o = up256(o + 16 * (int64_t)std::max(n, 1));
     L.fills = o;
     o += per_fill;
     L.bytes = o;
@@ -1110,7 +1242,7 @@ int run_qmethod(daq_ctx *ctx, const daq_fill *fills, const daq_q_out *outs, int3
         }
     }
     Scratch *s = scratch_for(ctx, stream);
-    int rc = ensure_scratch(s, std::max<int64_t>(total, n), n, 0);
+    int rc = ensure_scratch(s, std::max<int64_t>(total, n), n, 0, 0);
     if (rc) return rc;
     if (ped_need > s->q_ped_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
@@ -1154,14 +1286,14 @@ int run_qmethod(daq_ctx *ctx, const daq_fill *fills, const daq_q_out *outs, int3
         s->ring_pos = (s->ring_pos + 1) % kRing;
         if (s->ring_used[rs]) HIP_TRY(hipEventSynchronize(s->ring_ev[rs]));
         BatchHdr *h = reinterpret_cast<BatchHdr *>(s->ring_host[rs]);
-        FillDev *tab = reinterpret_cast<FillDev *>(h + 1);
+        FillDev *tab = reinterpret_cast<FillDev *>(reinterpret_cast<int64_t *>(h + 1) + 2 * (size_t)s->fill_cap);
         h->n_fills = n;
         h->stream_loads = a.stream_loads;
         h->total_tiles = total;
-        h->copy_slots = 0;
+        h->total_groups = 0;
         h->pad2 = 0;
         for (int32_t i = 0; i < n; i++) tab[i] = desc(i);
-        const size_t bytes = sizeof(BatchHdr) + (size_t)n * sizeof(FillDev);
+        const size_t bytes = desc_bytes(s->fill_cap, n);
         const uint8_t *img = reinterpret_cast<const uint8_t *>(h);
         if (s->last_desc.size() != bytes || std::memcmp(s->last_desc.data(), img, bytes) != 0) {
             HIP_TRY(hipMemcpyAsync(s->hdr, h, bytes, hipMemcpyHostToDevice, stream));
@@ -1382,7 +1514,7 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
     if (n == 0) return DAQ_OK;
     const daq_schedule sc = noalloc_schedule(ctx);
     const NoAllocLayout L = noalloc_layout(fills, n, sc);
-    if (L.bytes > DAQ_NOALLOC_SCRATCH_BYTES) return DAQ_ERANGE;
+    if (L.bytes > DAQ_NOALLOC_SCRATCH_BYTES || L.sum_bytes > kNoAllocSumBytes) return DAQ_ERANGE;
     DeviceGuard guard(ctx->device);
     uint8_t *base = noalloc_ptr(ctx->device);
     if (!base) return DAQ_EINVAL;
@@ -1394,50 +1526,57 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
     KArgs a{};
     a.table = d_table;
     a.hdr = d_hdr;
-    a.tile_state = reinterpret_cast<uint64_t *>(base + L.tile_state);
     a.ticket = reinterpret_cast<uint32_t *>(base + L.ticket);
     a.thr_eff = reinterpret_cast<int64_t *>(base + L.thr_eff);
-    a.tile_pref = reinterpret_cast<uint64_t *>(base + L.tile_pref);
+    int64_t *d_bases = reinterpret_cast<int64_t *>(base + L.bases);
+    a.tile_bases = d_bases;
+    a.sum_bases = d_bases + n;
+    uint8_t *sum_base_ptr = base + DAQ_NOALLOC_SCRATCH_BYTES;
+    a.sums = reinterpret_cast<int4 *>(sum_base_ptr + L.sums);
+    a.seg_sums = reinterpret_cast<daqk::FlagSum *>(sum_base_ptr + L.seg_sums);
     a.n_fills = n;
     a.total_tiles = L.total_tiles;
     a.stream_loads = raw_bytes > kStreamLoadBytes ? 1 : 0;
-    a.copy_slots = L.max_chunks * n;
+    a.total_groups = L.total_groups;
     a.part = 0;
     a.parts = 1;
+    a.split = 1;
+    a.ped_scan = scan_pedestals(fills, n) ? 1 : 0;
+    int64_t longest = 0;
+    for (int32_t i = 0; i < n; i++) longest = std::max(longest, fills[i].n_samples);
+    a.multi_seg = longest > (int64_t)daqk::kSegTiles * daqk::kScanTile ? 1 : 0;
     // descriptors, kPutFills per launch; the header with the first group
     PutDescArgs put{};
     put.hdr.n_fills = n;
     put.hdr.stream_loads = a.stream_loads;
     put.hdr.total_tiles = L.total_tiles;
-    put.hdr.copy_slots = a.copy_slots;
+    put.hdr.total_groups = L.total_groups;
     put.dst_hdr = d_hdr;
-    int64_t tile_base = 0, foff = L.fills;
+    int64_t groups = 0, foff = L.fills;
     for (int32_t i0 = 0; i0 < n; i0 += kPutFills) {
         put.count = std::min<int32_t>(kPutFills, n - i0);
         put.write_hdr = i0 == 0 ? 1 : 0;
         put.dst = d_table + i0;
+        put.tile_bases = d_bases + i0;
+        put.sum_bases = d_bases + n + i0;
         for (int32_t k = 0; k < put.count; k++) {
             const daq_fill &f = fills[i0 + k];
-            const SplitLayout sl = split_layout_of(f, sc);
-            FillDev d = make_desc(f, outs[i0 + k], tile_base, sc);
-            d.mbits = base + foff + daqk::kMaskGuard;
+            const SplitLayout sl = split_layout_of(f, false);
+            FillDev d = make_desc(f, outs[i0 + k], groups * daqk::kGroupTiles, sc);
+            d.sum_base = d.tile_base;
+            d.flags = reinterpret_cast<uint64_t *>(base + foff);
             d.runs = reinterpret_cast<int32_t *>(base + foff + sl.runs);
-            d.cmap = reinterpret_cast<int32_t *>(base + foff + sl.cmap);
             put.d[k] = d;
-            tile_base += d.n_tiles;
+            groups += groups_of(f);
             foff += up16(sl.bytes);
         }
         hipLaunchKernelGGL(k_put_descs, dim3(1), dim3(kPutFills * sizeof(FillDev) / 16), 0, stream, put);
         HIP_TRY(hipGetLastError());
     }
-    if (L.total_tiles == 0) {  // only counts and pedestals to clear
-        HIP_TRY(daqk::launch_prepare(a, prepare_blocks(a, 0), stream));
-        return DAQ_OK;
-    }
-    const int grid = chop_grid(ctx, sc, L.total_tiles);
-    HIP_TRY(daqk::launch_scan(a, sc.threads, grid, stream));
-    HIP_TRY(daqk::launch_emit(a, sc.threads, edge_grid(grid, L.total_tiles, sc.threads),
-                              daqk::kCopyWgsPerCu * ctx->n_cu, stream));
+    if (!a.ped_scan || L.total_tiles == 0) HIP_TRY(daqk::launch_prepare(a, prepare_blocks(a, L.total_tiles), stream));
+    if (L.total_tiles == 0) return DAQ_OK;  // only counts and pedestals to clear
+    HIP_TRY(daqk::launch_scan(a, scan_grid(L.total_tiles), stream));
+    HIP_TRY(daqk::launch_emit(a, edge_grid(L.total_groups), daqk::kCopyWgsPerCu * ctx->n_cu, stream));
     return DAQ_OK;
 }
 
@@ -1548,9 +1687,8 @@ int daq_autotune(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, 
     // the library's default first: it is the reference every other candidate
     // is compared with. The persistent variant is not on the menu (it never
     // won, and its bounded waits may give up); daq_ctx_set_schedule selects it.
-    const daq_schedule menu[] = {{512, 8, V5, 0},  {256, 16, V5, 0}, {512, 4, V5, 0},  {512, 8, V5, 2},
-                                 {256, 16, V5, 2}, {256, 16, V5, 3}, {256, 16, V5, 4},
-                                 {256, 8, V5, 0},  {256, 8, V5, 2},  {256, 4, V0, 0},
+    const daq_schedule menu[] = {{512, 8, V5, 0},  {256, 16, V5, 0}, {512, 8, V5, 2},  {256, 16, V5, 2},
+                                 {256, 16, V5, 3}, {256, 16, V5, 4}, {256, 4, V0, 0},
                                  {256, 8, V0, 0},  {512, 2, V0, 0},  {256, 2, V2, 0},  {256, 4, V3, 0},
                                  {256, 3, V4, 0},  {128, 8, V0, 0},  {256, 1, V1, 0}};
     for (const daq_schedule &m : menu)
@@ -1567,11 +1705,11 @@ int daq_autotune(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, 
         ctx->sched = cand[k];
         // the descriptor table is staged by the first run; poison through it
         // once it exists, then run again from poisoned outputs
-        rc = run_fused(ctx, fills, outs, n, st, true);  // warm-up (and capture)
+        rc = run_fused(ctx, fills, outs, n, st, true, nullptr, true);  // warm-up (and capture)
         if (rc) break;
         Scratch *s = scratch_for(ctx, st);
         rc = poison_outputs(s, n, st);
-        if (!rc) rc = run_fused(ctx, fills, outs, n, st, true);
+        if (!rc) rc = run_fused(ctx, fills, outs, n, st, true, nullptr, true);
         if (!rc) {
             float ms0 = 0.f;  // untimed: discard the two runs' timings
             rc = daq_ctx_kernel_time(ctx, &ms0);
@@ -1597,7 +1735,7 @@ int daq_autotune(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, 
         constexpr int reps = 10;
         float t[reps];
         for (int r = 0; r < reps && rc == DAQ_OK; r++) {
-            rc = run_fused(ctx, fills, outs, n, st, true);
+            rc = run_fused(ctx, fills, outs, n, st, true, nullptr, true);
             t[r] = 0.f;
             if (!rc) rc = daq_ctx_kernel_time(ctx, &t[r]);
         }
@@ -1622,10 +1760,10 @@ int daq_autotune(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, 
             ctx->graphs = g == 1;
             constexpr int reps = 10;
             float t[reps];
-            rc = run_fused(ctx, fills, outs, n, st, true);  // warm-up (and capture)
+            rc = run_fused(ctx, fills, outs, n, st, true, nullptr, true);  // warm-up (and capture)
             if (!rc) rc = daq_ctx_kernel_time(ctx, &t[0]);
             for (int r = 0; r < reps && rc == DAQ_OK; r++) {
-                rc = run_fused(ctx, fills, outs, n, st, true);
+                rc = run_fused(ctx, fills, outs, n, st, true, nullptr, true);
                 t[r] = 0.f;
                 if (!rc) rc = daq_ctx_kernel_time(ctx, &t[r]);
             }
