@@ -224,24 +224,25 @@ struct ZFillDev {
     int64_t max_len;           // rows hold at most this many samples
     uint32_t *hdr;             // C * ceil(L / 64) block headers
     int64_t *offsets;          // C * ceil(L / 64) payload word offsets, or null
-    int64_t *gofs;             // scratch: payload words of each wave of the grid
     uint32_t *words;
     int64_t cap;               // words that fit
     int64_t *n_words;          // payload words of the whole stream
     int32_t C;
     int32_t pad;
 };
-// Fills per launch (the descriptors travel as kernel arguments), waves per
-// work-group, work-groups per fill (each wave of the pack pass sums the
-// payload sizes of the waves before it: at most kZMaxGrid * kZWaves).
+// Fills per launch (the descriptors travel as kernel arguments, and 16 lanes
+// share the work-groups out), waves per work-group, work-groups per launch
+// (each wave of the pack pass sums the payload sizes of its fill's waves before
+// it).
 constexpr int kZMaxFills = 16;
 constexpr int kZWaves = 4;
 #ifndef DAQ_Z_MAX_GRID
-#define DAQ_Z_MAX_GRID 256
+#define DAQ_Z_MAX_GRID 2048
 #endif
 constexpr int kZMaxGrid = DAQ_Z_MAX_GRID;
 struct ZArgs {
     ZFillDev f[kZMaxFills];
+    int64_t *gofs;  // scratch: payload words of each wave of the grid
     int32_t n;
 };
 hipError_t launch_z(const ZArgs &a, int grid, hipStream_t s);
@@ -260,8 +261,9 @@ struct ZStreamDev {
 };
 struct ZDecArgs {
     ZStreamDev f[kZMaxFills];
+    int32_t wg0[kZMaxFills + 1];  // first work-group of each stream; wg0[n]: the launch's
     int32_t n;
 };
-hipError_t launch_unz(const ZDecArgs &a, int grid, hipStream_t s);
+hipError_t launch_unz(const ZDecArgs &a, hipStream_t s);
 
 }  // namespace daqk

@@ -1371,8 +1371,12 @@ int check_z_fill(const daq_z_fill &z) {
 
 }  // namespace
 
+// Work-groups per CU of a compression or decoding launch, shared by its fills.
 #ifndef DAQ_Z_WGS_PER_CU
-#define DAQ_Z_WGS_PER_CU 8  // compression work-groups per CU, shared by the launch's fills
+#define DAQ_Z_WGS_PER_CU 8
+#endif
+#ifndef DAQ_UNZ_WGS_PER_CU
+#define DAQ_UNZ_WGS_PER_CU 8
 #endif
 
 int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *stream_) {
@@ -1383,20 +1387,17 @@ int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *s
         const int rc = check_z_fill(fills[i]);
         if (rc) return rc;
     }
-    // Work-groups per fill of each launch: the resident count (8 per CU)
-    // shared by its fills, at most kZMaxGrid, fewer for short streams.
+    // Work-groups of each launch: the resident count (8 per CU), fewer for
+    // short streams, at least one for each fill.
     auto grid_of = [&](int32_t i0, int32_t m) {
-        int64_t most = 1;
-        for (int32_t j = 0; j < m; j++) most = std::max(most, z_groups(fills[i0 + j]));
-        const int64_t wide =
-            std::min<int64_t>(daqk::kZMaxGrid, std::max<int64_t>(1, (int64_t)DAQ_Z_WGS_PER_CU * ctx->n_cu / m));
-        return (int)std::max<int64_t>(1, std::min<int64_t>(wide, (most + daqk::kZWaves - 1) / daqk::kZWaves));
+        int64_t groups = 0;
+        for (int32_t j = 0; j < m; j++) groups += z_groups(fills[i0 + j]);
+        const int64_t wide = std::min<int64_t>(daqk::kZMaxGrid, (int64_t)DAQ_Z_WGS_PER_CU * ctx->n_cu);
+        return (int)std::max<int64_t>(m, std::min<int64_t>(wide, m + groups / daqk::kZWaves));
     };
     int64_t need = 0;  // one word per wave of a launch (launches run in stream order)
-    for (int32_t i0 = 0; i0 < n; i0 += daqk::kZMaxFills) {
-        const int32_t m = std::min<int32_t>(n - i0, daqk::kZMaxFills);
-        need = std::max<int64_t>(need, (int64_t)m * grid_of(i0, m) * daqk::kZWaves);
-    }
+    for (int32_t i0 = 0; i0 < n; i0 += daqk::kZMaxFills)
+        need = std::max<int64_t>(need, (int64_t)grid_of(i0, std::min<int32_t>(n - i0, daqk::kZMaxFills)) * daqk::kZWaves);
     DeviceGuard guard(ctx->device);
     Scratch *s = scratch_for(ctx, stream);
     if (need > s->z_gofs_cap) {
@@ -1417,6 +1418,7 @@ int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *s
         daqk::ZArgs a{};
         a.n = std::min<int32_t>(n - i0, daqk::kZMaxFills);
         const int grid = grid_of(i0, a.n);
+        a.gofs = s->z_gofs;
         for (int32_t j = 0; j < a.n; j++) {
             const daq_z_fill &z = fills[i0 + j];
             daqk::ZFillDev &d = a.f[j];
@@ -1426,7 +1428,6 @@ int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *s
             d.max_len = z.max_len;
             d.hdr = z.hdr;
             d.offsets = z.offsets;
-            d.gofs = s->z_gofs + (int64_t)j * grid * daqk::kZWaves;
             d.words = z.words;
             d.cap = z.words_cap;
             d.n_words = z.n_words;
@@ -1437,10 +1438,6 @@ int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *s
     if (ctx->timing) return timing_end(ctx, stream, slot);
     return DAQ_OK;
 }
-
-#ifndef DAQ_UNZ_WGS_PER_CU
-#define DAQ_UNZ_WGS_PER_CU 32  // decoding work-groups per CU, shared by the launch's streams (latency-bound: more in flight)
-#endif
 
 int daq_decompress_batch(daq_ctx *ctx, const daq_z_stream *streams, int32_t n, void *stream_) {
     if (!ctx || n < 0 || (n > 0 && !streams)) return DAQ_EINVAL;
@@ -1459,7 +1456,7 @@ int daq_decompress_batch(daq_ctx *ctx, const daq_z_stream *streams, int32_t n, v
     for (int32_t i0 = 0; i0 < n; i0 += daqk::kZMaxFills) {
         daqk::ZDecArgs a{};
         a.n = std::min<int32_t>(n - i0, daqk::kZMaxFills);
-        int64_t most = 1;
+        int64_t groups[daqk::kZMaxFills], all = 0;
         for (int32_t j = 0; j < a.n; j++) {
             const daq_z_stream &z = streams[i0 + j];
             daqk::ZStreamDev &d = a.f[j];
@@ -1472,11 +1469,15 @@ int daq_decompress_batch(daq_ctx *ctx, const daq_z_stream *streams, int32_t n, v
             d.L = z.n_samples;
             d.C = z.n_channels;
             const int64_t nb = (z.n_samples + DAQ_Z_BLOCK - 1) / DAQ_Z_BLOCK;
-            most = std::max<int64_t>(most, (nb + 7) / 8 * z.n_channels);
+            groups[j] = (nb + 7) / 8 * z.n_channels;
+            all += groups[j];
         }
-        const int64_t wide = std::max<int64_t>(1, (int64_t)DAQ_UNZ_WGS_PER_CU * ctx->n_cu / a.n);
-        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(wide, (most + daqk::kZWaves - 1) / daqk::kZWaves));
-        HIP_TRY(daqk::launch_unz(a, grid, (hipStream_t)stream_));
+        // the launch's work-groups by the streams' groups, at least one each
+        const int64_t wide = std::min<int64_t>((int64_t)DAQ_UNZ_WGS_PER_CU * ctx->n_cu, a.n + all / daqk::kZWaves);
+        const int64_t spare = std::max<int64_t>(wide - a.n, 0);
+        for (int32_t j = 0; j < a.n; j++)
+            a.wg0[j + 1] = a.wg0[j] + 1 + (all ? (int32_t)((double)groups[j] * (double)spare / (double)all) : 0);
+        HIP_TRY(daqk::launch_unz(a, (hipStream_t)stream_));
     }
     return DAQ_OK;
 }
