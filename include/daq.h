@@ -223,9 +223,8 @@ int daq_chop_fill(daq_ctx *ctx, const daq_fill *fill, const daq_fill_out *out,
 
 /* Many independent fills (uneven N, thresholds, windows) in one launch of
  * the context's schedule (by default the split schedule's kernels over every
- * fill), replayed from a captured HIP graph when the context's graphs are on
- * and launched plainly otherwise (and where the split schedule needs only two
- * kernels, for few fills: a replay costs more than they do). Results per
+ * fill, launched plainly; the other schedules' launches are replayed from a
+ * captured HIP graph when the context's graphs are on). Results per
  * fill are identical to daq_chop_fill whatever the schedule. The paper
  * chops each fill as it arrives (Section 3, fills in bursts at 12 Hz);
  * taking several in one launch is this library's addition, for throughput.
@@ -404,7 +403,8 @@ int daq_ctx_set_schedule(daq_ctx *ctx, const daq_schedule *s);
 int daq_ctx_get_schedule(daq_ctx *ctx, daq_schedule *s);
 
 /* Use captured HIP graphs for daq_process_batch (default on; daq_autotune
- * may switch it). daq_ctx_get_graphs writes the current mode (0 or 1). */
+ * may switch it) in the schedules that replay them, all but the split one.
+ * daq_ctx_get_graphs writes the current mode (0 or 1). */
 int daq_ctx_set_graphs(daq_ctx *ctx, int enable);
 int daq_ctx_get_graphs(daq_ctx *ctx, int *enable);
 

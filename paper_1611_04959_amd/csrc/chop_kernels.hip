@@ -2924,7 +2924,32 @@ __global__ void __launch_bounds__(256) k_unpack12(const uint8_t *in, int64_t in_
 // Effective thresholds (thr + the sum of the pedestals), pedestals, cleared
 // look-back words and counts, for the schedules whose scan does not compute
 // pedestals itself. A block handles whole fills.
+// Fills with at most kScanPed pedestal samples: as in the scan, each wave those
+// of a quarter of the channels, all loads of 16 rows in flight (a fill's
+// pedestals took 6.5 us as items of 8 samples added up by LDS atomics).
+__device__ int64_t short_pedestals(const FillDev &fd, int32_t *s_sum) {
+    constexpr int NW = 256 / 64;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = fd.n < (int64_t)fd.np ? (int)fd.n : fd.np;
+    const int nch = (n + kVec - 1) / kVec;
+    const int slice = (fd.C + NW - 1) / NW;
+    const int c0 = wid * slice, c1 = c0 + slice < fd.C ? c0 + slice : fd.C;
+    const ScanFill sf{fd.raw, fd.n, fd.stride, fd.C, fd.np, fd.thr, 0, nullptr, fd.ped, 0};
+    int32_t sum = 0;
+    for (int r0 = c0; r0 < c1; r0 += 16)
+        sum += ped_add(sf, ped_load(sf, r0, c1, nch, lane), r0, c1, n, fd.ped != nullptr, lane);
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    if (lane == 0) s_sum[wid] = sum;
+    __syncthreads();
+    int64_t all = 0;
+    for (int w = 0; w < NW; w++) all += s_sum[w];
+    return all;
+}
+
 __global__ void __launch_bounds__(256) k_prepare(KArgs a) {
+    __shared__ int32_t s_sum[4];
     __shared__ long long s_acc[kPedChannels];
     __shared__ long long s_ped;
     const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
@@ -2935,7 +2960,8 @@ __global__ void __launch_bounds__(256) k_prepare(KArgs a) {
     if (blockIdx.x == 0 && threadIdx.x < 8) a.ticket[threadIdx.x] = 0;  // dispenser, copy cursor, flags
     for (int f = blockIdx.x; f < nf; f += gridDim.x) {
         const FillDev fd = fill_at(a, f);
-        const int64_t ped_sum = fill_pedestals<256>(fd, true, s_acc, &s_ped);
+        const bool is_short = fd.n > 0 && (fd.n < (int64_t)fd.np ? fd.n : (int64_t)fd.np) <= kScanPed;
+        const int64_t ped_sum = is_short ? short_pedestals(fd, s_sum) : fill_pedestals<256>(fd, true, s_acc, &s_ped);
         if (threadIdx.x == 0) {
             a.thr_eff[f] = (int64_t)fd.thr + ped_sum;
             if (a.tile_pref) a.tile_pref[f] = 0;  // finished tiles (pipe variant)

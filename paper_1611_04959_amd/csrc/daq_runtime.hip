@@ -44,7 +44,7 @@ int hip_fail(hipError_t e, const char *what = "a HIP call") {
         if (e_ != hipSuccess) return hip_fail(e_, #expr); \
     } while (0)
 
-constexpr int kRing = 4;          // pinned staging slots per stream
+constexpr int kRing = 16;         // pinned staging slots per stream, an event per half
 // Launches reading more raw bytes than this stream them with non-temporal
 // loads; smaller ones keep their rows cached for the island write-out (the
 // last-level cache holds 256 MB).
@@ -58,14 +58,9 @@ struct GraphKey {
     int threads = 0, wgs = 0, variant = 0, parts = 0;
     const void *table = nullptr;
     const void *state = nullptr;
-    // split variant: what else the captured launches depend on
-    int64_t tiles = 0;  // the scan's grid
-    const void *sums = nullptr;
-    int stream_loads = 0, ped_scan = 0, multi_seg = 0;
     bool operator==(const GraphKey &o) const {
         return threads == o.threads && wgs == o.wgs && variant == o.variant && parts == o.parts &&
-               table == o.table && state == o.state && tiles == o.tiles && sums == o.sums &&
-               stream_loads == o.stream_loads && ped_scan == o.ped_scan && multi_seg == o.multi_seg;
+               table == o.table && state == o.state;
     }
 };
 
@@ -77,11 +72,11 @@ struct Scratch {
     int64_t *thr_eff = nullptr;
     BatchHdr *hdr = nullptr;    // device: the header, then the table (one upload)
     FillDev *table = nullptr;   // device, inside the hdr allocation
-    std::vector<uint8_t> last_desc;  // bytes of the last uploaded header and table
+    std::vector<uint8_t> last_desc, next_desc;  // descriptor images: on the device, of the call in hand
     int32_t fill_cap = 0;
-    void *ring_host[kRing] = {};
-    hipEvent_t ring_ev[kRing] = {};
-    bool ring_used[kRing] = {};
+    uint8_t *ring_host = nullptr;   // kRing slots of desc_bytes(fill_cap, fill_cap)
+    hipEvent_t ring_ev[2] = {};     // recorded after the last slot of each half of the ring
+    bool ring_used[2] = {};
     int ring_pos = 0;
     hipGraphExec_t g_prep = nullptr, g_chop = nullptr;  // the two halves (timed launches)
     hipGraphExec_t g_all = nullptr;                     // both in one graph (untimed launches)
@@ -189,10 +184,9 @@ void free_scratch(Scratch *s) {
     (void)hipFree(s->mask);
     (void)hipFree(s->q_ped);
     (void)hipFree(s->z_gofs);
-    for (int i = 0; i < kRing; i++) {
-        if (s->ring_ev[i]) (void)hipEventDestroy(s->ring_ev[i]);
-        if (s->ring_host[i]) (void)hipHostFree(s->ring_host[i]);
-    }
+    for (hipEvent_t ev : s->ring_ev)
+        if (ev) (void)hipEventDestroy(ev);
+    if (s->ring_host) (void)hipHostFree(s->ring_host);
     delete s;
 }
 
@@ -220,7 +214,7 @@ size_t desc_bytes(int32_t cap, int32_t n) {
 int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes, int64_t groups) {
     if (!s->ticket) HIP_TRY(hipMalloc(&s->ticket, 64));
     const int64_t sums = groups * daqk::kGroupTiles;
-    if (tiles <= s->tile_cap && fills <= s->fill_cap && s->ring_host[0] && mask_bytes <= s->mask_cap &&
+    if (tiles <= s->tile_cap && fills <= s->fill_cap && s->ring_host && mask_bytes <= s->mask_cap &&
         sums <= s->sum_cap)
         return DAQ_OK;
     HIP_TRY(hipStreamSynchronize(s->stream));
@@ -257,7 +251,7 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes,
         HIP_TRY(hipMalloc(&s->mask, (size_t)cap));
         s->mask_cap = cap;
     }
-    if (fills > s->fill_cap || !s->ring_host[0]) {
+    if (fills > s->fill_cap || !s->ring_host) {
         int32_t cap = (std::max<int32_t>(fills + fills / 2, 64) + 1) / 2 * 2;
         (void)hipFree(s->thr_eff);
         (void)hipFree(s->hdr);
@@ -270,15 +264,14 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes,
         s->bases = reinterpret_cast<int64_t *>(s->hdr + 1);
         s->table = reinterpret_cast<FillDev *>(s->bases + 2 * (size_t)cap);
         s->last_desc.clear();
-        for (int i = 0; i < kRing; i++) {
-            if (s->ring_used[i]) HIP_TRY(hipEventSynchronize(s->ring_ev[i]));
-            if (s->ring_host[i]) (void)hipHostFree(s->ring_host[i]);
-            s->ring_host[i] = nullptr;
-            s->ring_used[i] = false;
-            HIP_TRY(hipHostMalloc(&s->ring_host[i], desc_bytes(cap, cap), hipHostMallocDefault));
-            std::memset(s->ring_host[i], 0, desc_bytes(cap, cap));  // whole images are compared
-            if (!s->ring_ev[i]) HIP_TRY(hipEventCreateWithFlags(&s->ring_ev[i], hipEventDisableTiming));
-        }
+        if (s->ring_host) (void)hipHostFree(s->ring_host);  // the stream is idle: no slot is in use
+        s->ring_host = nullptr;
+        s->ring_pos = 0;
+        s->ring_used[0] = s->ring_used[1] = false;
+        for (hipEvent_t &ev : s->ring_ev)
+            if (!ev) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&s->ring_host), kRing * desc_bytes(cap, cap),
+                              hipHostMallocDefault));
         s->fill_cap = cap;
     }
     return DAQ_OK;
@@ -404,15 +397,6 @@ int ensure_parts(Scratch *sc, int parts) {
 int scan_grid(int64_t tiles) { return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 1 << 22); }
 int edge_grid(int64_t groups) { return (int)std::min<int64_t>(std::max<int64_t>(groups, 1), 1 << 20); }
 
-// A captured launch serves batches of other sizes too (smaller grids stride,
-// the work-groups of larger ones find nothing to do): its grids cover the
-// tiles rounded up to 1, 1.5 or 2 times a power of two.
-int64_t graph_tiles(int64_t tiles) {
-    int64_t p = 1;
-    while (2 * p <= tiles) p *= 2;
-    return tiles == p ? p : (2 * tiles <= 3 * p ? 3 * p / 2 : 2 * p);
-}
-
 // Whether a split launch takes the emit pass in place of the edge and copy
 // passes (the kernel's comment says when that is faster).
 bool emit_fused(const KArgs &a, int32_t n, int parts, int64_t longest) {
@@ -522,18 +506,8 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc, const Graph
     a.ticket = s->ticket;
     a.thr_eff = s->thr_eff;
     a.tile_pref = s->tile_pref;
-    a.tile_bases = s->bases;
-    a.sum_bases = s->bases + s->fill_cap;
-    a.sums = s->sums;
-    a.seg_sums = s->seg_sums;
-    a.split = sc.variant == daqk::kVariantSplit ? 1 : 0;
-    a.stream_loads = key.stream_loads;
-    a.ped_scan = key.ped_scan;
-    a.multi_seg = key.multi_seg;
-    const int64_t groups = (key.tiles + daqk::kGroupTiles - 1) / daqk::kGroupTiles;
     hipGraph_t g = nullptr;
-    // graphs never carry the Q-method: only schedules other than the split
-    // one need k_prepare
+    // (only schedules other than the split one are captured)
     const bool prep = needs_prepare(sc, a);
     hipError_t e = hipSuccess, e2 = hipSuccess;
     if (prep) {
@@ -548,7 +522,7 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc, const Graph
         if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
     }
     HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
-    const int rc0 = launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, key.tiles, groups, ctx->capture);
+    const int rc0 = launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, -1, -1, ctx->capture);
     e2 = hipStreamEndCapture(ctx->capture, &g);
     if (rc0) return rc0;
     if (e2 != hipSuccess) return hip_fail(e2, "hipStreamEndCapture");
@@ -558,7 +532,7 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc, const Graph
     // prepare (if any) and main pass in one graph: one launch, no gap between the two
     HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
     e = prep ? daqk::launch_prepare(a, kPrepareBlocks, ctx->capture) : hipSuccess;
-    const int rc1 = e == hipSuccess ? launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, key.tiles, groups, ctx->capture) : DAQ_OK;
+    const int rc1 = e == hipSuccess ? launch_main(ctx, s, a, sc, sc.wgs_per_cu * ctx->n_cu, -1, -1, ctx->capture) : DAQ_OK;
     e2 = hipStreamEndCapture(ctx->capture, &g);
     if (e != hipSuccess) return hip_fail(e, "launch_prepare (capture)");
     if (rc1) return rc1;
@@ -569,6 +543,96 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc, const Graph
     s->key = key;
     daqlog::say(2, "graphs captured for schedule %d/%d/%d/%d on stream %p", sc.threads, sc.wgs_per_cu, sc.variant,
                 sc.parts, (void *)s->stream);
+    return DAQ_OK;
+}
+
+// Descriptors of up to kPutFills fills travel as kernel arguments into their
+// table (no host staging buffer, no copy call).
+constexpr int kPutFills = 16;
+struct PutDescArgs {
+    FillDev d[kPutFills];
+    BatchHdr hdr;
+    FillDev *dst;      // table entry of d[0]
+    int64_t *tile_bases, *sum_bases;  // entries of d[0]
+    BatchHdr *dst_hdr; // written when write_hdr
+    int32_t count, write_hdr;
+};
+static_assert(sizeof(PutDescArgs) <= 3584, "kernel arguments of the descriptor upload (explicit arguments well below 4 KB)");
+
+__global__ void k_put_descs(PutDescArgs a) {
+    constexpr int W = (int)(sizeof(FillDev) / 16);  // 16-byte words per descriptor
+    const int i = (int)threadIdx.x;
+    if (i < a.count * W) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(&a.d[0]);
+        reinterpret_cast<uint4 *>(a.dst)[i] = src[i];
+    }
+    if (i < a.count) {
+        a.tile_bases[i] = a.d[i].tile_base;
+        a.sum_bases[i] = a.d[i].sum_base;
+    }
+    if (a.write_hdr && i == 0) *a.dst_hdr = a.hdr;
+}
+
+// Larger tables: read from pinned host memory by a kernel of 4 to 5 us. After a
+// copy call in its place the next kernel started 10 us (24 fills) to 21 us (96)
+// later; two launches of the kernel above take 10 us for 24 fills.
+__global__ void __launch_bounds__(256) k_read_descs(const uint4 *src, uint4 *dst, int32_t words) {
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i < words) dst[i] = src[i];
+}
+
+// Puts the header, the bases and the descriptors desc(0 .. n - 1) on the
+// device; skipped when it already holds exactly these bytes (the same batch
+// launched again).
+template <class F>
+int put_table(Scratch *s, const BatchHdr &h, int32_t n, F desc, hipStream_t stream) {
+    const size_t bytes = desc_bytes(s->fill_cap, n);
+    s->next_desc.assign(bytes, 0);
+    BatchHdr *hdr = reinterpret_cast<BatchHdr *>(s->next_desc.data());
+    int64_t *bases = reinterpret_cast<int64_t *>(hdr + 1);
+    FillDev *tab = reinterpret_cast<FillDev *>(bases + 2 * (size_t)s->fill_cap);
+    *hdr = h;
+    for (int32_t i = 0; i < n; i++) {
+        tab[i] = desc(i);
+        bases[i] = tab[i].tile_base;
+        bases[s->fill_cap + i] = tab[i].sum_base;
+    }
+    if (s->last_desc == s->next_desc) return DAQ_OK;
+    s->last_desc.clear();  // whatever happens now, the old image is gone
+    if (n <= kPutFills) {
+        PutDescArgs put{};
+        put.hdr = h;
+        put.dst_hdr = s->hdr;
+        put.count = n;
+        put.write_hdr = 1;
+        put.dst = s->table;
+        put.tile_bases = s->bases;
+        put.sum_bases = s->bases + s->fill_cap;
+        std::memcpy(put.d, tab, (size_t)n * sizeof(FillDev));
+        hipLaunchKernelGGL(k_put_descs, dim3(1), dim3(kPutFills * sizeof(FillDev) / 16), 0, stream, put);
+        HIP_TRY(hipGetLastError());
+    } else {
+        static_assert(sizeof(BatchHdr) % 16 == 0 && sizeof(FillDev) % 16 == 0, "tables are whole 16-byte words");
+        // a slot is free once its half's event has come; an event after each
+        // upload would hold the next kernel back by 6 us
+        const int slot = s->ring_pos, half = slot / (kRing / 2);
+        if (slot % (kRing / 2) == 0 && s->ring_used[half]) {
+            HIP_TRY(hipEventSynchronize(s->ring_ev[half]));
+            s->ring_used[half] = false;
+        }
+        uint8_t *const img = s->ring_host + (size_t)slot * desc_bytes(s->fill_cap, s->fill_cap);
+        std::memcpy(img, s->next_desc.data(), bytes);
+        const int32_t words = (int32_t)(bytes / 16);
+        hipLaunchKernelGGL(k_read_descs, dim3((uint32_t)(words + 255) / 256), dim3(256), 0, stream,
+                           reinterpret_cast<const uint4 *>(img), reinterpret_cast<uint4 *>(s->hdr), words);
+        HIP_TRY(hipGetLastError());
+        if (slot % (kRing / 2) == kRing / 2 - 1) {
+            HIP_TRY(hipEventRecord(s->ring_ev[half], stream));
+            s->ring_used[half] = true;
+        }
+        s->ring_pos = (slot + 1) % kRing;
+    }
+    s->last_desc.swap(s->next_desc);
     return DAQ_OK;
 }
 
@@ -690,39 +754,21 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
         a.one = desc(0);
         return launch_pair(ctx, s, a, total, stream, sc);
     }
-    // stage the descriptors
-    const int rs = s->ring_pos;
-    s->ring_pos = (s->ring_pos + 1) % kRing;
-    if (s->ring_used[rs]) HIP_TRY(hipEventSynchronize(s->ring_ev[rs]));
-    BatchHdr *h = reinterpret_cast<BatchHdr *>(s->ring_host[rs]);
-    int64_t *bases = reinterpret_cast<int64_t *>(h + 1);
-    FillDev *tab = reinterpret_cast<FillDev *>(bases + 2 * (size_t)s->fill_cap);
-    h->n_fills = n;
-    h->stream_loads = a.stream_loads;
-    h->total_tiles = total;
-    h->total_groups = groups;
-    h->pad2 = 0;
-    for (int32_t i = 0; i < n; i++) {
-        tab[i] = desc(i);
-        bases[i] = tab[i].tile_base;
-        bases[s->fill_cap + i] = tab[i].sum_base;
-    }
-    // one upload of header and table, skipped when the device already holds
-    // exactly these bytes (the same batch launched again)
-    const size_t bytes = desc_bytes(s->fill_cap, n);
-    const uint8_t *img = reinterpret_cast<const uint8_t *>(h);
-    if (s->last_desc.size() != bytes || std::memcmp(s->last_desc.data(), img, bytes) != 0) {
-        HIP_TRY(hipMemcpyAsync(s->hdr, h, bytes, hipMemcpyHostToDevice, stream));
-        HIP_TRY(hipEventRecord(s->ring_ev[rs], stream));
-        s->ring_used[rs] = true;
-        s->last_desc.assign(img, img + bytes);
-    }
+    BatchHdr h{};
+    h.n_fills = n;
+    h.stream_loads = a.stream_loads;
+    h.total_tiles = total;
+    h.total_groups = groups;
+    rc = put_table(s, h, n, desc, stream);
+    if (rc) return rc;
     a.table = s->table;
     a.hdr = s->hdr;
     a.tile_bases = s->bases;
     a.sum_bases = s->bases + s->fill_cap;
-    // two kernels (the emit pass) are cheaper launched than replayed
-    const bool use_graph = ctx->graphs && sc.wgs_per_cu > 0 && !qouts && !a.fused;
+    // the split schedule's two or three kernels are never replayed: a replay
+    // starts 8 us after the kernel before it ends, plain launches at once (24
+    // uneven fills: 265 us a batch replayed)
+    const bool use_graph = ctx->graphs && sc.wgs_per_cu > 0 && !is_split;
     if (!use_graph) return launch_pair(ctx, s, a, total, stream, sc);
     GraphKey want;
     want.threads = sc.threads;
@@ -731,13 +777,6 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     want.parts = sc.parts;
     want.table = s->table;
     want.state = s->tile_state;
-    if (a.split) {
-        want.tiles = graph_tiles(total);
-        want.sums = s->sums;
-        want.stream_loads = a.stream_loads;
-        want.ped_scan = a.ped_scan;
-        want.multi_seg = a.multi_seg;
-    }
     if (!s->g_chop || !(s->key == want)) {
         rc = capture_graphs(ctx, s, sc, want);
         if (rc) return rc;
@@ -992,33 +1031,6 @@ uint8_t *noalloc_ptr(int device) {
     if (device < 0 || device >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lk(g_noalloc_mu);
     return g_noalloc_ptr[device];
-}
-
-// Descriptors of up to kPutFills fills travel as kernel arguments into the
-// table in the scratch array (no host staging buffer, no copy call).
-constexpr int kPutFills = 16;
-struct PutDescArgs {
-    FillDev d[kPutFills];
-    BatchHdr hdr;
-    FillDev *dst;      // table entry of d[0]
-    int64_t *tile_bases, *sum_bases;  // entries of d[0]
-    BatchHdr *dst_hdr; // written when write_hdr
-    int32_t count, write_hdr;
-};
-static_assert(sizeof(PutDescArgs) <= 3584, "kernel arguments of the descriptor upload (explicit arguments well below 4 KB)");
-
-__global__ void k_put_descs(PutDescArgs a) {
-    constexpr int W = (int)(sizeof(FillDev) / 16);  // 16-byte words per descriptor
-    const int i = (int)threadIdx.x;
-    if (i < a.count * W) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(&a.d[0]);
-        reinterpret_cast<uint4 *>(a.dst)[i] = src[i];
-    }
-    if (i < a.count) {
-        a.tile_bases[i] = a.d[i].tile_base;
-        a.sum_bases[i] = a.d[i].sum_base;
-    }
-    if (a.write_hdr && i == 0) *a.dst_hdr = a.hdr;
 }
 
 // Layout of one no-allocation call inside the scratch array (byte offsets).
@@ -1282,25 +1294,12 @@ int run_qmethod(daq_ctx *ctx, const daq_fill *fills, const daq_q_out *outs, int3
     if (n == 1) {
         a.one = desc(0);
     } else {
-        const int rs = s->ring_pos;
-        s->ring_pos = (s->ring_pos + 1) % kRing;
-        if (s->ring_used[rs]) HIP_TRY(hipEventSynchronize(s->ring_ev[rs]));
-        BatchHdr *h = reinterpret_cast<BatchHdr *>(s->ring_host[rs]);
-        FillDev *tab = reinterpret_cast<FillDev *>(reinterpret_cast<int64_t *>(h + 1) + 2 * (size_t)s->fill_cap);
-        h->n_fills = n;
-        h->stream_loads = a.stream_loads;
-        h->total_tiles = total;
-        h->total_groups = 0;
-        h->pad2 = 0;
-        for (int32_t i = 0; i < n; i++) tab[i] = desc(i);
-        const size_t bytes = desc_bytes(s->fill_cap, n);
-        const uint8_t *img = reinterpret_cast<const uint8_t *>(h);
-        if (s->last_desc.size() != bytes || std::memcmp(s->last_desc.data(), img, bytes) != 0) {
-            HIP_TRY(hipMemcpyAsync(s->hdr, h, bytes, hipMemcpyHostToDevice, stream));
-            HIP_TRY(hipEventRecord(s->ring_ev[rs], stream));
-            s->ring_used[rs] = true;
-            s->last_desc.assign(img, img + bytes);
-        }
+        BatchHdr h{};
+        h.n_fills = n;
+        h.stream_loads = a.stream_loads;
+        h.total_tiles = total;
+        rc = put_table(s, h, n, desc, stream);
+        if (rc) return rc;
         a.table = s->table;
         a.hdr = s->hdr;
     }

@@ -66,7 +66,7 @@ def test_edges_of_tiles_groups_and_segments(N, pre, post):
             assert_same(o, ref, ctx="%s noalloc" % kind)
 
 
-@pytest.mark.parametrize("n", [2, 8, 9, 70])
+@pytest.mark.parametrize("n", [2, 4, 5, 8, 9, 16, 17, 70])
 @pytest.mark.parametrize("threads", [256, 512])
 def test_batches_around_the_emit_pass_limit(n, threads):
     """Mixed fills (empty ones, whole segments, capped outputs, find only) in
@@ -94,6 +94,34 @@ def test_batches_around_the_emit_pass_limit(n, threads):
             torch.cuda.synchronize()
             for i, (o, r) in enumerate(zip(outs, refs)):
                 assert_same(o, r, ctx="fill %d graphs %s" % (i, graphs))
+
+
+def test_many_batches_queued_behind_each_other():
+    """Descriptor tables of 17 and more fills wait in a ring of 16 slots: 40
+    different batches queued without a wait between them."""
+    rng = np.random.default_rng(40)
+    with daq.Context(0) as ctx:
+        queued = []
+        for k in range(40):
+            fills, outs, refs = [], [], []
+            for i in range(17 + k % 3):
+                N = int(rng.integers(1, 2 * TILE))
+                pre, post = WINDOWS[int(rng.integers(0, 3))]
+                x = _fill(rng, N, pre + post + 1, "edges")
+                p = _params(pre, post, "edges")
+                f = make_fill(dev(x), N, p)
+                fills.append(f)
+                refs.append(oracle_result(x, N, p))
+                outs.append(poison_out(daq.alloc_out(f)))
+            queued.append((fills, outs, refs))
+        torch.cuda.synchronize()
+        log("40 batches")
+        for fills, outs, _ in queued:
+            ctx.daq_process_batch(fills, outs)
+        torch.cuda.synchronize()
+        for k, (_, outs, refs) in enumerate(queued):
+            for i, (o, r) in enumerate(zip(outs, refs)):
+                assert_same(o, r, ctx="batch %d fill %d" % (k, i))
 
 
 def test_pedestals_longer_than_the_scan_takes():
