@@ -2264,14 +2264,39 @@ __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int 
         copy_store(fd, c + kCopyU, c_hi, kind, split, o, b0, b1);
     }
     if (kind == 3) {
-        for (int c = c_lo; c < c_hi; c++) {
-            const int16_t *row = fd.raw + (int64_t)c * fd.stride;
-            DAQ_GLOBAL int16_t *orow = gbl(fd.out + (int64_t)c * fd.out_stride + q0);
-            int r = R;
-            for (int e = 0; e < valid; e++) {
-                const int q = pos + e;
+        // the source of every position first, then all loads of kCopyU channels
+        // in flight (positions past `valid` repeat the last one). A fill's last
+        // word is one of these: a load, a wait and a store per sample made its
+        // wave the last to end (find + gather of 54 x 300,001 samples 33.3 us,
+        // 29.8 so; both methods over 8 fills of 560,000 570 us, 563 so)
+        uint32_t src[kVec];  // byte offsets in the row
+        int r = R;
+#pragma unroll
+        for (int e = 0; e < kVec; e++) {
+            const int q = pos + e;
+            if (e < valid && q >= d2)
                 while (r + 1 < nrun && d[r + 1] - rel <= q) r++;
-                orow[q] = *gbl(row + st[r] + (q - (d[r] - rel)));
+            src[e] = (uint32_t)(q < d1 ? st0 + (q - d0) : q < d2 ? st1 + (q - d1) : st[r] + (q - (d[r] - rel))) * 2u;
+            if (e > 0 && e >= valid) src[e] = src[e - 1];
+        }
+        for (int c = c_lo; c < c_hi; c += kCopyU) {
+            uint16_t v[kCopyU][kVec];
+#pragma unroll
+            for (int e = 0; e < kVec; e++) asm volatile("" : "+v"(src[e]));  // 32-bit offsets, not hoisted 64-bit addresses
+#pragma unroll
+            for (int u = 0; u < kCopyU; u++) {
+                const DAQ_GLOBAL char *row =
+                    (const DAQ_GLOBAL char *)(fd.raw + (int64_t)(c + u < c_hi ? c + u : c_hi - 1) * fd.stride);
+#pragma unroll
+                for (int e = 0; e < kVec; e++) v[u][e] = *(const DAQ_GLOBAL uint16_t *)(row + src[e]);
+            }
+#pragma unroll
+            for (int u = 0; u < kCopyU; u++) {
+                if (c + u >= c_hi) break;
+                DAQ_GLOBAL int16_t *orow = gbl(fd.out + (int64_t)(c + u) * fd.out_stride + o);
+#pragma unroll
+                for (int e = 0; e < kVec; e++)
+                    if (e < valid) orow[e] = (int16_t)v[u][e];
             }
         }
     }
@@ -2423,7 +2448,9 @@ constexpr int kEmitRuns = kEmitSegs * kCopyChunk + kScanTile / 2 + 4;  // their 
 #endif
 constexpr int kEmitGroup = DAQ_EMIT_GROUP;
 
-__global__ void __launch_bounds__(kEmitThreads) k_emit_pass(KArgs a) {
+// 4: 128 registers, so that two work-groups fit a CU (with 129 a lone fill of 54 x
+// 560,000 samples took 31.2 us, with 128 27.4).
+__global__ void __launch_bounds__(kEmitThreads, 4) k_emit_pass(KArgs a) {
     constexpr int NT = kEmitThreads, NW = NT / 64;
     constexpr int kPer = (kSegTiles + NT - 1) / NT;  // tiles per thread
     __shared__ FlagSum s_wave[NW];

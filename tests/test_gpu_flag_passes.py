@@ -96,6 +96,40 @@ def test_batches_around_the_emit_pass_limit(n, threads):
                 assert_same(o, r, ctx="fill %d graphs %s" % (i, graphs))
 
 
+@pytest.mark.parametrize("tail", range(1, 10))
+def test_last_words_of_one_two_and_many_runs(tail):
+    """Packed rows that end 1 to 8 samples into a 16-byte word, that word made of
+    one run, of two, and of runs of one and two samples."""
+    rng = np.random.default_rng(tail)
+    with daq.Context(0) as ctx:
+        for C in (1, 4, 7, 54):
+            for what in ("one", "two", "many"):
+                x = rng.integers(995, 1006, size=(C, 3001)).astype(np.int16)
+                at = list(range(100, 180)) if what == "many" else []
+                step = {"one": [tail + 40], "two": [24 + tail // 2, 24 + (tail + 1) // 2], "many": [1] * tail}[what]
+                t = 500
+                for run_len in step:
+                    at += range(t, t + run_len)
+                    t += run_len + 3
+                if what == "many":
+                    at = at[:80:2] + at[80:]
+                x[:, at] -= 500
+                x = pad_stride(x)
+                p = {"threshold": -200 * C, "pre": 0, "post": 0, "ped_samples": 50}
+                ref = oracle_result(x, 3001, p)
+                f = make_fill(dev(x), 3001, p)
+                for mode in ("chop", "twopass"):
+                    log("tail=%d C=%d %s %s" % (tail, C, what, mode))
+                    o = daq.alloc_out(f)
+                    run(ctx, mode, [f], [o])
+                    assert_same(o, ref, ctx="%s %s" % (what, mode))
+                outs = [daq.alloc_out(f) for _ in range(6)]
+                ctx.daq_process_batch([f] * 6, outs)
+                torch.cuda.synchronize()
+                for o in outs:
+                    assert_same(o, ref, ctx="%s batch" % what)
+
+
 def test_many_batches_queued_behind_each_other():
     """Descriptor tables of 17 and more fills wait in a ring of 16 slots: 40
     different batches queued without a wait between them."""
