@@ -6,8 +6,8 @@
 // stream and a private context; a free worker takes all queued fills (up to
 // max_batch, oldest first) and launches them as one batch, so fills that
 // arrive while other batches run are launched on another stream and overlap
-// with them on the device. A worker waits for its own batch, copies the
-// per-fill counts to the host in one transfer and publishes completions.
+// with them on the device. A worker waits for its own batch, whose per-fill
+// counts a last small kernel writes to the host, and publishes completions.
 //
 // Deadtime accounting (the abstract asks for deadtime-free records): a
 // fill's arrival time (given with daq_submit_fill_at by callers that retry
@@ -106,6 +106,7 @@ struct CountPtrs {
     const daq_counts *p[kMaxBatch];
 };
 
+// The counts of a batch, into pinned host memory (no copy call after it).
 __global__ void k_collect_counts(CountPtrs ptrs, int n, daq_counts *dst) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) dst[i] = *ptrs.p[i];
@@ -133,7 +134,6 @@ struct Worker {
     hipStream_t stream = nullptr;
     hipEvent_t done = nullptr;
     daq_ctx *ctx = nullptr;
-    daq_counts *d_counts = nullptr;  // kMaxBatch, device
     daq_counts *h_counts = nullptr;  // kMaxBatch, pinned host
     std::vector<Job *> held;         // timed-out fills whose launches may still run
 };
@@ -263,11 +263,8 @@ void worker_loop(daq_server *srv, Worker *w) {
         if (rc == DAQ_OK) {
             CountPtrs cp{};
             for (int i = 0; i < n; i++) cp.p[i] = outs[(size_t)i].counts;
-            hipLaunchKernelGGL(k_collect_counts, dim3(1), dim3(kMaxBatch), 0, w->stream, cp, n, w->d_counts);
+            hipLaunchKernelGGL(k_collect_counts, dim3(1), dim3(kMaxBatch), 0, w->stream, cp, n, w->h_counts);
             he = hipGetLastError();
-            if (he == hipSuccess)
-                he = hipMemcpyAsync(w->h_counts, w->d_counts, (size_t)n * sizeof(daq_counts),
-                                    hipMemcpyDeviceToHost, w->stream);
             if (he == hipSuccess) he = hipEventRecord(w->done, w->stream);
             if (he == hipSuccess) {
                 const int64_t limit = srv->batch_timeout_ns.load(std::memory_order_relaxed);
@@ -326,7 +323,6 @@ void worker_loop(daq_server *srv, Worker *w) {
 
 void free_worker(Worker &w) {
     if (w.ctx) daq_ctx_destroy(w.ctx);
-    if (w.d_counts) (void)hipFree(w.d_counts);
     if (w.h_counts) (void)hipHostFree(w.h_counts);
     if (w.done) (void)hipEventDestroy(w.done);
     if (w.stream) (void)hipStreamDestroy(w.stream);
@@ -374,8 +370,6 @@ int daq_server_create(daq_server **out, daq_ctx *ctx, void *d_arena, size_t aren
             rc = DAQ_EHIP;
         if (rc == DAQ_OK && (he = hipEventCreateWithFlags(&w.done, hipEventDisableTiming)) != hipSuccess)
             rc = DAQ_EHIP;
-        if (rc == DAQ_OK && (he = hipMalloc(&w.d_counts, kMaxBatch * sizeof(daq_counts))) != hipSuccess)
-            rc = he == hipErrorOutOfMemory ? DAQ_ENOMEM : DAQ_EHIP;
         if (rc == DAQ_OK &&
             (he = hipHostMalloc(&w.h_counts, kMaxBatch * sizeof(daq_counts), hipHostMallocDefault)) != hipSuccess)
             rc = he == hipErrorOutOfMemory ? DAQ_ENOMEM : DAQ_EHIP;
