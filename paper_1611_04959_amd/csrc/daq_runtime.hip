@@ -1782,7 +1782,8 @@ int daq_autotune(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, 
         return rc;
     }
     ctx->sched = best_s;
-    ctx->graphs = mode_ms[1] <= mode_ms[0];
+    // (the split schedule is launched plainly in either mode)
+    ctx->graphs = best_s.variant != daqk::kVariantSplit && mode_ms[1] <= mode_ms[0];
     daqlog::say(2, "autotune: kept %d/%d/%d/%d with %s (plain launches %.4f ms, graph replay %.4f ms)",
                 best_s.threads, best_s.wgs_per_cu, best_s.variant, best_s.parts,
                 ctx->graphs ? "graph replay" : "plain launches", mode_ms[0], mode_ms[1]);
