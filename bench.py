@@ -6,8 +6,7 @@ samples (12-bit values; 700 us at 800 MSPS, Section 3 of the paper) at 3x the
 nominal initial pulse rate, threshold -200 ADC on the pedestal-subtracted
 calorimeter sum, pre 8 / post 24 samples. A step chops all 16 fills: island
 tables, counts, pedestals and the packed raw samples of every channel, in one
-persistent batched launch replayed from a captured HIP graph (schedule from
-the library's autotuner). Inputs are resident in HBM before timing starts.
+batched launch (schedule from the library's autotuner). Inputs are resident in HBM before timing starts.
 
 Printed (one JSON line): raw ADC GB/s (value) and its fraction of the HBM
 peak, p50/p99 fill latency for the batched and the plain per-fill forms, the
@@ -94,8 +93,8 @@ def ceiling(daq):
                 best, out["read_blocks_per_cu"], out["read_layout"] = rate, per_cu, layout
     out["read_gbs"] = round(best, 1)
     del buf
-    # the scan's own read pattern (tiles of 4,096 samples x 54 rows, 6 rows in
-    # flight) over 16 fills of 54 x 560,000, with nothing else done
+    # the read pattern of a scan with halos (tiles of 4,096 samples x 54 rows, 9
+    # rows in flight) over 16 fills of 54 x 560,000, with nothing else done
     nf, C, N = 16, 54, 560_000
     raw = torch.ones(nf * C * N, dtype=torch.int16, device="cuda")
     best_t = None
@@ -152,7 +151,7 @@ def ceiling(daq):
     del src, dst
     torch.cuda.empty_cache()
     out["what"] = ("read_gbs: one streaming read of 2 GiB with 16-byte non-temporal loads (daq_read_stream); "
-                   "scan_pattern_gbs: the 16 bench-shaped fills read in the chop scan's tiles and nothing else "
+                   "scan_pattern_gbs: the 16 bench-shaped fills read in the tiles of a scan with halos and nothing else "
                    "(daq_read_tiles), raw bytes over time; scan_reread(_write)_us: the same read, then 1 in 7 "
                    "of each tile's groups read again (and written packed): a model of a single pass; "
                    "copy_gbs: torch device copy of 1 GiB, read + write bytes")

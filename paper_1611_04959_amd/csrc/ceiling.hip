@@ -4,7 +4,8 @@
 // k_read_stream reads a buffer once with 16-byte non-temporal loads (eight
 // in flight per thread, grid-stride), folds the words with XOR so the loads
 // cannot be dropped, and leaves one word per wave in a sink.
-// k_read_tiles reads calorimeter fills in the scan's own pattern (tiles of
+// k_read_tiles reads calorimeter fills in the pattern of a scan that
+// recomputes its tiles' halos, as the persistent schedule's does (tiles of
 // 4,096 samples x every channel row, 9 rows in flight, the same halo
 // overlap) and does nothing else: the rate of that access pattern alone.
 // Its two other modes model a single pass that writes the islands from the

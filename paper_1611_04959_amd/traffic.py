@@ -37,7 +37,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 #: the sources of the chop kernels (the kernels and their shared internal
 #: header): the counts recorded for one version are not reported for another
 KERNEL_SOURCES = (os.path.join(HERE, "csrc", "chop_kernels.hip"), os.path.join(HERE, "csrc", "chop_internal.h"))
-PASS_KERNELS = ("k_prepare", "k_scan_pass", "k_edge_pass", "k_copy_pass", "k_chop", "k_pipe")
+PASS_KERNELS = ("k_prepare", "k_scan_pass", "k_edge_pass", "k_copy_pass", "k_emit_pass", "k_chop", "k_pipe")
 
 
 def _code_only(text: str) -> str:
@@ -224,7 +224,7 @@ def streams(path, k):
     span = (t1 - t0) / 1e3
     print("| Kernel | Dispatches in the last %d launches | Mean (us) |" % len(opens))
     print("|---|---|---|")
-    for name in ("k_prepare", "k_scan_pass", "k_edge_pass", "k_copy_pass", "k_chop", "k_pipe"):
+    for name in ("k_prepare", "k_scan_pass", "k_edge_pass", "k_copy_pass", "k_emit_pass", "k_chop", "k_pipe"):
         if name in per:
             print("| `%s` | %d | %.1f |" % (name, len(per[name]), sum(per[name]) / len(per[name])))
     print()
