@@ -198,7 +198,22 @@ hipError_t launch_prepare(const KArgs &a, int blocks, hipStream_t s);
 hipError_t launch_chop(const KArgs &a, int threads, int variant, int grid, hipStream_t s);
 // Split variant: the scan pass, then the edge and copy passes, over the fill
 // group a.part of a.parts.
-hipError_t launch_scan(const KArgs &a, int grid, hipStream_t s);
+// Descriptors of up to kPutFills fills travel as kernel arguments into their
+// table (no host staging buffer, no copy call).
+constexpr int kPutFills = 16;
+struct PutDescArgs {
+    FillDev d[kPutFills];
+    BatchHdr hdr;
+    FillDev *dst;      // table entry of d[0]
+    int64_t *tile_bases, *sum_bases;  // entries of d[0]
+    BatchHdr *dst_hdr; // written when write_hdr
+    int32_t count, write_hdr;
+};
+static_assert(sizeof(PutDescArgs) + sizeof(KArgs) <= 3840, "kernel arguments of the scan (explicit arguments well below 4 KB)");
+
+// With `put` (split schedule, pedestals in the scan, one part): the scan takes
+// the descriptors from its arguments and writes the table for the later passes.
+hipError_t launch_scan(const KArgs &a, int grid, hipStream_t s, const PutDescArgs *put = nullptr);
 hipError_t launch_emit(const KArgs &a, int edge_grid, int copy_grid, hipStream_t s);
 // Both in one kernel, for launches of few fills of at most kSegTiles tiles.
 hipError_t launch_emit_fused(const KArgs &a, int wgs_per_fill, hipStream_t s);

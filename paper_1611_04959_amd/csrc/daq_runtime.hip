@@ -405,16 +405,17 @@ bool emit_fused(const KArgs &a, int32_t n, int parts, int64_t longest) {
 }
 
 // The scan of a split launch, or the Q-method's pass in its place.
-int launch_scan_or_q(const daq_ctx *ctx, const KArgs &a, int threads, int64_t tiles, hipStream_t stream) {
+int launch_scan_or_q(const daq_ctx *ctx, const KArgs &a, int threads, int64_t tiles, hipStream_t stream,
+                     const daqk::PutDescArgs *put = nullptr) {
     if (a.q_fused)
         HIP_TRY(daqk::launch_q(a, threads, (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 8 * (int64_t)ctx->n_cu), stream));
     else
-        HIP_TRY(daqk::launch_scan(a, scan_grid(tiles), stream));
+        HIP_TRY(daqk::launch_scan(a, scan_grid(tiles), stream, put));
     return DAQ_OK;
 }
 
 int launch_main(const daq_ctx *ctx, Scratch *sc, const KArgs &a, const daq_schedule &s, int grid,
-                int64_t tiles, int64_t groups, hipStream_t stream) {
+                int64_t tiles, int64_t groups, hipStream_t stream, const daqk::PutDescArgs *put = nullptr) {
     if (s.variant == daqk::kVariantPipe) {
         HIP_TRY(daqk::launch_pipe(a, s.threads, grid, stream));
         return DAQ_OK;
@@ -426,7 +427,7 @@ int launch_main(const daq_ctx *ctx, Scratch *sc, const KArgs &a, const daq_sched
             KArgs a1 = a;
             a1.part = 0;
             a1.parts = 1;
-            const int rc = launch_scan_or_q(ctx, a1, s.threads, tiles, stream);
+            const int rc = launch_scan_or_q(ctx, a1, s.threads, tiles, stream, put);
             if (rc) return rc;
             if (a1.fused) {
                 // two work-groups per CU, shared by the fills; where only records are written
@@ -481,7 +482,7 @@ int prepare_blocks(const KArgs &a, int64_t total_tiles) {
 }
 
 int launch_pair(daq_ctx *ctx, Scratch *sc, const KArgs &a, int64_t total_tiles, hipStream_t stream,
-                const daq_schedule &s) {
+                const daq_schedule &s, const daqk::PutDescArgs *put = nullptr) {
     // a launch without tiles only clears the counts and pedestals (k_prepare)
     if (needs_prepare(s, a) || total_tiles == 0) HIP_TRY(daqk::launch_prepare(a, prepare_blocks(a, total_tiles), stream));
     if (total_tiles == 0) return DAQ_OK;
@@ -490,7 +491,7 @@ int launch_pair(daq_ctx *ctx, Scratch *sc, const KArgs &a, int64_t total_tiles, 
         int rc = timing_begin(ctx, stream, &slot);
         if (rc) return rc;
     }
-    int rc = launch_main(ctx, sc, a, s, chop_grid(ctx, s, total_tiles), total_tiles, a.total_groups, stream);
+    int rc = launch_main(ctx, sc, a, s, chop_grid(ctx, s, total_tiles), total_tiles, a.total_groups, stream, put);
     if (rc) return rc;
     if (ctx->timing) return timing_end(ctx, stream, slot);
     return DAQ_OK;
@@ -548,18 +549,8 @@ int capture_graphs(daq_ctx *ctx, Scratch *s, const daq_schedule &sc, const Graph
     return DAQ_OK;
 }
 
-// Descriptors of up to kPutFills fills travel as kernel arguments into their
-// table (no host staging buffer, no copy call).
-constexpr int kPutFills = 16;
-struct PutDescArgs {
-    FillDev d[kPutFills];
-    BatchHdr hdr;
-    FillDev *dst;      // table entry of d[0]
-    int64_t *tile_bases, *sum_bases;  // entries of d[0]
-    BatchHdr *dst_hdr; // written when write_hdr
-    int32_t count, write_hdr;
-};
-static_assert(sizeof(PutDescArgs) <= 3584, "kernel arguments of the descriptor upload (explicit arguments well below 4 KB)");
+using daqk::kPutFills;
+using daqk::PutDescArgs;
 
 __global__ void k_put_descs(PutDescArgs a) {
     constexpr int W = (int)(sizeof(FillDev) / 16);  // 16-byte words per descriptor
@@ -585,9 +576,11 @@ __global__ void __launch_bounds__(256) k_read_descs(const uint4 *src, uint4 *dst
 
 // Puts the header, the bases and the descriptors desc(0 .. n - 1) on the
 // device; skipped when it already holds exactly these bytes (the same batch
-// launched again).
+// launched again). With `carry` (at most kPutFills fills) a new table is left
+// in *carry for the scan to write, count = 0 if it is there already; the caller
+// clears last_desc if that launch fails.
 template <class F>
-int put_table(Scratch *s, const BatchHdr &h, int32_t n, F desc, hipStream_t stream) {
+int put_table(Scratch *s, const BatchHdr &h, int32_t n, F desc, hipStream_t stream, PutDescArgs *carry = nullptr) {
     const size_t bytes = desc_bytes(s->fill_cap, n);
     s->next_desc.assign(bytes, 0);
     BatchHdr *hdr = reinterpret_cast<BatchHdr *>(s->next_desc.data());
@@ -602,7 +595,8 @@ int put_table(Scratch *s, const BatchHdr &h, int32_t n, F desc, hipStream_t stre
     if (s->last_desc == s->next_desc) return DAQ_OK;
     s->last_desc.clear();  // whatever happens now, the old image is gone
     if (n <= kPutFills) {
-        PutDescArgs put{};
+        PutDescArgs mine{};
+        PutDescArgs &put = carry ? *carry : mine;
         put.hdr = h;
         put.dst_hdr = s->hdr;
         put.count = n;
@@ -611,8 +605,10 @@ int put_table(Scratch *s, const BatchHdr &h, int32_t n, F desc, hipStream_t stre
         put.tile_bases = s->bases;
         put.sum_bases = s->bases + s->fill_cap;
         std::memcpy(put.d, tab, (size_t)n * sizeof(FillDev));
-        hipLaunchKernelGGL(k_put_descs, dim3(1), dim3(kPutFills * sizeof(FillDev) / 16), 0, stream, put);
-        HIP_TRY(hipGetLastError());
+        if (!carry) {
+            hipLaunchKernelGGL(k_put_descs, dim3(1), dim3(kPutFills * sizeof(FillDev) / 16), 0, stream, put);
+            HIP_TRY(hipGetLastError());
+        }
     } else {
         static_assert(sizeof(BatchHdr) % 16 == 0 && sizeof(FillDev) % 16 == 0, "tables are whole 16-byte words");
         // a slot is free once its half's event has come; an event after each
@@ -761,7 +757,9 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     h.stream_loads = a.stream_loads;
     h.total_tiles = total;
     h.total_groups = groups;
-    rc = put_table(s, h, n, desc, stream);
+    PutDescArgs put{};
+    const bool carry = a.ped_scan && n <= kPutFills && total > 0 && sc.parts <= 1;
+    rc = put_table(s, h, n, desc, stream, carry ? &put : nullptr);
     if (rc) return rc;
     a.table = s->table;
     a.hdr = s->hdr;
@@ -771,7 +769,11 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     // starts 8 us after the kernel before it ends, plain launches at once (24
     // uneven fills: 265 us a batch replayed)
     const bool use_graph = ctx->graphs && sc.wgs_per_cu > 0 && !is_split;
-    if (!use_graph) return launch_pair(ctx, s, a, total, stream, sc);
+    if (!use_graph) {
+        rc = launch_pair(ctx, s, a, total, stream, sc, put.count ? &put : nullptr);
+        if (rc) s->last_desc.clear();
+        return rc;
+    }
     GraphKey want;
     want.threads = sc.threads;
     want.wgs = sc.wgs_per_cu;
