@@ -37,7 +37,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 #: the sources of the chop kernels (the kernels and their shared internal
 #: header): the counts recorded for one version are not reported for another
 KERNEL_SOURCES = (os.path.join(HERE, "csrc", "chop_kernels.hip"), os.path.join(HERE, "csrc", "chop_internal.h"))
-PASS_KERNELS = ("k_prepare", "k_scan_pass", "k_scan_put", "k_edge_pass", "k_copy_pass", "k_emit_pass", "k_chop", "k_pipe")
+PASS_KERNELS = ("k_prepare", "k_scan_pass", "k_edge_pass", "k_copy_pass", "k_emit_pass", "k_chop", "k_pipe")
 
 
 def _code_only(text: str) -> str:
@@ -165,7 +165,7 @@ def tail(path, k):
         if name is not None:
             seq.append((name, int(r["Start_Timestamp"]), int(r["End_Timestamp"]), r["Kernel_Name"]))
     # launches: a scan (or fused) dispatch opens one; keep the last k
-    opens = [i for i, x in enumerate(seq) if x[0] in ("k_scan_pass", "k_scan_put", "k_chop", "k_pipe")][-k:]
+    opens = [i for i, x in enumerate(seq) if x[0] in ("k_scan_pass", "k_chop", "k_pipe")][-k:]
     if not opens:
         print("no launch found")
         return
@@ -201,7 +201,7 @@ def streams(path, k):
         if name is not None:
             seq.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), name, r.get("Stream_Id", "0")))
     seq.sort()
-    opens = [i for i, x in enumerate(seq) if x[2] in ("k_scan_pass", "k_scan_put", "k_chop", "k_pipe")][-k:]
+    opens = [i for i, x in enumerate(seq) if x[2] in ("k_scan_pass", "k_chop", "k_pipe")][-k:]
     if not opens:
         print("no launch found")
         return None
@@ -209,7 +209,7 @@ def streams(path, k):
     per, by_stream = defaultdict(list), defaultdict(int)
     for a, b, name, sid in window:
         per[name].append((b - a) / 1e3)
-        if name in ("k_scan_pass", "k_scan_put", "k_chop", "k_pipe"):
+        if name in ("k_scan_pass", "k_chop", "k_pipe"):
             by_stream[sid] += 1
     t0 = window[0][0]
     t1 = max(b for _, b, _, _ in window)
@@ -224,7 +224,7 @@ def streams(path, k):
     span = (t1 - t0) / 1e3
     print("| Kernel | Dispatches in the last %d launches | Mean (us) |" % len(opens))
     print("|---|---|---|")
-    for name in ("k_prepare", "k_scan_pass", "k_scan_put", "k_edge_pass", "k_copy_pass", "k_emit_pass", "k_chop", "k_pipe"):
+    for name in ("k_prepare", "k_scan_pass", "k_edge_pass", "k_copy_pass", "k_emit_pass", "k_chop", "k_pipe"):
         if name in per:
             print("| `%s` | %d | %.1f |" % (name, len(per[name]), sum(per[name]) / len(per[name])))
     print()
