@@ -72,6 +72,7 @@ struct Scratch {
     int64_t *thr_eff = nullptr;
     BatchHdr *hdr = nullptr;    // device: the header, then the table (one upload)
     FillDev *table = nullptr;   // device, inside the hdr allocation
+    bool captured = false;      // a caller's graph holds launches that write the table when it is replayed
     std::vector<uint8_t> last_desc, next_desc;  // descriptor images: on the device, of the call in hand
     int32_t fill_cap = 0;
     uint8_t *ring_host = nullptr;   // kRing slots of desc_bytes(fill_cap, fill_cap)
@@ -576,7 +577,8 @@ __global__ void __launch_bounds__(256) k_read_descs(const uint4 *src, uint4 *dst
 
 // Puts the header, the bases and the descriptors desc(0 .. n - 1) on the
 // device; skipped when it already holds exactly these bytes (the same batch
-// launched again). With `carry` (at most kPutFills fills) a new table is left
+// launched again), unless a captured launch may have written it since. Under
+// capture every table travels as kernel arguments, which the graph keeps. With `carry` (at most kPutFills fills) a new table is left
 // in *carry for the scan to write, count = 0 if it is there already; the caller
 // clears last_desc if that launch fails.
 template <class F>
@@ -592,20 +594,25 @@ int put_table(Scratch *s, const BatchHdr &h, int32_t n, F desc, hipStream_t stre
         bases[i] = tab[i].tile_base;
         bases[s->fill_cap + i] = tab[i].sum_base;
     }
-    if (s->last_desc == s->next_desc) return DAQ_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &cap));
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    if (capturing) s->captured = true;
+    if (!s->captured && s->last_desc == s->next_desc) return DAQ_OK;
     s->last_desc.clear();  // whatever happens now, the old image is gone
-    if (n <= kPutFills) {
+    if (n <= kPutFills || capturing) {
         PutDescArgs mine{};
         PutDescArgs &put = carry ? *carry : mine;
         put.hdr = h;
         put.dst_hdr = s->hdr;
-        put.count = n;
-        put.write_hdr = 1;
-        put.dst = s->table;
-        put.tile_bases = s->bases;
-        put.sum_bases = s->bases + s->fill_cap;
-        std::memcpy(put.d, tab, (size_t)n * sizeof(FillDev));
-        if (!carry) {
+        for (int32_t i0 = 0; i0 < n; i0 += kPutFills) {
+            put.count = std::min<int32_t>(kPutFills, n - i0);
+            put.write_hdr = i0 == 0 ? 1 : 0;
+            put.dst = s->table + i0;
+            put.tile_bases = s->bases + i0;
+            put.sum_bases = s->bases + s->fill_cap + i0;
+            std::memcpy(put.d, tab + i0, (size_t)put.count * sizeof(FillDev));
+            if (carry) break;
             hipLaunchKernelGGL(k_put_descs, dim3(1), dim3(kPutFills * sizeof(FillDev) / 16), 0, stream, put);
             HIP_TRY(hipGetLastError());
         }

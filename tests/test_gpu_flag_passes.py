@@ -158,6 +158,56 @@ def test_many_batches_queued_behind_each_other():
                 assert_same(o, r, ctx="batch %d fill %d" % (k, i))
 
 
+@pytest.mark.parametrize("n", [3, 16, 20])
+def test_a_captured_batch_keeps_its_descriptors(n):
+    """A batch captured into a caller's graph, with other batches (and the same
+    one) launched plainly between its replays."""
+    rng = np.random.default_rng(n)
+
+    def batch():
+        fills, outs, refs = [], [], []
+        for _ in range(n):
+            N = int(rng.integers(1, 3 * TILE))
+            x = _fill(rng, N, 33, "edges")
+            p = _params(8, 24, "edges")
+            f = make_fill(dev(x), N, p)
+            fills.append(f)
+            refs.append(oracle_result(x, N, p))
+            outs.append(poison_out(daq.alloc_out(f)))
+        return fills, outs, refs
+
+    def check(b, what):
+        torch.cuda.synchronize()
+        for i, (o, r) in enumerate(zip(b[1], b[2])):
+            assert_same(o, r, ctx="%s fill %d" % (what, i))
+            poison_out(o)
+        torch.cuda.synchronize()
+
+    with daq.Context(0) as ctx:
+        kept, other = batch(), batch()
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            ctx.daq_process_batch(other[0], other[1])  # scratch grows here
+        check(other, "warm-up")
+        log("capture of %d" % n)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            ctx.daq_process_batch(kept[0], kept[1])
+        for k in range(3):
+            with torch.cuda.stream(s):
+                ctx.daq_process_batch(kept[0], kept[1])
+            check(kept, "plain %d" % k)
+            with torch.cuda.stream(s):
+                ctx.daq_process_batch(other[0], other[1])
+            check(other, "other %d" % k)
+            with torch.cuda.stream(s):
+                g.replay()
+            check(kept, "replay %d" % k)
+            with torch.cuda.stream(s):
+                ctx.daq_process_batch(other[0], other[1])
+            check(other, "other after replay %d" % k)
+
+
 def test_pedestals_longer_than_the_scan_takes():
     """Pedestal sums up to 128 samples are the scan's; longer ones come from a
     kernel of their own, and change the threshold alike."""
