@@ -2033,13 +2033,26 @@ __device__ __forceinline__ FlagSum sum_range(const T *p, int m, int32_t gap) {
 // their lengths.
 __device__ __forceinline__ int64_t seg_at(int64_t sum_base, int f) { return sum_base / kSegTiles + f; }
 
-// FlagSums of the segments of fills of more than kSegTiles tiles.
+// Groups of tiles [lo, hi) of the launch's part of the batch. Every pass over
+// summaries keeps to them: the other parts' are written by scans on other
+// streams meanwhile.
+struct GroupRange {
+    int64_t lo, hi;
+};
+__device__ __forceinline__ GroupRange group_range(const KArgs &a, int nf) {
+    const int64_t groups = a.hdr ? a.hdr->total_groups : a.total_groups;
+    const PartRange pr = part_range(a, nf, 0);
+    return GroupRange{pr.lo == 0 ? 0 : (pr.lo < nf ? *gbl(a.sum_bases + pr.lo) / kGroupTiles : groups),
+                      pr.hi < nf ? *gbl(a.sum_bases + pr.hi) / kGroupTiles : groups};
+}
+
+// FlagSums of the segments of the part's fills of more than kSegTiles tiles.
 __global__ void __launch_bounds__(kEdgeThreads) k_seg_pass(KArgs a) {
     constexpr int NW = kEdgeThreads / 64;
     __shared__ FlagSum s_w[NW];
     const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
-    const int64_t groups = a.hdr ? a.hdr->total_groups : a.total_groups;
-    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+    const GroupRange gr = group_range(a, nf);
+    for (int64_t g = gr.lo + blockIdx.x; g < gr.hi; g += gridDim.x) {
         const int f = a.table ? fill_of(a.sum_bases, nf, g * kGroupTiles) : 0;
         const EdgeFill fd = edge_fill(a, f);
         const int64_t t0 = g * kGroupTiles - fd.sum_base;
@@ -2063,13 +2076,10 @@ __global__ void __launch_bounds__(kEdgeThreads) k_edge_pass(KArgs a) {
     constexpr int NW = kEdgeThreads / 64;
     __shared__ FlagSum s_seg[NW], s_tiles[NW], s_words[NW];
     const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
-    const int64_t groups = a.hdr ? a.hdr->total_groups : a.total_groups;
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const PartRange pr = part_range(a, nf, 0);
-    const int64_t lo = pr.lo == 0 ? 0 : (pr.lo < nf ? *gbl(a.sum_bases + pr.lo) / kGroupTiles : groups);
-    const int64_t hi = pr.hi < nf ? *gbl(a.sum_bases + pr.hi) / kGroupTiles : groups;
-    for (int64_t g = lo + blockIdx.x; g < hi; g += gridDim.x) {
+    const GroupRange gr = group_range(a, nf);
+    for (int64_t g = gr.lo + blockIdx.x; g < gr.hi; g += gridDim.x) {
         const int f = a.table ? fill_of(a.sum_bases, nf, g * kGroupTiles) : 0;
         const EdgeFill fd = edge_fill(a, f);
         const int64_t t0 = g * kGroupTiles - fd.sum_base;  // the group's first tile in the fill
@@ -2112,7 +2122,7 @@ __global__ void __launch_bounds__(kEdgeThreads) k_edge_pass(KArgs a) {
         if (t0 + kGroupTiles >= tiles && threadIdx.x == 0) put_totals(fd, all);
         if (fd.n == 0 && fd.ped != nullptr)  // no tile wrote them
             for (int c = (int)threadIdx.x; c < fd.C; c += kEdgeThreads) *gbl(fd.ped + c) = 0;
-        if (g + gridDim.x < hi) lds_barrier();
+        if (g + gridDim.x < gr.hi) lds_barrier();
     }
 }
 
