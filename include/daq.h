@@ -207,7 +207,10 @@ int daq_find_islands(daq_ctx *ctx, const daq_fill *fill, daq_island *d_islands,
  * d_out[c * out_stride + offset + k]. Reads the island count from d_counts
  * on the device and copies at most `capacity` islands; positions at or past
  * out_stride are skipped (and DAQ_STATUS_OUT_STRIDE is or-ed into
- * d_counts->status). Errors: as daq_find_islands, plus EINVAL for
+ * d_counts->status). In a table of the caller's own, positions before the
+ * first record's offset (a tail of an island table) continue that record to
+ * the left, and a sample outside the fill's n_channels * row_stride elements
+ * is not read: its copy is 0. Errors: as daq_find_islands, plus EINVAL for
  * d_out == NULL or out_stride < 0. */
 int daq_gather_islands(daq_ctx *ctx, const daq_fill *fill,
                        const daq_island *d_islands, int64_t capacity,

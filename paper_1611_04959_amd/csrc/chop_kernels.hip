@@ -2241,12 +2241,22 @@ __device__ __forceinline__ void copy_store(const FillDev &fd, int c, int c_hi, i
     }
 }
 
+// Sample t of channel c, whatever t: 0 outside the fill's rows, which hold
+// C * stride samples from raw on.
+__device__ __forceinline__ uint16_t raw_sample(const int16_t *raw, int64_t stride, int C, int c, int64_t t) {
+    const bool in = t >= -(int64_t)c * stride && t < (int64_t)(C - c) * stride;
+    const uint16_t v = *(const DAQ_GLOBAL uint16_t *)(raw + (in ? (int64_t)c * stride + t : 0));
+    return in ? v : (uint16_t)0;
+}
+
 // Packed positions [q0, q0 + m) of channels [c_lo, c_hi) of fill fd; the
 // nrun runs that cover it are in st[] / d[] (packed starts d relative to dq,
 // the first one at or before q0; two more words of either may be read).
 // Executed by one whole wave. CHECK: the runs come
-// from a table of the caller's, which may not be one that the library wrote:
-// words whose 16-byte loads would leave the row go sample by sample.
+// from a table of the caller's, which may not be one that the library wrote.
+// The first one may then begin after q0 (the positions before it follow from
+// it too), words whose 16-byte loads would leave the row go sample by sample,
+// and of these none outside the fill's rows is read (raw_sample).
 template <bool CHECK = false>
 __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int m, int c_lo, int c_hi,
                                              const int32_t *st, const int32_t *d, int64_t dq, int32_t *slot,
@@ -2261,7 +2271,8 @@ __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int 
         if (w < 64) atomicMax(&slot[w], j);
     }
     __builtin_amdgcn_wave_barrier();
-    const int R = scan_max(slot[lane]);
+    int R = scan_max(slot[lane]);
+    if (CHECK && R < 0) R = 0;
     const int pos = kVec * lane;                       // first packed position of this lane's word
     const int valid = m - pos < kVec ? m - pos : kVec;  // positions of the word inside the segment
     const int d0 = d[R] - rel;
@@ -2311,14 +2322,28 @@ __device__ __forceinline__ void copy_segment(const FillDev &fd, int64_t q0, int 
         // wave the last to end (find + gather of 54 x 300,001 samples 33.3 us,
         // 29.8 so; both methods over 8 fills of 560,000 570 us, 563 so)
         uint32_t src[kVec];  // byte offsets in the row
+        uint32_t furthest = 0;
         int r = R;
 #pragma unroll
         for (int e = 0; e < kVec; e++) {
             const int q = pos + e;
             if (e < valid && q >= d2)
                 while (r + 1 < nrun && d[r + 1] - rel <= q) r++;
-            src[e] = (uint32_t)(q < d1 ? st0 + (q - d0) : q < d2 ? st1 + (q - d1) : st[r] + (q - (d[r] - rel))) * 2u;
+            const int at = q < d1 ? st0 + (q - d0) : q < d2 ? st1 + (q - d1) : st[r] + (q - (d[r] - rel));
+            src[e] = (uint32_t)at * 2u;
             if (e > 0 && e >= valid) src[e] = src[e - 1];
+            else furthest = furthest > (uint32_t)at ? furthest : (uint32_t)at;  // (one before the row: 2^31 and up)
+        }
+        if (CHECK && furthest >= (uint32_t)fd.n) {
+            r = R;
+            for (int e = 0; e < valid; e++) {
+                const int q = pos + e;
+                while (r + 1 < nrun && d[r + 1] - rel <= q) r++;
+                const int64_t at = (int64_t)st[r] + q - (d[r] - rel);
+                for (int c = c_lo; c < c_hi; c++)
+                    gbl(fd.out + (int64_t)c * fd.out_stride + o)[e] = (int16_t)raw_sample(fd.raw, fd.stride, fd.C, c, at);
+            }
+            return;
         }
         for (int c = c_lo; c < c_hi; c += kCopyU) {
             uint16_t v[kCopyU][kVec];
@@ -3061,6 +3086,8 @@ __global__ void __launch_bounds__(256) k_prepare(KArgs a) {
 // The table is the caller's: a word whose 16-byte loads would leave the row
 // (records not in increasing start, or past the fill) goes sample by sample,
 // as does a segment touched by more than kSegRuns - 2 records (empty ones).
+// Positions before the first record (a tail of a table) continue it to the
+// left.
 
 // Last of the records [0, n) with offset <= q (0 if there is none); n >= 1.
 // Executed by one whole wave.
@@ -3094,7 +3121,7 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather(GatherArgs g) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && g.counts->total_len > g.out_stride)
         atomicOr(&g.counts->status, DAQ_STATUS_OUT_STRIDE);
     const int64_t lim = total < g.out_stride ? total : g.out_stride;
-    if (lim <= 0) return;
+    if (lim <= 0 || g.raw == nullptr || g.stride == 0) return;
     FillDev fd{};
     fd.raw = g.raw;
     fd.n = g.n;
@@ -3146,7 +3173,7 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather(GatherArgs g) {
                 }
                 const int64_t src = *gbl(&g.isl[lo].start) + (pos - *gbl(&g.isl[lo].offset));
                 for (int c = c_lo; c < c_hi; c++)
-                    *gbl(g.out + (int64_t)c * g.out_stride + pos) = *gbl(g.raw + (int64_t)c * g.stride + src);
+                    *gbl(g.out + (int64_t)c * g.out_stride + pos) = (int16_t)raw_sample(g.raw, g.stride, g.C, c, src);
             }
         }
         __builtin_amdgcn_wave_barrier();
