@@ -551,7 +551,9 @@ __global__ void __launch_bounds__(kZWaves * 64) k_unz(ZDecArgs a) {
         const int blocks = g.nb - p.at.gr * kZGroup;
         const int last = 8 * ((blocks < kZGroup ? blocks : kZGroup) - 1);
         p.start = lane_i64(p.off, 0);
-        const int64_t span = lane_i64(p.off, last) + __builtin_amdgcn_readlane((int)nw, last) - p.start;
+        // (a damaged stream's offsets can be anything: unsigned, so that nothing overflows)
+        const int64_t span = (int64_t)((uint64_t)lane_i64(p.off, last) + (uint64_t)__builtin_amdgcn_readlane((int)nw, last) -
+                                       (uint64_t)p.start);
         p.span = (int)(span < 0 ? 0 : (span > kZGroupWords ? kZGroupWords : span));
         int64_t k0 = p.start < most ? p.start : most;
         k0 = k0 < 0 ? 0 : k0;
@@ -566,13 +568,13 @@ __global__ void __launch_bounds__(kZWaves * 64) k_unz(ZDecArgs a) {
         const ZAt at = p.at;
         const uint32_t rel = (uint32_t)p.off - (uint32_t)p.start;  // the block's first word (clamped below)
         const int span = p.span;
-        if (p.start >= 0 && p.start + span <= f.n_words) {
+        if (p.start >= 0 && p.start <= f.n_words - span) {  // (no sum that could wrap)
             buf[1 + lane] = p.x0;
             buf[1 + 64 + lane] = p.x1;
             for (int k = (int)lane + 128; k < span; k += 64) buf[1 + k] = (words + p.start)[k];
         } else {  // a damaged stream: words outside it are zero
             for (int k = lane; k < span + 2; k += 64) {
-                const int64_t i = p.start + k;
+                const int64_t i = (int64_t)((uint64_t)p.start + (uint64_t)k);
                 buf[1 + k] = i >= 0 && i < f.n_words ? words[i] : 0u;
             }
         }
