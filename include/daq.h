@@ -35,6 +35,14 @@
  *  - A context is not thread-safe: one host thread at a time. Calls on the
  *    same context may use different streams; each stream gets its own
  *    scratch, so work on different streams may overlap.
+ *  - Calls that launch plainly (all but daq_process_batch with graphs on in
+ *    a schedule that replays them) may be captured into a HIP graph of the
+ *    caller's, once an equal call has grown the stream's scratch; one that
+ *    would have to grow it fails while the stream captures. The graph uses
+ *    that stream's scratch: its replays are ordered by the caller with the
+ *    context's other calls on that stream. Scratch that it may use is kept until
+ *    daq_ctx_destroy, also when later calls need more; none is replayed after
+ *    that.
  *  - Return value 0 = success, negative = error (daq_strerror names it).
  *    A call that returns an error enqueued nothing.
  */

@@ -72,7 +72,9 @@ struct Scratch {
     int64_t *thr_eff = nullptr;
     BatchHdr *hdr = nullptr;    // device: the header, then the table (one upload)
     FillDev *table = nullptr;   // device, inside the hdr allocation
-    bool captured = false;      // a caller's graph holds launches that write the table when it is replayed
+    bool capturing = false;     // the call in hand is being captured into a caller's graph
+    bool captured = false;      // such a graph holds launches that use these buffers when it is replayed ..
+    std::vector<void *> retired;  // .. and those that were grown out of since, kept for it
     std::vector<uint8_t> last_desc, next_desc;  // descriptor images: on the device, of the call in hand
     int32_t fill_cap = 0;
     uint8_t *ring_host = nullptr;   // kRing slots of desc_bytes(fill_cap, fill_cap)
@@ -185,6 +187,7 @@ void free_scratch(Scratch *s) {
     (void)hipFree(s->mask);
     (void)hipFree(s->q_ped);
     (void)hipFree(s->z_gofs);
+    for (void *p : s->retired) (void)hipFree(p);
     for (hipEvent_t ev : s->ring_ev)
         if (ev) (void)hipEventDestroy(ev);
     if (s->ring_host) (void)hipHostFree(s->ring_host);
@@ -200,6 +203,28 @@ Scratch *scratch_for(daq_ctx *ctx, hipStream_t stream) {
     return s;
 }
 
+// The scratch of a call on `stream`, which may be capturing. (The null stream
+// cannot be captured, and asking fails while another stream is.)
+Scratch *open_scratch(daq_ctx *ctx, hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (stream && hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();  // whatever is wrong with the stream, the launches will say
+        st = hipStreamCaptureStatusNone;
+    }
+    Scratch *s = scratch_for(ctx, stream);
+    s->capturing = st != hipStreamCaptureStatusNone;
+    s->captured = s->captured || s->capturing;
+    return s;
+}
+
+// Gives up a scratch buffer that is grown out of: frees it, or keeps it for the
+// graphs that callers have captured (buffers grow by half, so what is kept is at
+// most twice what is in use).
+void give_up(Scratch *s, void *p) {
+    if (p && s->captured) s->retired.push_back(p);
+    else (void)hipFree(p);
+}
+
 // Segment summaries that the fills of `groups` groups of tiles can need (a fill
 // takes at least one group).
 int64_t seg_entries(int64_t groups) { return groups / daqk::kSegGroups + groups + 2; }
@@ -211,7 +236,7 @@ size_t desc_bytes(int32_t cap, int32_t n) {
 }
 
 // Grows the scratch of one stream; waits for that stream first because the
-// old buffers may still be in use by queued work or captured graphs.
+// old buffers may still be in use by queued work or its own captured graphs.
 int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes, int64_t groups) {
     if (!s->ticket) HIP_TRY(hipMalloc(&s->ticket, 64));
     const int64_t sums = groups * daqk::kGroupTiles;
@@ -224,8 +249,8 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes,
                 (long long)tiles, fills, (long long)mask_bytes);
     if (tiles > s->tile_cap) {
         int64_t cap = std::max<int64_t>(tiles + tiles / 2, 4096);
-        (void)hipFree(s->tile_state);
-        (void)hipFree(s->tile_pref);
+        give_up(s, s->tile_state);
+        give_up(s, s->tile_pref);
         s->tile_state = nullptr;
         s->tile_pref = nullptr;
         s->tile_cap = 0;
@@ -235,7 +260,7 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes,
     }
     if (sums > s->sum_cap) {
         const int64_t cap = std::max<int64_t>(groups + groups / 2, 256);
-        (void)hipFree(s->sums);
+        give_up(s, s->sums);
         s->sums = nullptr;
         s->seg_sums = nullptr;
         s->sum_cap = 0;
@@ -246,7 +271,7 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes,
     }
     if (mask_bytes > s->mask_cap) {
         const int64_t cap = std::max<int64_t>(mask_bytes + mask_bytes / 2, 1 << 20);
-        (void)hipFree(s->mask);
+        give_up(s, s->mask);
         s->mask = nullptr;
         s->mask_cap = 0;
         HIP_TRY(hipMalloc(&s->mask, (size_t)cap));
@@ -254,8 +279,8 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes,
     }
     if (fills > s->fill_cap || !s->ring_host) {
         int32_t cap = (std::max<int32_t>(fills + fills / 2, 64) + 1) / 2 * 2;
-        (void)hipFree(s->thr_eff);
-        (void)hipFree(s->hdr);
+        give_up(s, s->thr_eff);
+        give_up(s, s->hdr);
         s->thr_eff = nullptr;
         s->table = nullptr;
         s->hdr = nullptr;
@@ -594,10 +619,7 @@ int put_table(Scratch *s, const BatchHdr &h, int32_t n, F desc, hipStream_t stre
         bases[i] = tab[i].tile_base;
         bases[s->fill_cap + i] = tab[i].sum_base;
     }
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(stream, &cap));
-    const bool capturing = cap != hipStreamCaptureStatusNone;
-    if (capturing) s->captured = true;
+    const bool capturing = s->capturing;
     if (!s->captured && s->last_desc == s->next_desc) return DAQ_OK;
     s->last_desc.clear();  // whatever happens now, the old image is gone
     if (n <= kPutFills || capturing) {
@@ -696,7 +718,7 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
             mask_total += lay[(size_t)i].bytes;
         }
     }
-    Scratch *s = scratch_for(ctx, stream);
+    Scratch *s = open_scratch(ctx, stream);
     // one look-back word per tile; they double as per-fill words (pipe
     // variant): at least one per fill
     const bool is_split = sc.variant == daqk::kVariantSplit;
@@ -713,7 +735,7 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
             }
         if (ped_need > s->q_ped_cap) {
             HIP_TRY(hipStreamSynchronize(stream));
-            (void)hipFree(s->q_ped);
+            give_up(s, s->q_ped);
             s->q_ped = nullptr;
             s->q_ped_cap = 0;
             const int64_t cap = std::max<int64_t>(ped_need + ped_need / 2, 4096);
@@ -1264,12 +1286,12 @@ int run_qmethod(daq_ctx *ctx, const daq_fill *fills, const daq_q_out *outs, int3
             ped_need += fills[i].n_channels;
         }
     }
-    Scratch *s = scratch_for(ctx, stream);
+    Scratch *s = open_scratch(ctx, stream);
     int rc = ensure_scratch(s, std::max<int64_t>(total, n), n, 0, 0);
     if (rc) return rc;
     if (ped_need > s->q_ped_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
-        (void)hipFree(s->q_ped);
+        give_up(s, s->q_ped);
         s->q_ped = nullptr;
         s->q_ped_cap = 0;
         const int64_t cap = std::max<int64_t>(ped_need + ped_need / 2, 4096);
@@ -1409,10 +1431,10 @@ int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *s
     for (int32_t i0 = 0; i0 < n; i0 += daqk::kZMaxFills)
         need = std::max<int64_t>(need, (int64_t)grid_of(i0, std::min<int32_t>(n - i0, daqk::kZMaxFills)) * daqk::kZWaves);
     DeviceGuard guard(ctx->device);
-    Scratch *s = scratch_for(ctx, stream);
+    Scratch *s = open_scratch(ctx, stream);
     if (need > s->z_gofs_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
-        (void)hipFree(s->z_gofs);
+        give_up(s, s->z_gofs);
         s->z_gofs = nullptr;
         s->z_gofs_cap = 0;
         const int64_t cap = std::max<int64_t>(need, 4096);
