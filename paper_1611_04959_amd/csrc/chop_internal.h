@@ -249,8 +249,8 @@ struct ZFillDev {
 };
 // Fills per launch (the descriptors travel as kernel arguments, and 16 lanes
 // share the work-groups out), waves per work-group, work-groups per launch
-// (each wave of the pack pass sums the payload sizes of its fill's waves before
-// it).
+// (each wave of the pack pass sums the payload sizes of its fill's work-groups
+// before its own).
 constexpr int kZMaxFills = 16;
 constexpr int kZWaves = 4;
 #ifndef DAQ_Z_MAX_GRID
@@ -259,7 +259,7 @@ constexpr int kZWaves = 4;
 constexpr int kZMaxGrid = DAQ_Z_MAX_GRID;
 struct ZArgs {
     ZFillDev f[kZMaxFills];
-    int64_t *gofs;  // scratch: payload words of each wave of the grid
+    int64_t *gofs;  // scratch: payload words of each work-group of the grid, then of each wave
     int32_t n;
 };
 hipError_t launch_z(const ZArgs &a, int grid, hipStream_t s);

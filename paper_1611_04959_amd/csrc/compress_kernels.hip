@@ -18,7 +18,7 @@
 // walks its groups in order, ORs each lane's codes into the group's payload
 // in LDS (all eight as one or two 64-bit values, three atomics each) and stores
 // the payload with coalesced writes. Every wave touches only its own LDS, so
-// there are no work-group barriers.
+// there are no work-group barriers but the one behind the size pass's sums.
 //
 // These kernels are bound by the vector instructions a sample takes and by
 // each wave's chain of loads. So codes are computed two at a time in 16-bit
@@ -47,6 +47,7 @@ constexpr int kZGroupWords = kZGroup * kZMaxWords;
 #endif
 constexpr int kZUnroll = DAQ_Z_UNROLL;
 constexpr int kZPackUnroll = DAQ_Z_PACK_UNROLL;
+constexpr int kZSums = 2;
 // LDS words of a group's payload: a spare word in front (a block's first lane
 // starts its codes one width early, with zeros) and three behind.
 constexpr int kZLdsWords = kZGroupWords + 4;
@@ -130,7 +131,8 @@ __device__ __forceinline__ ZRange z_range(int64_t groups, int32_t gpr, int v, in
 }
 
 // A wave's part of a compression launch: its fill, its number in the launch
-// and that of its fill's first wave, whether it is the fill's last one.
+// and that of its fill's first wave, whether it has the fill's last group (or is
+// the first wave of a fill without any).
 struct ZPart {
     int fill;
     bool last;
@@ -178,7 +180,7 @@ __device__ __forceinline__ bool z_part(const ZArgs &a, ZPart *p) {
     const int v = ((int)blockIdx.x - wg0) * kZWaves + wl, W = wgs * kZWaves;
     p->r = z_range(lane_i64(groups, j), p->g.gpr, v, W);
     p->fill = j;
-    p->last = v == W - 1;
+    p->last = p->r.hi == lane_i64(groups, j) && (p->r.lo < p->r.hi || v == 0);
     p->wave0 = wg0 * kZWaves;
     p->wave = p->wave0 + v;
     return true;
@@ -337,8 +339,20 @@ __global__ void __launch_bounds__(kZWaves * 64) k_z_size(ZArgs a) {
             }
         }
     }
+    // the wave's payload words, and those of the work-group's waves together
+    __shared__ int64_t s_tot[kZWaves];
     const int64_t tot = wave_sum_i64(mine);
-    if (lane == 0) a.gofs[p.wave] = tot;
+    if (lane == 0) {
+        a.gofs[gridDim.x + p.wave] = tot;
+        s_tot[p.wave & (kZWaves - 1)] = tot;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t all = 0;
+#pragma unroll
+        for (int w = 0; w < kZWaves; w++) all += s_tot[w];
+        a.gofs[blockIdx.x] = all;
+    }
 }
 
 // Ordering of one wave's own LDS accesses (clear, OR, read back, clear).
@@ -368,6 +382,10 @@ __global__ void __launch_bounds__(kZWaves * 64) k_z_pack(ZArgs a) {
     const ZFillDev &f = a.f[p.fill];
     const ZGeom g = p.g;
     const int lane = threadIdx.x & 63;
+    if (p.r.lo >= p.r.hi) {  // an empty fill, or more waves than groups
+        if (p.last && lane == 0) *f.n_words = 0;
+        return;
+    }
     const int sub = lane & 7, jb = lane >> 3;
     const uint32_t first = sub ? ~0u : 0xFFFF0000u;
     const int wl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -393,11 +411,25 @@ __global__ void __launch_bounds__(kZWaves * 64) k_z_pack(ZArgs a) {
         }
     };
     Batch b0, b1;
-    if (lo < hi) load(b0);
-    // where this wave's payload starts: the sizes of the fill's waves before it
-    int64_t before = 0;
-#pragma unroll 4
-    for (int k = p.wave0 + lane; k < p.wave; k += 64) before += a.gofs[k];
+    load(b0);
+    // where this wave's payload starts: the sizes of the fill's work-groups before
+    // its own, kZSums of them per lane at a time, and of the waves before it in
+    // that one. (A lone fill has up to 8,192 waves: with the sizes of all those
+    // before it to add up, four loads in flight, the last ones had 32 rounds to
+    // wait for; 54 x 20,000 samples took 25.6 us, 11.4 so. More loads at a time
+    // gain up to 0.3 us there and cost 16 fills of 61,000 up to 0.7.)
+    const int wg0 = p.wave0 / kZWaves, wg = (int)blockIdx.x;
+    int64_t before = lane < (p.wave & (kZWaves - 1)) ? a.gofs[gridDim.x + wg * kZWaves + lane] : 0;
+    for (int k0 = wg0; k0 < wg; k0 += 64 * kZSums) {
+        int64_t v[kZSums];
+#pragma unroll
+        for (int u = 0; u < kZSums; u++) {
+            const int k = k0 + 64 * u + lane;
+            v[u] = k < wg ? a.gofs[k] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kZSums; u++) before += v[u];
+    }
     int64_t carry = wave_sum_i64(before);
     auto pack = [&](const Batch &b, int64_t g0) {
 #pragma unroll

@@ -1427,9 +1427,9 @@ int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *s
         const int64_t wide = std::min<int64_t>(daqk::kZMaxGrid, (int64_t)DAQ_Z_WGS_PER_CU * ctx->n_cu);
         return (int)std::max<int64_t>(m, std::min<int64_t>(wide, m + groups / daqk::kZWaves));
     };
-    int64_t need = 0;  // one word per wave of a launch (launches run in stream order)
+    int64_t need = 0;  // a word per work-group and wave of a launch (launches run in stream order)
     for (int32_t i0 = 0; i0 < n; i0 += daqk::kZMaxFills)
-        need = std::max<int64_t>(need, (int64_t)grid_of(i0, std::min<int32_t>(n - i0, daqk::kZMaxFills)) * daqk::kZWaves);
+        need = std::max<int64_t>(need, (int64_t)grid_of(i0, std::min<int32_t>(n - i0, daqk::kZMaxFills)) * (daqk::kZWaves + 1));
     DeviceGuard guard(ctx->device);
     Scratch *s = open_scratch(ctx, stream);
     if (need > s->z_gofs_cap) {
