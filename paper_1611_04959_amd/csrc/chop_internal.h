@@ -278,9 +278,10 @@ struct ZStreamDev {
 };
 struct ZDecArgs {
     ZStreamDev f[kZMaxFills];
-    int32_t wg0[kZMaxFills + 1];  // first work-group of each stream; wg0[n]: the launch's
-    int32_t n;
+    int32_t wg0[kZMaxFills + 1];  // first work-group of each stream, then the launch's number, then INT32_MAX
 };
-hipError_t launch_unz(const ZDecArgs &a, hipStream_t s);
+// one: a wave takes one group at most, and each of the n streams has `grid`
+// work-groups; else `grid` is the launch's, shared out by wg0.
+hipError_t launch_unz(const ZDecArgs &a, int n, bool one, int grid, hipStream_t s);
 
 }  // namespace daqk

@@ -510,7 +510,9 @@ __global__ void __launch_bounds__(kZWaves * 64) k_z_pack(ZArgs a) {
 // first sample. Words past n_words are read as zero, so a damaged stream cannot
 // make the kernel read out of bounds. Samples are int16, so all sums are modulo
 // 2^16: groups whose codes are at most 16 bits wide are decoded two samples to
-// a word.
+// a word. ONE: every stream (blockIdx.y) has a wave for each of its groups. Else
+// the streams share the work-groups out, and a wave takes a range of groups, the
+// next one's loads in flight while one is decoded.
 
 // 64 bits of the payload from bit `pos` on (pos >= -16; three words).
 __device__ __forceinline__ uint64_t z_get64(const uint32_t *buf, int pos) {
@@ -520,9 +522,9 @@ __device__ __forceinline__ uint64_t z_get64(const uint32_t *buf, int pos) {
     return ((uint64_t)__builtin_amdgcn_alignbit(c, b, r) << 32) | __builtin_amdgcn_alignbit(b, a, r);
 }
 
-// Eight decoded samples, stored non-temporally: the rows are larger than the L2
-// caches, and left dirty there they are written back when the kernel ends (24.5
-// against 28.3 us for the input above).
+// Eight decoded samples, stored non-temporally: left dirty in the L2 caches the
+// rows are written back when the kernel ends (62 MB 23.2 us, with plain stores
+// 29.6; 26 MB 14.4 and 15.7; 8.6 MB 7.1 and 7.6).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store16_out(int16_t *p, u32x4 v) {
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p));
@@ -533,13 +535,25 @@ __device__ __forceinline__ uint32_t z_pair(uint32_t v, uint32_t w, uint32_t mask
     return (v & mask) | (((v >> w) & mask) << 16);
 }
 
+template <bool ONE>
 __global__ void __launch_bounds__(kZWaves * 64) k_unz(ZDecArgs a) {
     // a lane's clamped start, the 34 words of its block and the spare words
     constexpr int kBuf = kZGroupWords + kZMaxWords + 8;
     __shared__ uint32_t s_words[kZWaves][kBuf];
-    // the stream whose work-groups include this one, and its waves' ranges
-    int si = 0;
-    while (si + 1 < a.n && (int)blockIdx.x >= a.wg0[si + 1]) si++;
+    // the stream whose work-groups include this one (all bounds in one load)
+    int si = 0, wg0 = 0, wg1 = 0;
+    if constexpr (ONE) {
+        si = blockIdx.y;
+    } else {
+        wg1 = a.wg0[1];
+#pragma unroll
+        for (int j = 1; j < kZMaxFills; j++) {
+            const bool at_or_after = (int)blockIdx.x >= a.wg0[j];
+            si = at_or_after ? j : si;
+            wg0 = at_or_after ? a.wg0[j] : wg0;
+            wg1 = at_or_after ? a.wg0[j + 1] : wg1;
+        }
+    }
     const ZStreamDev &f = a.f[si];
     const uint32_t lane = threadIdx.x & 63;
     const int sub = lane & 7;
@@ -548,8 +562,17 @@ __global__ void __launch_bounds__(kZWaves * 64) k_unz(ZDecArgs a) {
     uint32_t *buf = s_words[wl];  // payload word k of the group at buf[1 + k]
     for (int k = lane; k < kBuf; k += 64) buf[k] = 0u;
     const ZGeom g = z_geom_of(f.L);
-    const int v = ((int)blockIdx.x - a.wg0[si]) * kZWaves + wl, W = (a.wg0[si + 1] - a.wg0[si]) * kZWaves;
-    const ZRange r = z_range((int64_t)g.gpr * f.C, g.gpr, v, W);
+    const int v = ((int)blockIdx.x - wg0) * kZWaves + wl;
+    ZRange r;
+    if constexpr (ONE) {
+        const int64_t groups = (int64_t)g.gpr * f.C;
+        r.lo = v;
+        r.hi = v < groups ? v + 1 : v;
+        r.c = g.gpr ? (int32_t)udiv(v, g.gpr) : 0;
+        r.gr = v - r.c * g.gpr;
+    } else {
+        r = z_range((int64_t)g.gpr * f.C, g.gpr, v, (wg1 - wg0) * kZWaves);
+    }
     if (r.lo >= r.hi) return;
     // payload words are read at clamped indices, without branches around the
     // loads (a stream without words reads a header instead, and drops it)
@@ -610,8 +633,10 @@ __global__ void __launch_bounds__(kZWaves * 64) k_unz(ZDecArgs a) {
                 buf[1 + k] = i >= 0 && i < f.n_words ? words[i] : 0u;
             }
         }
-        load_payload(q);
-        load_head(p);
+        if constexpr (!ONE) {
+            load_payload(q);
+            load_head(p);
+        }
         wave_lds_order();
         uint32_t w = hw >> 16;
         w = w > 17u ? 17u : w;
@@ -701,6 +726,11 @@ __global__ void __launch_bounds__(kZWaves * 64) k_unz(ZDecArgs a) {
     };
     Group p, q;
     load_head(p);
+    if constexpr (ONE) {
+        load_payload(p);
+        turn(p, q);
+        return;
+    }
     load_head(q);
     load_payload(p);
     // (two turns per round, with the groups' roles swapped: carried through a
@@ -715,9 +745,10 @@ __global__ void __launch_bounds__(kZWaves * 64) k_unz(ZDecArgs a) {
 
 }  // namespace
 
-hipError_t launch_unz(const ZDecArgs &a, hipStream_t s) {
-    if (a.n < 1 || a.n > kZMaxFills || a.wg0[a.n] < a.n) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_unz, dim3(a.wg0[a.n]), dim3(kZWaves * 64), 0, s, a);
+hipError_t launch_unz(const ZDecArgs &a, int n, bool one, int grid, hipStream_t s) {
+    if (grid < 1 || n < 1 || n > kZMaxFills) return hipErrorInvalidValue;
+    if (one) hipLaunchKernelGGL(k_unz<true>, dim3(grid, n), dim3(kZWaves * 64), 0, s, a);
+    else hipLaunchKernelGGL(k_unz<false>, dim3(grid), dim3(kZWaves * 64), 0, s, a);
     return hipGetLastError();
 }
 

@@ -1404,11 +1404,20 @@ int check_z_fill(const daq_z_fill &z) {
 }  // namespace
 
 // Work-groups per CU of a compression or decoding launch, shared by its fills.
+// Decoding launches of streams with room for at most DAQ_UNZ_ONE_GROUPS groups of
+// eight blocks have a wave for each instead: no wave then waits for a second
+// group, and the kernel is half as long. 54 rows of: 4 x 20,000 samples 9.1 us
+// shared out, 7.0 with a wave a group; 16 x 20,000 (34,560 groups) 17.5, 15.0;
+// 8 x 60,000 (50,976) 21.1, 20.4; 10 x 60,000 (63,720) 23.3, 24.8; 9 uneven of up
+// to 50,000 (room for 47,628) 15.8, 16.2.
 #ifndef DAQ_Z_WGS_PER_CU
 #define DAQ_Z_WGS_PER_CU 8
 #endif
 #ifndef DAQ_UNZ_WGS_PER_CU
 #define DAQ_UNZ_WGS_PER_CU 8
+#endif
+#ifndef DAQ_UNZ_ONE_GROUPS
+#define DAQ_UNZ_ONE_GROUPS (44 * 1024)
 #endif
 
 int daq_compress_batch(daq_ctx *ctx, const daq_z_fill *fills, int32_t n, void *stream_) {
@@ -1487,9 +1496,9 @@ int daq_decompress_batch(daq_ctx *ctx, const daq_z_stream *streams, int32_t n, v
     DeviceGuard guard(ctx->device);
     for (int32_t i0 = 0; i0 < n; i0 += daqk::kZMaxFills) {
         daqk::ZDecArgs a{};
-        a.n = std::min<int32_t>(n - i0, daqk::kZMaxFills);
+        const int32_t m = std::min<int32_t>(n - i0, daqk::kZMaxFills);
         int64_t groups[daqk::kZMaxFills], all = 0;
-        for (int32_t j = 0; j < a.n; j++) {
+        for (int32_t j = 0; j < m; j++) {
             const daq_z_stream &z = streams[i0 + j];
             daqk::ZStreamDev &d = a.f[j];
             d.hdr = z.hdr;
@@ -1504,12 +1513,22 @@ int daq_decompress_batch(daq_ctx *ctx, const daq_z_stream *streams, int32_t n, v
             groups[j] = (nb + 7) / 8 * z.n_channels;
             all += groups[j];
         }
-        // the launch's work-groups by the streams' groups, at least one each
-        const int64_t wide = std::min<int64_t>((int64_t)DAQ_UNZ_WGS_PER_CU * ctx->n_cu, a.n + all / daqk::kZWaves);
-        const int64_t spare = std::max<int64_t>(wide - a.n, 0);
-        for (int32_t j = 0; j < a.n; j++)
-            a.wg0[j + 1] = a.wg0[j] + 1 + (all ? (int32_t)((double)groups[j] * (double)spare / (double)all) : 0);
-        HIP_TRY(daqk::launch_unz(a, (hipStream_t)stream_));
+        // a small launch has a wave for every group; else the resident work-groups
+        // are shared out by the streams' groups, at least one for each
+        const int64_t most = *std::max_element(groups, groups + m);
+        const bool one = most * m <= DAQ_UNZ_ONE_GROUPS;
+        int grid = 0;
+        if (one) {
+            grid = (int)std::max<int64_t>(1, (most + daqk::kZWaves - 1) / daqk::kZWaves);
+        } else {
+            const int64_t wide = std::min<int64_t>((int64_t)DAQ_UNZ_WGS_PER_CU * ctx->n_cu, m + all / daqk::kZWaves);
+            const int64_t spare = std::max<int64_t>(wide - m, 0);
+            for (int32_t j = 0; j < daqk::kZMaxFills; j++) {
+                if (j < m) grid += 1 + (int)((double)groups[j] * (double)spare / (double)all);
+                a.wg0[j + 1] = j < m ? grid : INT32_MAX;
+            }
+        }
+        HIP_TRY(daqk::launch_unz(a, m, one, grid, (hipStream_t)stream_));
     }
     return DAQ_OK;
 }
