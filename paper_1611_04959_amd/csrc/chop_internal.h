@@ -45,6 +45,16 @@ constexpr int kScanTile = 512;
 // this many rows in flight (54 channels: 14 a wave, all at once).
 constexpr int kScanThreads = 256;
 constexpr int kScanRows = 14;
+// The scan of launches without a fill of more than kNarrowChannels channels, and
+// with at least kNarrowTiles tiles a CU: a wave per tile, kNarrowRows rows in
+// flight. Whole calls over 24 fills of 560,000 samples, four waves per tile
+// against this: 1 channel 116.8 / 38.3 us, 6 136.4 / 59.0, 12 154.1 / 92.4, 20
+// 184.8 / 139.9, 28 207.8 / 189.6. Short launches are chains of loads, which
+// four waves shorten: one fill of 8,191 samples, 12 channels 12.4 / 13.0, 20
+// channels 12.9 / 14.3; of 560,000, 12 channels 21.8 / 19.0.
+constexpr int kNarrowRows = 7;
+constexpr int kNarrowChannels = 28;
+constexpr int kNarrowTiles = 2;
 // The scan computes its fill's pedestals itself up to this many pedestal
 // samples (16 lanes hold them, 8 each); k_prepare does for more.
 constexpr int kScanPed = 128;
@@ -148,6 +158,7 @@ struct KArgs {
     int32_t multi_seg;     // split variant: a fill has more than kSegTiles tiles
     int32_t fused;         // split variant: the emit pass takes the edge and copy passes' place
     int32_t copies;        // split variant: some fill has packed rows to write
+    int32_t narrow;        // split variant: the scan takes a wave per tile (fills of few channels)
     FillDev one;
 };
 

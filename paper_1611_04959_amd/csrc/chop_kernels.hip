@@ -1845,16 +1845,128 @@ __device__ __forceinline__ void scan_tiles(const KArgs &a, const PutDescArgs &pu
     }
 }
 
-template <bool PED, bool STREAM>
+// Flag word of 8 lanes' flag bytes, in each of them.
+__device__ __forceinline__ uint64_t word_of8(uint32_t fb, int lane) {
+    auto or8 = [](uint32_t m) {
+        m |= (uint32_t)dpp_move<0xB1>((int32_t)m, 0);   // lanes 1 0 3 2
+        m |= (uint32_t)dpp_move<0x4E>((int32_t)m, 0);   // lanes 2 3 0 1
+        return m | (uint32_t)dpp_move<0x141>((int32_t)m, 0);  // 7 - i within 8
+    };
+    const uint32_t b = fb << (8 * (lane & 3));
+    return ((uint64_t)or8((lane & 4) ? b : 0u) << 32) | or8((lane & 4) ? 0u : b);
+}
+
+// The same for long launches of fills of few channels: a wave takes whole tiles,
+// one after the other, and nothing goes through LDS. Such a tile has too little
+// to read for four waves that meet at two barriers (24 fills of 6 x 560,000: 136.4
+// us a call, so 59.0), and a wave computes its fill's pedestals once for all its
+// tiles. Seven rows in flight leave room for twice the
+// waves that 14 do, and what bounds it is their number, up to HBM.
+template <bool PED, bool STREAM, bool PUT>
+__device__ __forceinline__ void scan_narrow(const KArgs &a, const PutDescArgs &put) {
+    constexpr int NW = kScanThreads / 64, R = kNarrowRows;
+    const int nf = !PUT && a.hdr ? a.hdr->n_fills : a.n_fills;
+    const int64_t total = !PUT && a.hdr ? a.hdr->total_tiles : a.total_tiles;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto ld = [](const int16_t *q) { return STREAM ? load16_stream(q) : load16(q); };
+    const PartRange pr = part_range(a, nf, total);
+    const int64_t waves = (int64_t)gridDim.x * NW;
+    const int64_t per = (pr.tile_hi - pr.tile_lo + waves - 1) / waves;
+    int64_t tile = pr.tile_lo + ((int64_t)blockIdx.x * NW + wid) * per;
+    const int64_t end = tile + per < pr.tile_hi ? tile + per : pr.tile_hi;
+    ScanFill fd{};
+    int64_t fill_end = -1;  // one past the last of the fill's tile numbers
+    int32_t thr_eff = 0;
+    for (; tile < end; tile++) {
+        const bool next_fill = tile >= fill_end;
+        int64_t te = 0;
+        if (next_fill) {
+            if constexpr (PUT) {
+                const int l = threadIdx.x & (kPutFills - 1);
+                const uint64_t le = __ballot(lane < nf && put.d[l].tile_base <= tile);
+                const FillDev &d = put.d[__builtin_amdgcn_readfirstlane(__popcll(le) - 1)];
+                fd = ScanFill{d.raw, d.n, d.stride, d.C, d.np, d.thr, d.pre + d.post + 1, d.flags, d.ped, d.tile_base};
+            } else if (a.table) {
+                const int f = fill_of(a.tile_bases, nf, tile);
+                const DAQ_CONST FillDev *d = fill_const(a, f);
+                fd = ScanFill{d->raw, d->n, d->stride, d->C, d->np, d->thr, d->pre + d->post + 1, d->flags, d->ped,
+                              d->tile_base};
+                if (!PED) te = *gbl(a.thr_eff + f);
+            } else {
+                fd = ScanFill{a.one.raw, a.one.n, a.one.stride, a.one.C, a.one.np, a.one.thr,
+                              a.one.pre + a.one.post + 1, a.one.flags, a.one.ped, 0};
+                if (!PED) te = *gbl(a.thr_eff);
+            }
+            const int64_t groups = (fd.n + kScanTile * kGroupTiles - 1) / (kScanTile * kGroupTiles);
+            fill_end = fd.tile_base + (groups > 1 ? groups : 1) * kGroupTiles;
+        }
+        const int64_t lt = tile - fd.tile_base;
+        if (lt * kScanTile >= fd.n) continue;  // padding up to a whole group of tiles
+        const int64_t p = lt * kScanTile + lane * kVec;
+        const int n_ped = fd.n < (int64_t)fd.np ? (int)fd.n : fd.np;
+        const int nch = (n_ped + kVec - 1) / kVec;
+        PedLoads pl;
+        if (PED && next_fill) pl = ped_load(fd, 0, fd.C, nch, lane);
+        // the rows, R in flight
+        int32_t s[kVec] = {0, 0, 0, 0, 0, 0, 0, 0};
+        const int16_t *x = fd.raw + p;
+        uint4 v[R];
+        auto load_round = [&](int c) {
+#pragma unroll
+            for (int u = 0; u < R; u++) {
+                v[u] = make_uint4(0, 0, 0, 0);
+                if (c + u < fd.C) v[u] = ld(x + (int64_t)(c + u) * fd.stride);
+            }
+        };
+        const bool in = p < fd.n;
+        if (in) load_round(0);
+        if (next_fill) {
+            if constexpr (PED) {
+                int32_t ps = ped_add(fd, pl, 0, fd.C, n_ped, lt == 0 && fd.ped != nullptr, lane);
+                for (int r0 = 16; r0 < fd.C; r0 += 16)
+                    ps += ped_add(fd, ped_load(fd, r0, fd.C, nch, lane), r0, fd.C, n_ped, lt == 0 && fd.ped != nullptr, lane);
+                ps += __shfl_xor(ps, 16, 64);
+                ps += __shfl_xor(ps, 32, 64);
+                te = (int64_t)fd.thr + __builtin_amdgcn_readfirstlane(ps);
+            }
+            thr_eff = clamp_thr(te);
+        }
+        uint32_t fb = 0;
+        if (in) {
+#pragma unroll
+            for (int u = 0; u < R; u++) add8(s, v[u]);
+            for (int c = R; c < fd.C; c += R) {
+                load_round(c);
+#pragma unroll
+                for (int u = 0; u < R; u++) add8(s, v[u]);
+            }
+            fb = flags8(s, thr_eff, fd.n - p);
+        }
+        const uint64_t mine = word_of8(fb, lane);
+        // word j from lane 8 j to lane j
+        const uint32_t xl = __shfl((uint32_t)mine, 8 * (lane & 7), 64);
+        const uint32_t xh = __shfl((uint32_t)(mine >> 32), 8 * (lane & 7), 64);
+        constexpr int kWords = kScanTile / 64;
+        const uint64_t word = lane < kWords ? ((uint64_t)xh << 32) | xl : 0ull;
+        const int64_t w = lt * kWords + lane;
+        if (lane < kWords) *gbl(fd.flags + w) = word;
+        const FlagSum sum = tile_sum(word, (int32_t)((uint32_t)w << 6), fd.gap);
+        if (lane == 0) store_sum(a.sums + tile, sum);
+    }
+}
+
+template <bool PED, bool STREAM, bool NARROW>
 __global__ void __launch_bounds__(kScanThreads) k_scan_pass(KArgs a) {
-    scan_tiles<PED, STREAM, false>(a, PutDescArgs{});
+    if constexpr (NARROW) scan_narrow<PED, STREAM, false>(a, PutDescArgs{});
+    else scan_tiles<PED, STREAM, false>(a, PutDescArgs{});
 }
 
 // The same for a batch of up to kPutFills fills whose descriptors are new: they
 // come as arguments, and the first work-groups write the table that the later
 // passes read. With a kernel before the scan that writes it a batch of 16 fills
 // of 54 x 560,000 samples took 223.4 us, so 220.9.
-template <bool STREAM>
+template <bool STREAM, bool NARROW>
 __global__ void __launch_bounds__(kScanThreads) k_scan_put(KArgs a, PutDescArgs put) {
     constexpr int W = (int)(sizeof(FillDev) / 16);
     for (int f = blockIdx.x; f < put.count; f += gridDim.x) {
@@ -1867,7 +1979,8 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_put(KArgs a, PutDescArgs 
         if (i == 65) put.sum_bases[f] = put.d[f].sum_base;
         if (i == 128 && f == 0) *put.dst_hdr = put.hdr;
     }
-    scan_tiles<true, STREAM, true>(a, put);
+    if constexpr (NARROW) scan_narrow<true, STREAM, true>(a, put);
+    else scan_tiles<true, STREAM, true>(a, put);
 }
 
 // The run table entries (start, packed offset) of the islands the calling
@@ -3213,17 +3326,28 @@ hipError_t launch_chop(const KArgs &a, int threads, int variant, int grid, hipSt
 }
 
 hipError_t launch_scan(const KArgs &a, int grid, hipStream_t s, const PutDescArgs *put) {
+    if (grid < 1) return hipErrorInvalidValue;
+    const dim3 g(grid), b(kScanThreads);
     if (put) {
         if (!a.ped_scan || a.parts != 1 || put->count != a.n_fills) return hipErrorInvalidValue;
-        if (a.stream_loads) hipLaunchKernelGGL(k_scan_put<true>, dim3(grid), dim3(kScanThreads), 0, s, a, *put);
-        else hipLaunchKernelGGL(k_scan_put<false>, dim3(grid), dim3(kScanThreads), 0, s, a, *put);
+#define DAQ_SCAN(S_, N_) hipLaunchKernelGGL((k_scan_put<S_, N_>), g, b, 0, s, a, *put)
+        if (a.stream_loads && a.narrow) DAQ_SCAN(true, true);
+        else if (a.stream_loads) DAQ_SCAN(true, false);
+        else if (a.narrow) DAQ_SCAN(false, true);
+        else DAQ_SCAN(false, false);
+#undef DAQ_SCAN
         return hipGetLastError();
     }
-    if (grid < 1) return hipErrorInvalidValue;
-    if (a.ped_scan && a.stream_loads) hipLaunchKernelGGL((k_scan_pass<true, true>), dim3(grid), dim3(kScanThreads), 0, s, a);
-    else if (a.ped_scan) hipLaunchKernelGGL((k_scan_pass<true, false>), dim3(grid), dim3(kScanThreads), 0, s, a);
-    else if (a.stream_loads) hipLaunchKernelGGL((k_scan_pass<false, true>), dim3(grid), dim3(kScanThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_scan_pass<false, false>), dim3(grid), dim3(kScanThreads), 0, s, a);
+#define DAQ_SCAN(P_, S_)                                                                 \
+    do {                                                                                 \
+        if (a.narrow) hipLaunchKernelGGL((k_scan_pass<P_, S_, true>), g, b, 0, s, a);    \
+        else hipLaunchKernelGGL((k_scan_pass<P_, S_, false>), g, b, 0, s, a);            \
+    } while (0)
+    if (a.ped_scan && a.stream_loads) DAQ_SCAN(true, true);
+    else if (a.ped_scan) DAQ_SCAN(true, false);
+    else if (a.stream_loads) DAQ_SCAN(false, true);
+    else DAQ_SCAN(false, false);
+#undef DAQ_SCAN
     return hipGetLastError();
 }
 

@@ -418,9 +418,23 @@ int ensure_parts(Scratch *sc, int parts) {
     return DAQ_OK;
 }
 
-// Work-groups of the split variant's scan (one per tile) and edge pass (one
-// per group). Both stride over their work, so smaller grids are right too.
-int scan_grid(int64_t tiles) { return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 1 << 22); }
+// Work-groups of the split variant's scan (one per tile; of waves that take tiles
+// of their own, the resident eight per CU: 16 took 1 to 4 us more) and edge pass
+// (one per group). All stride over their work, so smaller grids are right too.
+int scan_grid(const daq_ctx *ctx, const KArgs &a, int64_t tiles) {
+    if (a.narrow) {
+        constexpr int kWaves = daqk::kScanThreads / 64;
+        return (int)std::min<int64_t>((tiles + kWaves - 1) / kWaves, (int64_t)8 * ctx->n_cu);
+    }
+    return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 1 << 22);
+}
+// Whether the scan takes a wave per tile.
+bool narrow_scan(const daq_ctx *ctx, const daq_fill *fills, int32_t n, int64_t tiles) {
+    if (tiles < (int64_t)daqk::kNarrowTiles * ctx->n_cu) return false;
+    for (int32_t i = 0; i < n; i++)
+        if (fills[i].n_channels > daqk::kNarrowChannels) return false;
+    return true;
+}
 int edge_grid(int64_t groups) { return (int)std::min<int64_t>(std::max<int64_t>(groups, 1), 1 << 20); }
 
 // Whether a split launch takes the emit pass in place of the edge and copy
@@ -436,7 +450,7 @@ int launch_scan_or_q(const daq_ctx *ctx, const KArgs &a, int threads, int64_t ti
     if (a.q_fused)
         HIP_TRY(daqk::launch_q(a, threads, (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 8 * (int64_t)ctx->n_cu), stream));
     else
-        HIP_TRY(daqk::launch_scan(a, scan_grid(tiles), stream, put));
+        HIP_TRY(daqk::launch_scan(a, scan_grid(ctx, a, tiles), stream, put));
     return DAQ_OK;
 }
 
@@ -777,6 +791,7 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     a.multi_seg = longest > (int64_t)daqk::kSegTiles * daqk::kScanTile ? 1 : 0;
     a.fused = emit_fused(a, n, sc.parts, longest) ? 1 : 0;
     a.copies = copies ? 1 : 0;
+    a.narrow = narrow_scan(ctx, fills, n, total) ? 1 : 0;
     if (n == 1 && !force_table && (!batch || is_split)) {
         a.one = desc(0);
         return launch_pair(ctx, s, a, total, stream, sc);
@@ -1594,6 +1609,7 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
     a.parts = 1;
     a.split = 1;
     a.ped_scan = scan_pedestals(fills, n) ? 1 : 0;
+    a.narrow = narrow_scan(ctx, fills, n, L.total_tiles) ? 1 : 0;
     int64_t longest = 0;
     for (int32_t i = 0; i < n; i++) longest = std::max(longest, fills[i].n_samples);
     a.multi_seg = longest > (int64_t)daqk::kSegTiles * daqk::kScanTile ? 1 : 0;
@@ -1627,7 +1643,7 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
     }
     if (!a.ped_scan || L.total_tiles == 0) HIP_TRY(daqk::launch_prepare(a, prepare_blocks(a, L.total_tiles), stream));
     if (L.total_tiles == 0) return DAQ_OK;  // only counts and pedestals to clear
-    HIP_TRY(daqk::launch_scan(a, scan_grid(L.total_tiles), stream));
+    HIP_TRY(daqk::launch_scan(a, scan_grid(ctx, a, L.total_tiles), stream));
     HIP_TRY(daqk::launch_emit(a, edge_grid(L.total_groups), daqk::kCopyWgsPerCu * ctx->n_cu, stream));
     return DAQ_OK;
 }
