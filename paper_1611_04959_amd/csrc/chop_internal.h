@@ -158,6 +158,7 @@ struct KArgs {
     int32_t multi_seg;     // split variant: a fill has more than kSegTiles tiles
     int32_t fused;         // split variant: the emit pass takes the edge and copy passes' place
     int32_t copies;        // split variant: some fill has packed rows to write
+    int32_t q_small;       // the Q-method's pass loads accumulator rows together (launches the caches hold)
     int32_t narrow;        // split variant: the scan takes a wave per tile (fills of few channels)
     FillDev one;
 };
@@ -234,7 +235,7 @@ hipError_t launch_emit_fused(const KArgs &a, int wgs_per_fill, hipStream_t s);
 #endif
 constexpr int kCopyWgsPerCu = DAQ_COPY_WGS_PER_CU;
 hipError_t launch_pipe(const KArgs &a, int threads, int grid, hipStream_t s);
-hipError_t launch_q(const KArgs &a, int threads, int grid, hipStream_t s);
+hipError_t launch_q(const KArgs &a, int threads, bool small, int grid, hipStream_t s);
 hipError_t launch_unpack12(const uint8_t *in, int64_t in_stride, int32_t C, int64_t n, int16_t *out,
                            int64_t out_stride, int grid, hipStream_t s);
 // Most fill groups a split launch is cut into (one HIP stream each).

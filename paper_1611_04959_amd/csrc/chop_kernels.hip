@@ -2976,9 +2976,10 @@ __global__ void __launch_bounds__(NT) k_pipe(KArgs a) {
 // subtracted column sums of four consecutive threads make one 32-sample bin.
 // When both methods run on one read, the column sums are also compared with
 // the threshold and the flags written for the edge pass, in place of the scan
-// pass.
+// pass. SMALL: the rows of a round are loaded before its first store, else the
+// accumulator's row by row.
 
-template <int NT>
+template <int NT, bool SMALL>
 __global__ void __launch_bounds__(NT) k_q_pass(KArgs a) {
     static_assert((NT * kVec) % kQBin == 0 && kQBin % kVec == 0, "bins never cross a tile");
     constexpr int kGroupsPerBin = kQBin / kVec;
@@ -3033,13 +3034,33 @@ __global__ void __launch_bounds__(NT) k_q_pass(KArgs a) {
                     d[2 * k] = (uint32_t)((int32_t)(int16_t)(w[k] & 0xFFFFu) - pc);
                     d[2 * k + 1] = (uint32_t)((int32_t)(int16_t)(w[k] >> 16) - pc);
                 }
+                const uint4 v0 = make_uint4(d[0], d[1], d[2], d[3]), v1 = make_uint4(d[4], d[5], d[6], d[7]);
+                auto sum4 = [](const u32x4 x, const uint4 y) {
+                    return make_uint4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+                };
+                // A fill's last group, when it is not whole, is loaded as fours (a
+                // row holds whole ones) before the others and stored word by word,
+                // nothing past the fill. (Loaded word by word too, each load waited
+                // for the store before it: 54 rows of 5 words took longer than all
+                // the rest of a fill of 80,000 samples.)
+                u32x4 a0{0u, 0u, 0u, 0u}, a1{0u, 0u, 0u, 0u};
+                if (SMALL || nv != kVec) {
+                    a0 = *(const DAQ_GLOBAL u32x4 *)row;
+                    if (nv > 4) a1 = *(const DAQ_GLOBAL u32x4 *)(row + 4);
+                }
                 if (nv == kVec) {
-                    const u32x4 a0 = *(const DAQ_GLOBAL u32x4 *)row;
-                    const u32x4 a1 = *(const DAQ_GLOBAL u32x4 *)(row + 4);
-                    store16_i32(row, make_uint4(a0.x + d[0], a0.y + d[1], a0.z + d[2], a0.w + d[3]), stream);
-                    store16_i32(row + 4, make_uint4(a1.x + d[4], a1.y + d[5], a1.z + d[6], a1.w + d[7]), stream);
+                    if constexpr (!SMALL) {
+                        a0 = *(const DAQ_GLOBAL u32x4 *)row;
+                        a1 = *(const DAQ_GLOBAL u32x4 *)(row + 4);
+                    }
+                    store16_i32(row, sum4(a0, v0), stream);
+                    store16_i32(row + 4, sum4(a1, v1), stream);
                 } else {
-                    for (int k = 0; k < nv; k++) gbl(row)[k] = (int32_t)((uint32_t)gbl(row)[k] + d[k]);
+                    const uint4 r0 = sum4(a0, v0), r1 = sum4(a1, v1);
+                    const uint32_t r[kVec - 1] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z};
+#pragma unroll
+                    for (int k = 0; k < kVec - 1; k++)
+                        if (k < nv) gbl(row)[k] = (int32_t)r[k];
                 }
             };
             constexpr int R = 4;  // raw rows in flight
@@ -3375,9 +3396,12 @@ hipError_t launch_pipe(const KArgs &a, int threads, int grid, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_q(const KArgs &a, int threads, int grid, hipStream_t s) {
-    if (threads == 256) hipLaunchKernelGGL((k_q_pass<256>), dim3(grid), dim3(256), 0, s, a);
-    else if (threads == 512) hipLaunchKernelGGL((k_q_pass<512>), dim3(grid), dim3(512), 0, s, a);
+hipError_t launch_q(const KArgs &a, int threads, bool small, int grid, hipStream_t s) {
+    const dim3 g(grid), b(threads);
+    if (threads == 256 && small) hipLaunchKernelGGL((k_q_pass<256, true>), g, b, 0, s, a);
+    else if (threads == 256) hipLaunchKernelGGL((k_q_pass<256, false>), g, b, 0, s, a);
+    else if (threads == 512 && small) hipLaunchKernelGGL((k_q_pass<512, true>), g, b, 0, s, a);
+    else if (threads == 512) hipLaunchKernelGGL((k_q_pass<512, false>), g, b, 0, s, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
