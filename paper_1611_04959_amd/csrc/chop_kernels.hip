@@ -1680,7 +1680,7 @@ struct ScanFill {
     int32_t C, np, thr, gap;  // gap: pre + post + 1
     uint64_t *flags;
     int32_t *ped;
-    int64_t tile_base;
+    int64_t tile_base, sum_base;
 };
 
 // The sum over the 16 lanes of a DPP row (every lane gets it).
@@ -1754,20 +1754,20 @@ __device__ __forceinline__ void scan_tiles(const KArgs &a, const PutDescArgs &pu
             const int l = threadIdx.x & (kPutFills - 1);
             const uint64_t le = __ballot(lane < nf && put.d[l].tile_base <= tile);
             const FillDev &d = put.d[__builtin_amdgcn_readfirstlane(__popcll(le) - 1)];
-            fd = ScanFill{d.raw, d.n, d.stride, d.C, d.np, d.thr, d.pre + d.post + 1, d.flags, d.ped, d.tile_base};
+            fd = ScanFill{d.raw, d.n, d.stride, d.C, d.np, d.thr, d.pre + d.post + 1, d.flags, d.ped, d.tile_base,
+                          d.sum_base};
         } else if (a.table) {
             const int f = fill_of(a.tile_bases, nf, tile);
             const DAQ_CONST FillDev *d = fill_const(a, f);
             fd = ScanFill{d->raw, d->n, d->stride, d->C, d->np, d->thr, d->pre + d->post + 1, d->flags, d->ped,
-                          d->tile_base};
+                          d->tile_base, d->sum_base};
             if (!PED) te = *gbl(a.thr_eff + f);
         } else {
             fd = ScanFill{a.one.raw, a.one.n, a.one.stride, a.one.C, a.one.np, a.one.thr, a.one.pre + a.one.post + 1,
-                          a.one.flags, a.one.ped, 0};
+                          a.one.flags, a.one.ped, 0, 0};
             if (!PED) te = *gbl(a.thr_eff);
         }
         const int64_t lt = tile - fd.tile_base;
-        if (lt * kScanTile >= fd.n) continue;  // padding up to a whole group of tiles
         const int64_t p = lt * kScanTile + lane * kVec;  // this lane's first sample
         const int slice = (fd.C + NW - 1) / NW;
         const int c0 = wid * slice;
@@ -1839,7 +1839,7 @@ __device__ __forceinline__ void scan_tiles(const KArgs &a, const PutDescArgs &pu
             const uint64_t x = lane < kWords ? s_word[lane] : 0ull;
             if (lane < kWords) *gbl(fd.flags + w) = x;
             const FlagSum sum = tile_sum(x, (int32_t)((uint32_t)w << 6), fd.gap);
-            if (lane == 0) store_sum(a.sums + tile, sum);
+            if (lane == 0) store_sum(a.sums + fd.sum_base + lt, sum);
         }
         // (the next tile's LDS writes come after barriers that the readers above have passed)
     }
@@ -1886,23 +1886,22 @@ __device__ __forceinline__ void scan_narrow(const KArgs &a, const PutDescArgs &p
                 const int l = threadIdx.x & (kPutFills - 1);
                 const uint64_t le = __ballot(lane < nf && put.d[l].tile_base <= tile);
                 const FillDev &d = put.d[__builtin_amdgcn_readfirstlane(__popcll(le) - 1)];
-                fd = ScanFill{d.raw, d.n, d.stride, d.C, d.np, d.thr, d.pre + d.post + 1, d.flags, d.ped, d.tile_base};
+                fd = ScanFill{d.raw, d.n, d.stride, d.C, d.np, d.thr, d.pre + d.post + 1, d.flags, d.ped, d.tile_base,
+                              d.sum_base};
             } else if (a.table) {
                 const int f = fill_of(a.tile_bases, nf, tile);
                 const DAQ_CONST FillDev *d = fill_const(a, f);
                 fd = ScanFill{d->raw, d->n, d->stride, d->C, d->np, d->thr, d->pre + d->post + 1, d->flags, d->ped,
-                              d->tile_base};
+                              d->tile_base, d->sum_base};
                 if (!PED) te = *gbl(a.thr_eff + f);
             } else {
                 fd = ScanFill{a.one.raw, a.one.n, a.one.stride, a.one.C, a.one.np, a.one.thr,
-                              a.one.pre + a.one.post + 1, a.one.flags, a.one.ped, 0};
+                              a.one.pre + a.one.post + 1, a.one.flags, a.one.ped, 0, 0};
                 if (!PED) te = *gbl(a.thr_eff);
             }
-            const int64_t groups = (fd.n + kScanTile * kGroupTiles - 1) / (kScanTile * kGroupTiles);
-            fill_end = fd.tile_base + (groups > 1 ? groups : 1) * kGroupTiles;
+            fill_end = fd.tile_base + (fd.n + kScanTile - 1) / kScanTile;
         }
         const int64_t lt = tile - fd.tile_base;
-        if (lt * kScanTile >= fd.n) continue;  // padding up to a whole group of tiles
         const int64_t p = lt * kScanTile + lane * kVec;
         const int n_ped = fd.n < (int64_t)fd.np ? (int)fd.n : fd.np;
         const int nch = (n_ped + kVec - 1) / kVec;
@@ -1952,7 +1951,7 @@ __device__ __forceinline__ void scan_narrow(const KArgs &a, const PutDescArgs &p
         const int64_t w = lt * kWords + lane;
         if (lane < kWords) *gbl(fd.flags + w) = word;
         const FlagSum sum = tile_sum(word, (int32_t)((uint32_t)w << 6), fd.gap);
-        if (lane == 0) store_sum(a.sums + tile, sum);
+        if (lane == 0) store_sum(a.sums + fd.sum_base + lt, sum);
     }
 }
 
@@ -3164,7 +3163,7 @@ __device__ int64_t short_pedestals(const FillDev &fd, int32_t *s_sum) {
     const int nch = (n + kVec - 1) / kVec;
     const int slice = (fd.C + NW - 1) / NW;
     const int c0 = wid * slice, c1 = c0 + slice < fd.C ? c0 + slice : fd.C;
-    const ScanFill sf{fd.raw, fd.n, fd.stride, fd.C, fd.np, fd.thr, 0, nullptr, fd.ped, 0};
+    const ScanFill sf{fd.raw, fd.n, fd.stride, fd.C, fd.np, fd.thr, 0, nullptr, fd.ped, 0, 0};
     int32_t sum = 0;
     for (int r0 = c0; r0 < c1; r0 += 16)
         sum += ped_add(sf, ped_load(sf, r0, c1, nch, lane), r0, c1, n, fd.ped != nullptr, lane);

@@ -506,7 +506,8 @@ int launch_main(const daq_ctx *ctx, Scratch *sc, const KArgs &a, const daq_sched
                 HIP_TRY(hipStreamWaitEvent(sk, sc->ev_fork, 0));
                 HIP_TRY(hipStreamWaitEvent(sk, sc->ev_scan[k - 1], 0));
             }
-            rc = launch_scan_or_q(ctx, ak, s.threads, tiles, sk);
+            // (groups have equal numbers of fills, not of tiles: the scan strides)
+            rc = launch_scan_or_q(ctx, ak, s.threads, (tiles + parts - 1) / parts, sk);
             if (rc) return rc;
             HIP_TRY(hipEventRecord(sc->ev_scan[k], sk));
             HIP_TRY(daqk::launch_emit(ak, edge_grid(groups), copy_grid, sk));
@@ -730,8 +731,6 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     for (int32_t i = 0; i < n; i++) {
         sbase[(size_t)i] = groups * daqk::kGroupTiles;
         groups += groups_of(fills[i]);
-        // the split variant's scan numbers its tiles as their summaries
-        if (sc.variant == daqk::kVariantSplit && !qouts) total = sbase[(size_t)i];
         base[(size_t)i] = total;
         total += qouts ? q_tiles_of(fills[i], q_threads) : tiles_of(fills[i], sc);
         longest = std::max(longest, fills[i].n_samples);
@@ -1108,7 +1107,7 @@ NoAllocLayout noalloc_layout(const daq_fill *fills, int32_t n, const daq_schedul
     NoAllocLayout L;
     int64_t groups = 0, per_fill = 0;
     for (int32_t i = 0; i < n; i++) {
-        L.total_tiles = groups * daqk::kGroupTiles + tiles_of(fills[i], sc);
+        L.total_tiles += tiles_of(fills[i], sc);
         groups += groups_of(fills[i]);
         per_fill += up16(split_layout_of(fills[i], false).bytes);
     }
@@ -1633,7 +1632,7 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
     put.hdr.total_tiles = L.total_tiles;
     put.hdr.total_groups = L.total_groups;
     put.dst_hdr = d_hdr;
-    int64_t groups = 0, foff = L.fills;
+    int64_t groups = 0, tiles = 0, foff = L.fills;
     for (int32_t i0 = 0; i0 < n; i0 += kPutFills) {
         put.count = std::min<int32_t>(kPutFills, n - i0);
         put.write_hdr = i0 == 0 ? 1 : 0;
@@ -1643,11 +1642,12 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
         for (int32_t k = 0; k < put.count; k++) {
             const daq_fill &f = fills[i0 + k];
             const SplitLayout sl = split_layout_of(f, false);
-            FillDev d = make_desc(f, outs[i0 + k], groups * daqk::kGroupTiles, sc);
-            d.sum_base = d.tile_base;
+            FillDev d = make_desc(f, outs[i0 + k], tiles, sc);
+            d.sum_base = groups * daqk::kGroupTiles;
             d.flags = reinterpret_cast<uint64_t *>(base + foff);
             d.runs = reinterpret_cast<int32_t *>(base + foff + sl.runs);
             put.d[k] = d;
+            tiles += d.n_tiles;
             groups += groups_of(f);
             foff += up16(sl.bytes);
         }
