@@ -58,6 +58,12 @@ constexpr int kNarrowTiles = 2;
 // The scan computes its fill's pedestals itself up to this many pedestal
 // samples (16 lanes hold them, 8 each); k_prepare does for more.
 constexpr int kScanPed = 128;
+// Split schedule: longer pedestals than this take a kernel with a work-group per
+// channel after k_prepare.
+#ifndef DAQ_LONG_PED
+#define DAQ_LONG_PED 512
+#endif
+constexpr int kLongPed = DAQ_LONG_PED;
 // Edge pass: a work-group takes a group of tiles, one 64-sample flag word per
 // thread; every fill's summaries start at a whole group.
 constexpr int kEdgeThreads = 256;
@@ -152,14 +158,17 @@ struct KArgs {
     int64_t total_groups;  // split variant, when hdr is null
     int32_t part, parts;   // split variant: this launch covers fill group `part`
                            // of `parts` equal groups of the batch
-    int32_t q_fused;       // split variant: the Q-method's pass takes the scan's place
     int32_t split;         // 1: the split variant
-    int32_t ped_scan;      // split variant: the scan computes the pedestals
-    int32_t multi_seg;     // split variant: a fill has more than kSegTiles tiles
-    int32_t fused;         // split variant: the emit pass takes the edge and copy passes' place
-    int32_t copies;        // split variant: some fill has packed rows to write
-    int32_t q_small;       // the Q-method's pass loads accumulator rows together (launches the caches hold)
-    int32_t narrow;        // split variant: the scan takes a wave per tile (fills of few channels)
+    int32_t long_ped;      // split variant: most channels of a fill with more than kLongPed pedestal samples, or 0
+    // which kernels are launched (split variant; read by the host alone)
+    int16_t q_fused;       // the Q-method's pass takes the scan's place
+    int16_t q_small;       // .. and loads accumulator rows together (launches the caches hold)
+    int16_t ped_scan;      // the scan computes the pedestals
+    int16_t narrow;        // the scan takes a wave per tile (fills of few channels)
+    int16_t multi_seg;     // a fill has more than kSegTiles tiles
+    int16_t fused;         // the emit pass takes the edge and copy passes' place
+    int16_t copies;        // some fill has packed rows to write
+    int16_t pad16;
     FillDev one;
 };
 

@@ -3189,7 +3189,10 @@ __global__ void __launch_bounds__(256) k_prepare(KArgs a) {
     for (int f = blockIdx.x; f < nf; f += gridDim.x) {
         const FillDev fd = fill_at(a, f);
         const bool is_short = fd.n > 0 && (fd.n < (int64_t)fd.np ? fd.n : (int64_t)fd.np) <= kScanPed;
-        const int64_t ped_sum = is_short ? short_pedestals(fd, s_sum) : fill_pedestals<256>(fd, true, s_acc, &s_ped);
+        const bool is_long = a.long_ped && (fd.n < (int64_t)fd.np ? fd.n : (int64_t)fd.np) > kLongPed;
+        const int64_t ped_sum = is_long    ? 0  // k_long_pedestals adds them
+                                : is_short ? short_pedestals(fd, s_sum)
+                                           : fill_pedestals<256>(fd, true, s_acc, &s_ped);
         if (threadIdx.x == 0) {
             a.thr_eff[f] = (int64_t)fd.thr + ped_sum;
             if (a.tile_pref) a.tile_pref[f] = 0;  // finished tiles (pipe variant)
@@ -3199,6 +3202,54 @@ __global__ void __launch_bounds__(256) k_prepare(KArgs a) {
                 fd.counts->status = 0;
                 fd.counts->reserved = 0;
             }
+        }
+        __syncthreads();
+    }
+}
+
+// Pedestals of more than kLongPed samples, a work-group per channel, added to the
+// effective thresholds that k_prepare has set (split schedule). One work-group
+// for all of a fill's channels, as in k_prepare, is bound by its own loads: a
+// fill of 54 channels with 20,000 pedestal samples took 213 us.
+__global__ void __launch_bounds__(256) k_long_pedestals(KArgs a) {
+    __shared__ long long s_acc[4];
+    const int nf = a.hdr ? a.hdr->n_fills : a.n_fills;
+    const int64_t items = (int64_t)nf * a.long_ped;
+    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const int f = (int)(it / a.long_ped), c = (int)(it - (int64_t)f * a.long_ped);
+        const FillDev fd = fill_at(a, f);
+        const int64_t n = fd.n < (int64_t)fd.np ? fd.n : (int64_t)fd.np;
+        if (n <= kLongPed || c >= fd.C) continue;
+        const int16_t *row = fd.raw + (int64_t)c * fd.stride;
+        int64_t sum = 0;
+        constexpr int U = 8;
+        for (int64_t t0 = threadIdx.x * kVec; t0 < n; t0 += 256 * kVec * U) {
+            uint4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int64_t t = t0 + (int64_t)u * 256 * kVec;
+                v[u] = make_uint4(0, 0, 0, 0);
+                if (t < n) v[u] = load16(row + t);
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int64_t left = n - (t0 + (int64_t)u * 256 * kVec);
+                int32_t s[kVec] = {0, 0, 0, 0, 0, 0, 0, 0};
+                add8(s, v[u]);
+                int32_t part = 0;
+#pragma unroll
+                for (int k = 0; k < kVec; k++) part += k < left ? s[k] : 0;
+                sum += part;
+            }
+        }
+        sum = (int64_t)wave_sum_u64((uint64_t)sum);
+        if ((threadIdx.x & 63) == 0) s_acc[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int64_t all = s_acc[0] + s_acc[1] + s_acc[2] + s_acc[3];
+            const int32_t ped = (int32_t)floor_div(2 * all + n, 2 * n);
+            if (fd.ped) fd.ped[c] = ped;
+            atomicAdd(reinterpret_cast<unsigned long long *>(a.thr_eff + f), (unsigned long long)(long long)ped);
         }
         __syncthreads();
     }
@@ -3317,6 +3368,10 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather(GatherArgs g) {
 
 hipError_t launch_prepare(const KArgs &a, int blocks, hipStream_t s) {
     hipLaunchKernelGGL(k_prepare, dim3(blocks), dim3(256), 0, s, a);
+    if (a.long_ped) {
+        const int64_t items = (int64_t)a.n_fills * a.long_ped;
+        hipLaunchKernelGGL(k_long_pedestals, dim3((uint32_t)(items < 8192 ? items : 8192)), dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 

@@ -379,6 +379,15 @@ bool scan_pedestals(const daq_fill *fills, int32_t n) {
     return true;
 }
 
+// Most channels of a fill whose pedestals k_long_pedestals computes, or 0.
+int32_t long_pedestals(const daq_fill *fills, int32_t n) {
+    int32_t most = 0;
+    for (int32_t i = 0; i < n; i++)
+        if (std::min<int64_t>(fills[i].ped_samples, fills[i].n_samples) > daqk::kLongPed)
+            most = std::max(most, fills[i].n_channels);
+    return most;
+}
+
 FillDev make_desc(const daq_fill &f, const daq_fill_out &o, int64_t tile_base, const daq_schedule &sc) {
     const daqk::TileShape ts = daqk::tile_shape(f.pre, f.post, f.n_channels, sc.threads, sc.variant);
     FillDev d{};
@@ -799,6 +808,7 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     a.q_fused = qouts ? 1 : 0;
     a.split = is_split ? 1 : 0;
     a.ped_scan = is_split && !qouts && scan_pedestals(fills, n) ? 1 : 0;
+    a.long_ped = is_split ? long_pedestals(fills, n) : 0;
     a.multi_seg = longest > (int64_t)daqk::kSegTiles * daqk::kScanTile ? 1 : 0;
     a.fused = emit_fused(a, n, sc.parts, longest) ? 1 : 0;
     a.copies = copies ? 1 : 0;
@@ -1621,6 +1631,7 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
     a.parts = 1;
     a.split = 1;
     a.ped_scan = scan_pedestals(fills, n) ? 1 : 0;
+    a.long_ped = long_pedestals(fills, n);
     a.narrow = narrow_scan(ctx, fills, n, L.total_tiles) ? 1 : 0;
     int64_t longest = 0;
     for (int32_t i = 0; i < n; i++) longest = std::max(longest, fills[i].n_samples);
