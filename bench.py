@@ -958,8 +958,8 @@ def main():
         stream2 = torch.cuda.Stream()
         pipe = [(ctx, daq.Batch(fills, outs), stream), (ctx2, daq.Batch(fills2, outs2), stream2)]
         pipelined = None
-        # overlapping batches want a smaller persistent grid: try the tuned one and 8 per CU
-        for cand in sorted({sched, (sched[0], 8, sched[2], sched[3])}):
+        # overlapping batches want a smaller persistent grid: try the tuned one, 8 and 4 per CU
+        for cand in sorted({sched, (sched[0], 8, sched[2], sched[3]), (sched[0], 4, sched[2], sched[3])}):
             ctx.set_schedule(*cand)
             ctx2.set_schedule(*cand)
             for i in range(4):

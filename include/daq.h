@@ -152,7 +152,9 @@ typedef struct daq_schedule {
     int32_t threads;     /* work-group size: 128, 256 or 512                    */
     int32_t wgs_per_cu;  /* persistent grid = wgs_per_cu x CUs (1..16); 0 =
                             one work-group per tile, as the split variant's
-                            scan always has                                    */
+                            scan also has from 8 on: fewer bound the scan of
+                            long launches, for contexts whose batches
+                            overlap with others on the device (4 there)        */
     int32_t variant;     /* DAQ_VARIANT_*; under DAQ_VARIANT_LDS, fills it
                             cannot take (other channel counts, halos wider
                             than a quarter of its tile) use the re-read path

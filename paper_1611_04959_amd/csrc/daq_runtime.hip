@@ -440,13 +440,25 @@ int ensure_parts(Scratch *sc, int parts) {
 
 // Work-groups of the split variant's scan (one per tile; of waves that take tiles
 // of their own, the resident eight per CU: 16 took 1 to 4 us more) and edge pass
-// (one per group). All stride over their work, so smaller grids are right too.
-int scan_grid(const daq_ctx *ctx, const KArgs &a, int64_t tiles) {
+// (one per group). All stride over their work, so smaller grids are right too. A
+// schedule of fewer than kScanWgs work-groups per CU bounds the scan's grid by
+// them: a launch that overlaps with other streams' then leaves them room for
+// their short passes, which otherwise queue behind its work-groups. 16 fills of 54
+// x 560,000, a batch, one work-group per tile against 4 per CU: on one stream 213 /
+// 223 us, two streams in turn 219 / 212, three 221 / 214; at the nominal pulse rate
+// 201 / 210, 204 / 196, 211 / 200.
+constexpr int kScanWgs = 8;
+constexpr int kScanRounds = 8;  // shorter launches end too unevenly: they keep a work-group per tile
+int scan_grid(const daq_ctx *ctx, const KArgs &a, int64_t tiles, int wgs_per_cu) {
+    int64_t most = 1 << 22;
     if (a.narrow) {
         constexpr int kWaves = daqk::kScanThreads / 64;
-        return (int)std::min<int64_t>((tiles + kWaves - 1) / kWaves, (int64_t)8 * ctx->n_cu);
+        tiles = (tiles + kWaves - 1) / kWaves;
+        most = (int64_t)8 * ctx->n_cu;
     }
-    return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 1 << 22);
+    const int64_t bound = (int64_t)wgs_per_cu * ctx->n_cu;
+    if (wgs_per_cu > 0 && wgs_per_cu < kScanWgs && tiles >= kScanRounds * bound) most = std::min(most, bound);
+    return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), most);
 }
 // Whether the scan takes a wave per tile.
 bool narrow_scan(const daq_ctx *ctx, const daq_fill *fills, int32_t n, int64_t tiles) {
@@ -465,12 +477,12 @@ bool emit_fused(const KArgs &a, int32_t n, int parts, int64_t longest) {
 }
 
 // The scan of a split launch, or the Q-method's pass in its place.
-int launch_scan_or_q(const daq_ctx *ctx, const KArgs &a, int threads, int64_t tiles, hipStream_t stream,
+int launch_scan_or_q(const daq_ctx *ctx, const KArgs &a, const daq_schedule &sc, int64_t tiles, hipStream_t stream,
                      const daqk::PutDescArgs *put = nullptr) {
     if (a.q_fused)
-        HIP_TRY(daqk::launch_q(a, threads, a.q_small, (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 8 * (int64_t)ctx->n_cu), stream));
+        HIP_TRY(daqk::launch_q(a, sc.threads, a.q_small, (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), 8 * (int64_t)ctx->n_cu), stream));
     else
-        HIP_TRY(daqk::launch_scan(a, scan_grid(ctx, a, tiles), stream, put));
+        HIP_TRY(daqk::launch_scan(a, scan_grid(ctx, a, tiles, sc.wgs_per_cu), stream, put));
     return DAQ_OK;
 }
 
@@ -487,7 +499,7 @@ int launch_main(const daq_ctx *ctx, Scratch *sc, const KArgs &a, const daq_sched
             KArgs a1 = a;
             a1.part = 0;
             a1.parts = 1;
-            const int rc = launch_scan_or_q(ctx, a1, s.threads, tiles, stream, put);
+            const int rc = launch_scan_or_q(ctx, a1, s, tiles, stream, put);
             if (rc) return rc;
             if (a1.fused) {
                 // two work-groups per CU, shared by the fills; where only records are written
@@ -516,7 +528,7 @@ int launch_main(const daq_ctx *ctx, Scratch *sc, const KArgs &a, const daq_sched
                 HIP_TRY(hipStreamWaitEvent(sk, sc->ev_scan[k - 1], 0));
             }
             // (groups have equal numbers of fills, not of tiles: the scan strides)
-            rc = launch_scan_or_q(ctx, ak, s.threads, (tiles + parts - 1) / parts, sk);
+            rc = launch_scan_or_q(ctx, ak, s, (tiles + parts - 1) / parts, sk);
             if (rc) return rc;
             HIP_TRY(hipEventRecord(sc->ev_scan[k], sk));
             HIP_TRY(daqk::launch_emit(ak, edge_grid(groups), copy_grid, sk));
@@ -1667,7 +1679,7 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
     }
     if (!a.ped_scan || L.total_tiles == 0) HIP_TRY(daqk::launch_prepare(a, prepare_blocks(a, L.total_tiles), stream));
     if (L.total_tiles == 0) return DAQ_OK;  // only counts and pedestals to clear
-    HIP_TRY(daqk::launch_scan(a, scan_grid(ctx, a, L.total_tiles), stream));
+    HIP_TRY(daqk::launch_scan(a, scan_grid(ctx, a, L.total_tiles, sc.wgs_per_cu), stream));
     HIP_TRY(daqk::launch_emit(a, edge_grid(L.total_groups), daqk::kCopyWgsPerCu * ctx->n_cu, stream));
     return DAQ_OK;
 }
