@@ -72,15 +72,19 @@ constexpr int kGroupTiles = kEdgeThreads * 64 / kScanTile;
 // samples is one such segment; longer fills have segment summaries too.
 constexpr int kSegGroups = 36;
 constexpr int kSegTiles = kSegGroups * kGroupTiles;
-// Emit pass: threads per work-group, and the most fills of a launch that takes
-// it in place of the edge and copy passes (54 x 70,000 fills, whole call, emit
-// against edge + copy: 1 fill 28.8 / 32.6 us, 2 47.9 / 52.5, 4 74.9 / 75.7, 8
-// 120.1 / 119.7, 16 240 / 230).
+// Emit pass: threads per work-group, and the launches that take it in place of the
+// edge and copy passes: one fill, or up to kEmitFills of kEmitSamples samples
+// together. Whole calls at the nominal pulse rate, emit against edge + copy, on
+// one stream: 2 x 8,191 samples 14.1 / 18.5 us, 4 x 70,000 24.1 / 26.7, 4 x 140,000
+// 32.3 / 34.8, 3 x 280,000 35.3 / 37.5, 2 x 560,000 39.0 / 37.7, 4 x 560,000 63.7 /
+// 63.9. On three streams in turn its work-groups leave the other launches less
+// room: 4 x 70,000 16.6 / 16.0, 2 x 560,000 29.1 / 27.8, 4 x 560,000 51.8 / 51.1.
 constexpr int kEmitThreads = 512;
 #ifndef DAQ_EMIT_FILLS
 #define DAQ_EMIT_FILLS 4
 #endif
 constexpr int kEmitFills = DAQ_EMIT_FILLS;
+constexpr int64_t kEmitSamples = 1 << 20;
 
 // Flags of a stretch of samples, as a fill's islands see them (gap = pre + post
 // + 1: windows of flags at most gap apart are one island). Stretches add up

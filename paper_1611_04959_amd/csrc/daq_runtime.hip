@@ -469,11 +469,11 @@ bool narrow_scan(const daq_ctx *ctx, const daq_fill *fills, int32_t n, int64_t t
 }
 int edge_grid(int64_t groups) { return (int)std::min<int64_t>(std::max<int64_t>(groups, 1), 1 << 20); }
 
-// Whether a split launch takes the emit pass in place of the edge and copy
-// passes (the kernel's comment says when that is faster).
-bool emit_fused(const KArgs &a, int32_t n, int parts, int64_t longest) {
-    return a.split && n <= daqk::kEmitFills && parts <= 1 &&
-           longest <= (int64_t)daqk::kSegTiles * daqk::kScanTile;
+// Whether a split launch of n fills, of `samples` in all and `longest` the longest,
+// takes the emit pass in place of the edge and copy passes.
+bool emit_fused(const KArgs &a, int32_t n, int parts, int64_t samples, int64_t longest) {
+    return a.split && parts <= 1 && longest <= (int64_t)daqk::kSegTiles * daqk::kScanTile &&
+           (n == 1 || (n <= daqk::kEmitFills && samples <= daqk::kEmitSamples));
 }
 
 // The scan of a split launch, or the Q-method's pass in its place.
@@ -741,7 +741,7 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     // the register variant keeps exactly 54 rows per thread: calls with other
     // channel counts run the re-read variant
     if (sc.variant == daqk::kVariantResident && !all_calorimeters(fills, n)) sc.variant = daqk::kVariantReload;
-    int64_t total = 0, mask_total = 0, groups = 0, longest = 0;
+    int64_t total = 0, mask_total = 0, groups = 0, samples = 0, longest = 0;
     std::vector<int64_t> base((size_t)n), sbase((size_t)n), moff((size_t)n, -1);
     std::vector<SplitLayout> lay((size_t)n);
     const int q_threads = sc.threads;  // work-group size of the Q-method's pass
@@ -754,6 +754,7 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
         groups += groups_of(fills[i]);
         base[(size_t)i] = total;
         total += qouts ? q_tiles_of(fills[i], q_threads) : tiles_of(fills[i], sc);
+        samples += fills[i].n_samples;
         longest = std::max(longest, fills[i].n_samples);
         copies = copies || outs[i].out != nullptr;
         raw_bytes += 2 * (int64_t)fills[i].n_channels * fills[i].n_samples;
@@ -822,7 +823,7 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     a.ped_scan = is_split && !qouts && scan_pedestals(fills, n) ? 1 : 0;
     a.long_ped = is_split ? long_pedestals(fills, n) : 0;
     a.multi_seg = longest > (int64_t)daqk::kSegTiles * daqk::kScanTile ? 1 : 0;
-    a.fused = emit_fused(a, n, sc.parts, longest) ? 1 : 0;
+    a.fused = emit_fused(a, n, sc.parts, samples, longest) ? 1 : 0;
     a.copies = copies ? 1 : 0;
     a.narrow = narrow_scan(ctx, fills, n, total) ? 1 : 0;
     if (n == 1 && !force_table && (!batch || is_split)) {
