@@ -1986,12 +1986,10 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_put(KArgs a, PutDescArgs 
 // thread begins and, for the multiple k of kCopyChunk among its packed
 // positions (at most one), the island holding packed position k; the thread
 // owns samples p .. p + 7 with island mask r.mm and the prefixes of r.
-// COHERENT: device-scope stores (read by other work-groups of the launch).
-template <bool COHERENT = false>
+// Device-scope stores: other work-groups of the launch read them.
 __device__ __forceinline__ void write_runs(const FillDev &fd, const TileScan &r, int64_t p) {
     auto put = [](DAQ_GLOBAL int32_t *dst, int32_t v) {
-        if constexpr (COHERENT) __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else *dst = v;
+        __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     if (fd.out == nullptr || r.mm == 0) return;
     const int64_t mbase = r.m_before + r.th_m;
@@ -2246,9 +2244,9 @@ struct ChunkInfo {
 };
 // Chunk k of fill fd's packed rows (the fill's counts, run table and chunk
 // map complete; ci the same in every thread); L is a CopyLayout for
-// kCopyChunk + 1 runs. COHERENT: the run table is read with device-scope
-// loads (it was written in the same launch).
-template <int NT, class L, bool COHERENT = false, int U = DAQ_EMIT_U>
+// kCopyChunk + 1 runs. The run table is read with device-scope loads (it was
+// written in the same launch).
+template <int NT, class L, int U = DAQ_EMIT_U>
 __device__ __forceinline__ void copy_chunk(const FillDev &fd, int64_t k, const ChunkInfo &ci, const CopyView &v) {
     constexpr int P = kCopyChunk;
     const int tid = threadIdx.x;
@@ -2258,14 +2256,8 @@ __device__ __forceinline__ void copy_chunk(const FillDev &fd, int64_t k, const C
     const int nrun = ci.i1 - ci.i0 + 1;  // islands touching [q0, q0 + P], at most P + 1
     for (int r = tid; r < nrun; r += NT) {
         const DAQ_GLOBAL int32_t *e = gbl(fd.runs + 2 * (int64_t)(ci.i0 + r));
-        int32_t st, of;
-        if constexpr (COHERENT) {
-            st = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            of = __hip_atomic_load(e + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            st = e[0];
-            of = e[1];
-        }
+        const int32_t st = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t of = __hip_atomic_load(e + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int64_t d = (int64_t)of - q0;  // negative only for the first island
         v.dst[r] = d > 0 ? (int32_t)d : 0;
         v.src[r] = d > 0 ? st : (int32_t)(st - d);
@@ -2522,9 +2514,9 @@ __device__ __forceinline__ int load_runs(const int32_t *runs, int64_t n_isl, int
 
 constexpr int kCopyFills = kLdsFills;  // fills per window of the item prefix
 
-template <int NT>
-__global__ void __launch_bounds__(NT) k_copy_pass(KArgs a) {
-    constexpr int NW = NT / 64;
+constexpr int kCopyThreads = 512;
+__global__ void __launch_bounds__(kCopyThreads) k_copy_pass(KArgs a) {
+    constexpr int NT = kCopyThreads, NW = NT / 64;
     __shared__ int64_t s_item[kCopyFills + 1];
     __shared__ int32_t s_tl[kCopyFills], s_nisl[kCopyFills];  // each fill's counts
     __shared__ int32_t s_st[NW][kSegRuns];
@@ -2905,7 +2897,7 @@ __device__ __forceinline__ void pipe_tile(const KArgs &a, const FillDev &fd, int
     scan_back(a, fd, q.lt, r, s_excl, a.ticket + 4);
     write_records(fd, r, q.p);
     write_counts<true>(fd, q.lt, r);
-    write_runs<true>(fd, r, q.p);
+    write_runs(fd, r, q.p);
     if (threadIdx.x == 0 && fd.counts != nullptr &&
         __hip_atomic_load(a.ticket + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
         __hip_atomic_fetch_or(&fd.counts->status, DAQ_STATUS_INCOMPLETE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2958,7 +2950,7 @@ __global__ void __launch_bounds__(NT) k_pipe(KArgs a) {
             const uint64_t id = (uint64_t)(kJobCopy - job);
             const FillDev fc = fill_at(a, (int)(id >> 32));
             const ChunkInfo ci = s_ci;
-            copy_chunk<NT, PipeCopyLayout, true>(fc, (int64_t)(uint32_t)id, ci, copy_view<PipeCopyLayout>(s_lds));
+            copy_chunk<NT, PipeCopyLayout>(fc, (int64_t)(uint32_t)id, ci, copy_view<PipeCopyLayout>(s_lds));
         }
         lds_barrier();
     }
@@ -3433,7 +3425,7 @@ hipError_t launch_emit(const KArgs &a, int edge_grid, int copy_grid, hipStream_t
     const int cg = copy_grid < 1 ? 1 : copy_grid;
     if (a.multi_seg) hipLaunchKernelGGL(k_seg_pass, dim3(eg), dim3(kEdgeThreads), 0, s, a);
     hipLaunchKernelGGL(k_edge_pass, dim3(eg), dim3(kEdgeThreads), 0, s, a);
-    hipLaunchKernelGGL((k_copy_pass<512>), dim3(cg), dim3(512), 0, s, a);
+    hipLaunchKernelGGL(k_copy_pass, dim3(cg), dim3(kCopyThreads), 0, s, a);
     return hipGetLastError();
 }
 
