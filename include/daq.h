@@ -256,8 +256,8 @@ int daq_process_batch(daq_ctx *ctx, const daq_fill *fills,
  * no allocation, no graph, no event, no memset and no host staging. Every
  * scratch buffer of the call (effective thresholds, the descriptor table, each
  * fill's flag bits and run table) lives in one static device array of
- * DAQ_NOALLOC_SCRATCH_BYTES per GPU, and the tile summaries in three times as
- * much behind it, which the library holds from the first
+ * DAQ_NOALLOC_SCRATCH_BYTES per GPU, and the tile summaries in half as much
+ * behind it, which the library holds from the first
  * daq_ctx_create on that GPU until the process ends; the descriptors reach it
  * through kernel arguments. Calls on one GPU share that array: calls that
  * overlap in time on one GPU (other streams, other contexts or threads) race

@@ -118,7 +118,7 @@ struct FillDev {
     int32_t pad1;
     int64_t tout;       // samples a tile owns (decides and writes)
     int64_t n_tiles;
-    int64_t sum_base;   // split variant: index of the fill's first tile summary, a multiple of kGroupTiles
+    int64_t sum_base;   // split variant: where the fill's groups of tiles begin, a multiple of kGroupTiles
     daq_island *isl;
     int64_t cap;
     daq_counts *counts;
@@ -126,8 +126,11 @@ struct FillDev {
     int64_t out_stride;
     int32_t *runs;      // split and pipe variants: (start, offset) of every island
                         // (room for the worst-case island count)
-    int32_t *cmap;      // pipe variant: island holding packed position
-                        // k * kCopyChunk, for every such position < total_len
+    union {
+        int32_t *cmap;   // pipe variant: island holding packed position
+                         // k * kCopyChunk, for every such position < total_len
+        int64_t sum_at;  // split variant: index of the fill's first tile summary
+    };
     int64_t *qsum;      // Q-method: decimated sums, or null
     int32_t *acc;       // Q-method: fill-by-fill accumulator rows, or null
     int64_t acc_stride;

@@ -1680,7 +1680,7 @@ struct ScanFill {
     int32_t C, np, thr, gap;  // gap: pre + post + 1
     uint64_t *flags;
     int32_t *ped;
-    int64_t tile_base, sum_base;
+    int64_t tile_base, sum_at;
 };
 
 // The sum over the 16 lanes of a DPP row (every lane gets it).
@@ -1755,12 +1755,12 @@ __device__ __forceinline__ void scan_tiles(const KArgs &a, const PutDescArgs &pu
             const uint64_t le = __ballot(lane < nf && put.d[l].tile_base <= tile);
             const FillDev &d = put.d[__builtin_amdgcn_readfirstlane(__popcll(le) - 1)];
             fd = ScanFill{d.raw, d.n, d.stride, d.C, d.np, d.thr, d.pre + d.post + 1, d.flags, d.ped, d.tile_base,
-                          d.sum_base};
+                          d.sum_at};
         } else if (a.table) {
             const int f = fill_of(a.tile_bases, nf, tile);
             const DAQ_CONST FillDev *d = fill_const(a, f);
             fd = ScanFill{d->raw, d->n, d->stride, d->C, d->np, d->thr, d->pre + d->post + 1, d->flags, d->ped,
-                          d->tile_base, d->sum_base};
+                          d->tile_base, d->sum_at};
             if (!PED) te = *gbl(a.thr_eff + f);
         } else {
             fd = ScanFill{a.one.raw, a.one.n, a.one.stride, a.one.C, a.one.np, a.one.thr, a.one.pre + a.one.post + 1,
@@ -1839,7 +1839,7 @@ __device__ __forceinline__ void scan_tiles(const KArgs &a, const PutDescArgs &pu
             const uint64_t x = lane < kWords ? s_word[lane] : 0ull;
             if (lane < kWords) *gbl(fd.flags + w) = x;
             const FlagSum sum = tile_sum(x, (int32_t)((uint32_t)w << 6), fd.gap);
-            if (lane == 0) store_sum(a.sums + fd.sum_base + lt, sum);
+            if (lane == 0) store_sum(a.sums + fd.sum_at + lt, sum);
         }
         // (the next tile's LDS writes come after barriers that the readers above have passed)
     }
@@ -1887,12 +1887,12 @@ __device__ __forceinline__ void scan_narrow(const KArgs &a, const PutDescArgs &p
                 const uint64_t le = __ballot(lane < nf && put.d[l].tile_base <= tile);
                 const FillDev &d = put.d[__builtin_amdgcn_readfirstlane(__popcll(le) - 1)];
                 fd = ScanFill{d.raw, d.n, d.stride, d.C, d.np, d.thr, d.pre + d.post + 1, d.flags, d.ped, d.tile_base,
-                              d.sum_base};
+                              d.sum_at};
             } else if (a.table) {
                 const int f = fill_of(a.tile_bases, nf, tile);
                 const DAQ_CONST FillDev *d = fill_const(a, f);
                 fd = ScanFill{d->raw, d->n, d->stride, d->C, d->np, d->thr, d->pre + d->post + 1, d->flags, d->ped,
-                              d->tile_base, d->sum_base};
+                              d->tile_base, d->sum_at};
                 if (!PED) te = *gbl(a.thr_eff + f);
             } else {
                 fd = ScanFill{a.one.raw, a.one.n, a.one.stride, a.one.C, a.one.np, a.one.thr,
@@ -1951,7 +1951,7 @@ __device__ __forceinline__ void scan_narrow(const KArgs &a, const PutDescArgs &p
         const int64_t w = lt * kWords + lane;
         if (lane < kWords) *gbl(fd.flags + w) = word;
         const FlagSum sum = tile_sum(word, (int32_t)((uint32_t)w << 6), fd.gap);
-        if (lane == 0) store_sum(a.sums + fd.sum_base + lt, sum);
+        if (lane == 0) store_sum(a.sums + fd.sum_at + lt, sum);
     }
 }
 
@@ -2036,7 +2036,7 @@ struct EdgeFill {
     const uint64_t *flags;
     int64_t n;
     int32_t pre, post, C;
-    int64_t sum_base;
+    int64_t sum_base, sum_at;
     daq_island *isl;
     int64_t cap;
     daq_counts *counts;
@@ -2047,7 +2047,7 @@ struct EdgeFill {
 };
 template <class D>
 __device__ __forceinline__ EdgeFill edge_fill_of(const D &d) {
-    return EdgeFill{d.flags, d.n, d.pre, d.post, d.C, d.sum_base, d.isl, d.cap, d.counts, d.ped, d.out, d.out_stride,
+    return EdgeFill{d.flags, d.n, d.pre, d.post, d.C, d.sum_base, d.sum_at, d.isl, d.cap, d.counts, d.ped, d.out, d.out_stride,
                     d.runs};
 }
 __device__ __forceinline__ EdgeFill edge_fill(const KArgs &a, int f) {
@@ -2170,7 +2170,7 @@ __global__ void __launch_bounds__(kEdgeThreads) k_seg_pass(KArgs a) {
         if (tiles <= kSegTiles || t0 % kSegTiles != 0) continue;
         const int m = (int)(tiles - t0 < kSegTiles ? tiles - t0 : kSegTiles);
         const int32_t gap = fd.pre + fd.post + 1;
-        const FlagSum s = sum_range<kEdgeThreads>(a.sums + fd.sum_base + t0, m, gap);
+        const FlagSum s = sum_range<kEdgeThreads>(a.sums + fd.sum_at + t0, m, gap);
         if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = s;
         lds_barrier();
         if (threadIdx.x == 0) {
@@ -2199,7 +2199,7 @@ __global__ void __launch_bounds__(kEdgeThreads) k_edge_pass(KArgs a) {
         const uint64_t x = w < (fd.n + 63) >> 6 ? *gbl(fd.flags + w) : 0ull;
         const int32_t ws = (int32_t)((uint32_t)w << 6);
         const int64_t seg = t0 / kSegTiles;
-        const FlagSum before = sum_range<kEdgeThreads>(a.sums + fd.sum_base + seg * kSegTiles, (int)(t0 - seg * kSegTiles), gap);
+        const FlagSum before = sum_range<kEdgeThreads>(a.sums + fd.sum_at + seg * kSegTiles, (int)(t0 - seg * kSegTiles), gap);
         FlagSum segs = kNoFlags;
         if (seg > 0) segs = sum_range<kEdgeThreads>(a.seg_sums + seg_at(fd.sum_base, f), (int)seg, gap);
         const FlagSum s = scan_sums(word_sum(x, ws, gap), gap);
@@ -2641,7 +2641,7 @@ __global__ void __launch_bounds__(kEmitThreads, 4) k_emit_pass(KArgs a) {
     const int32_t gap = fd.pre + fd.post + 1;
     const int tiles = (int)((fd.n + kScanTile - 1) / kScanTile);
     const int per = (tiles + NT - 1) / NT;
-    const int4 *sums = a.sums + fd.sum_base;
+    const int4 *sums = a.sums + fd.sum_at;
     FlagSum t[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; i++) {
@@ -3092,7 +3092,7 @@ __global__ void __launch_bounds__(NT) k_q_pass(KArgs a) {
             const uint32_t xl = __shfl((int)lo, 8 * (tid & 7), 64), xh = __shfl((int)hi, 8 * (tid & 7), 64);
             const uint64_t xs = (tid & 63) < 8 ? ((uint64_t)xh << 32) | xl : 0ull;
             const FlagSum sum = tile_sum(xs, (int32_t)((uint32_t)(8 * t512 + (tid & 7)) << 6), fd.pre + fd.post + 1);
-            if ((tid & 63) == 0 && t512 * kScanTile < fd.n) store_sum(a.sums + fd.sum_base + t512, sum);
+            if ((tid & 63) == 0 && t512 * kScanTile < fd.n) store_sum(a.sums + fd.sum_at + t512, sum);
         }
         // one bin = kGroupsPerBin consecutive threads (within one wave)
 #pragma unroll

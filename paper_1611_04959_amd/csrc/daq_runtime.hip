@@ -99,7 +99,7 @@ struct Scratch {
     int64_t *bases = nullptr;       // device, inside the hdr allocation: fill_cap tile bases, as many summary bases
     int4 *sums = nullptr;           // split variant: tile summaries (sum_cap) ..
     daqk::FlagSum *seg_sums = nullptr;  // .. and segment summaries, in one allocation
-    int64_t sum_cap = 0;
+    int64_t sum_cap = 0, group_cap = 0;
     uint8_t *mask = nullptr;        // split and pipe variants: flags, run tables and chunk maps of all fills
     int64_t mask_cap = 0;
     int32_t *q_ped = nullptr;       // Q-method: pedestals of fills that have no ped output
@@ -248,11 +248,10 @@ size_t desc_bytes(int32_t cap, int32_t n) {
 
 // Grows the scratch of one stream; waits for that stream first because the
 // old buffers may still be in use by queued work or its own captured graphs.
-int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes, int64_t groups) {
+int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes, int64_t sums, int64_t groups) {
     if (!s->ticket) HIP_TRY(hipMalloc(&s->ticket, 64));
-    const int64_t sums = groups * daqk::kGroupTiles;
     if (tiles <= s->tile_cap && fills <= s->fill_cap && s->ring_host && mask_bytes <= s->mask_cap &&
-        sums <= s->sum_cap)
+        sums <= s->sum_cap && groups <= s->group_cap)
         return DAQ_OK;
     HIP_TRY(hipStreamSynchronize(s->stream));
     free_graphs(s);
@@ -269,16 +268,17 @@ int ensure_scratch(Scratch *s, int64_t tiles, int32_t fills, int64_t mask_bytes,
         HIP_TRY(hipMalloc(&s->tile_pref, (size_t)cap * sizeof(uint64_t)));
         s->tile_cap = cap;
     }
-    if (sums > s->sum_cap) {
-        const int64_t cap = std::max<int64_t>(groups + groups / 2, 256);
+    if (sums > s->sum_cap || groups > s->group_cap) {
+        const int64_t cap = std::max<int64_t>({sums + sums / 2, s->sum_cap, 8192});
+        const int64_t gcap = std::max<int64_t>({groups + groups / 2, s->group_cap, 256});
         give_up(s, s->sums);
         s->sums = nullptr;
         s->seg_sums = nullptr;
-        s->sum_cap = 0;
-        HIP_TRY(hipMalloc(&s->sums, (size_t)cap * daqk::kGroupTiles * sizeof(int4) +
-                                        (size_t)seg_entries(cap) * sizeof(daqk::FlagSum)));
-        s->seg_sums = reinterpret_cast<daqk::FlagSum *>(s->sums + cap * daqk::kGroupTiles);
-        s->sum_cap = cap * daqk::kGroupTiles;
+        s->sum_cap = s->group_cap = 0;
+        HIP_TRY(hipMalloc(&s->sums, (size_t)cap * sizeof(int4) + (size_t)seg_entries(gcap) * sizeof(daqk::FlagSum)));
+        s->seg_sums = reinterpret_cast<daqk::FlagSum *>(s->sums + cap);
+        s->sum_cap = cap;
+        s->group_cap = gcap;
     }
     if (mask_bytes > s->mask_cap) {
         const int64_t cap = std::max<int64_t>(mask_bytes + mask_bytes / 2, 1 << 20);
@@ -348,8 +348,9 @@ int64_t q_tiles_of(const daq_fill &f, int threads) {
     return (f.n_samples + T - 1) / T;
 }
 
-// Tile summaries of a fill (split variant), in whole groups; a fill without
-// samples takes a group too (its counts are written there).
+// Tile summaries of a fill (split variant), and its groups of tiles; a fill
+// without samples takes a group too (its counts are written there).
+int64_t scan_tiles_of(const daq_fill &f) { return (f.n_samples + daqk::kScanTile - 1) / daqk::kScanTile; }
 int64_t groups_of(const daq_fill &f) {
     constexpr int64_t T = (int64_t)daqk::kScanTile * daqk::kGroupTiles;
     return std::max<int64_t>(1, (f.n_samples + T - 1) / T);
@@ -741,8 +742,8 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     // the register variant keeps exactly 54 rows per thread: calls with other
     // channel counts run the re-read variant
     if (sc.variant == daqk::kVariantResident && !all_calorimeters(fills, n)) sc.variant = daqk::kVariantReload;
-    int64_t total = 0, mask_total = 0, groups = 0, samples = 0, longest = 0;
-    std::vector<int64_t> base((size_t)n), sbase((size_t)n), moff((size_t)n, -1);
+    int64_t total = 0, mask_total = 0, groups = 0, sums = 0, samples = 0, longest = 0;
+    std::vector<int64_t> base((size_t)n), sbase((size_t)n), sum_at((size_t)n), moff((size_t)n, -1);
     std::vector<SplitLayout> lay((size_t)n);
     const int q_threads = sc.threads;  // work-group size of the Q-method's pass
     // the pipe variant uses the split variant's run table and chunk map
@@ -752,6 +753,8 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     for (int32_t i = 0; i < n; i++) {
         sbase[(size_t)i] = groups * daqk::kGroupTiles;
         groups += groups_of(fills[i]);
+        sum_at[(size_t)i] = sums;
+        sums += scan_tiles_of(fills[i]);
         base[(size_t)i] = total;
         total += qouts ? q_tiles_of(fills[i], q_threads) : tiles_of(fills[i], sc);
         samples += fills[i].n_samples;
@@ -768,7 +771,8 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
     // one look-back word per tile; they double as per-fill words (pipe
     // variant): at least one per fill
     const bool is_split = sc.variant == daqk::kVariantSplit;
-    int rc = ensure_scratch(s, std::max<int64_t>(is_split ? 0 : total, n), n, mask_total, is_split ? groups : 0);
+    int rc = ensure_scratch(s, std::max<int64_t>(is_split ? 0 : total, n), n, mask_total, is_split ? sums : 0,
+                            is_split ? groups : 0);
     if (rc) return rc;
     // fused Q-method: the accumulator update needs the pedestals in memory
     std::vector<int64_t> poff((size_t)n, -1);
@@ -794,7 +798,9 @@ int run_fused(daq_ctx *ctx, const daq_fill *fills, const daq_fill_out *outs, int
         d.sum_base = sbase[(size_t)i];
         d.flags = split ? reinterpret_cast<uint64_t *>(s->mask + moff[(size_t)i]) : nullptr;
         d.runs = split ? reinterpret_cast<int32_t *>(s->mask + moff[(size_t)i] + lay[(size_t)i].runs) : nullptr;
-        d.cmap = split ? reinterpret_cast<int32_t *>(s->mask + moff[(size_t)i] + lay[(size_t)i].cmap) : nullptr;
+        if (sc.variant == daqk::kVariantPipe)
+            d.cmap = reinterpret_cast<int32_t *>(s->mask + moff[(size_t)i] + lay[(size_t)i].cmap);
+        if (sc.variant == daqk::kVariantSplit) d.sum_at = sum_at[(size_t)i];
         if (qouts) {
             const daq_q_out &q = qouts[i];
             d.tout = (int64_t)q_threads * daqk::kVec;
@@ -1061,12 +1067,11 @@ std::string shape_key(const daq_ctx *ctx, const daq_fill *fills, int32_t n) {
 // looked up once per device, at the first daq_ctx_create on it, and kept in
 // g_noalloc_ptr.
 //
-// The tile summaries have a part of their own behind the documented bytes,
-// three times as large: a call that fits these never needs more. (A group of
-// 16,384 samples takes at most 533 bytes of summaries; a fill takes at least
-// 216 bytes of the rest for its descriptor and words, and over 2,048 for each
-// group after its first.)
-constexpr int64_t kNoAllocSumBytes = DAQ_NOALLOC_SCRATCH_BYTES * 3;
+// The tile summaries have a part of their own behind the documented bytes, half
+// as large: a call that fits these never needs more. (16,384 samples take at most
+// 533 bytes of summaries and over 2,048 of the rest; a fill's first ones at most 37,
+// and at least 216 for its descriptor and words.)
+constexpr int64_t kNoAllocSumBytes = DAQ_NOALLOC_SCRATCH_BYTES / 2;
 static __device__ __align__(256) uint8_t scratch[DAQ_NOALLOC_SCRATCH_BYTES + kNoAllocSumBytes];
 
 constexpr int kMaxDevices = 64;
@@ -1135,7 +1140,7 @@ NoAllocLayout noalloc_layout(const daq_fill *fills, int32_t n, const daq_schedul
         per_fill += up16(split_layout_of(fills[i], false).bytes);
     }
     L.total_groups = groups;
-    L.seg_sums = groups * daqk::kGroupTiles * (int64_t)sizeof(int4);
+    L.seg_sums = L.total_tiles * (int64_t)sizeof(int4);
     L.sum_bytes = L.seg_sums + seg_entries(groups) * (int64_t)sizeof(daqk::FlagSum);
     int64_t o = 0;
     L.ticket = o;
@@ -1336,7 +1341,7 @@ int run_qmethod(daq_ctx *ctx, const daq_fill *fills, const daq_q_out *outs, int3
         }
     }
     Scratch *s = open_scratch(ctx, stream);
-    int rc = ensure_scratch(s, std::max<int64_t>(total, n), n, 0, 0);
+    int rc = ensure_scratch(s, std::max<int64_t>(total, n), n, 0, 0, 0);
     if (rc) return rc;
     if (ped_need > s->q_ped_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
@@ -1668,6 +1673,7 @@ int daq_process_batch_noalloc(daq_ctx *ctx, const daq_fill *fills, const daq_fil
             const SplitLayout sl = split_layout_of(f, false);
             FillDev d = make_desc(f, outs[i0 + k], tiles, sc);
             d.sum_base = groups * daqk::kGroupTiles;
+            d.sum_at = tiles;
             d.flags = reinterpret_cast<uint64_t *>(base + foff);
             d.runs = reinterpret_cast<int32_t *>(base + foff + sl.runs);
             put.d[k] = d;
