@@ -8,15 +8,19 @@
 //            threshold thr + sum(ped); clears the look-back words and counts
 //            (every schedule but the split one, which sums the pedestals in
 //            its scan).
-// k_scan_pass, k_edge_pass, k_copy_pass, k_emit_pass
+// k_long_pedestals
+//            after it, for pedestals of more than 512 samples: a work-group per
+//            channel (split schedule).
+// k_scan_pass (k_scan_put), k_edge_pass, k_copy_pass, k_emit_pass
 //            the split schedule (the default): a streaming scan that computes
 //            its fill's pedestals and writes one threshold flag per sample
 //            and a summary of each tile's flags; an edge pass (the island
 //            records, a run table and the counts, from the flags and the
 //            summaries of the fill's earlier tiles; k_seg_pass sums these up
 //            for very long fills); and a copy of the island samples in equal
-//            chunks of packed positions. The emit pass is both in one, for
-//            launches of few fills.
+//            chunks of packed positions. The emit pass is both in one, for one
+//            fill or a few short ones. k_scan_put is the scan of a new batch,
+//            whose table it writes.
 // k_pipe     one persistent kernel: scan tiles (steps 1-4a below) and copy
 //            chunks of finished fills, taken from shared counters.
 // k_chop     the fused pass. Each thread of a work-group takes 8 consecutive

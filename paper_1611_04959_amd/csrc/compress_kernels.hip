@@ -13,8 +13,8 @@
 // group is lanes 8 j .. 8 j + 7. The launch's work-groups are shared out to the
 // fills by their groups, and a fill's groups cut into one contiguous range per
 // wave. Two kernels:
-// the size pass writes the block headers and each wave's payload words; the
-// pack pass starts each wave at the sum of the sizes of the waves before it,
+// the size pass writes the block headers and the payload words of each wave and
+// work-group; the pack pass starts each wave at the sum of the sizes before it,
 // walks its groups in order, ORs each lane's codes into the group's payload
 // in LDS (all eight as one or two 64-bit values, three atomics each) and stores
 // the payload with coalesced writes. Every wave touches only its own LDS, so
@@ -28,7 +28,7 @@
 // while one is worked on, at clamped indices rather than behind branches.
 // 16 fills of 54 rows of 11,000 to 61,000 samples (31 M samples, 62 MB, 21 MB
 // of payload): size pass 16.6 -> 14.5 us (4.3 TB/s), pack pass 32.7 -> 22.3 us
-// (4.0 TB/s), decoding 35.3 -> 25 us (3.6 TB/s).
+// (4.0 TB/s), decoding 35.3 -> 22.8 us a call (3.7 TB/s).
 #include "chop_internal.h"
 
 namespace daqk {
