@@ -101,6 +101,7 @@ def test_a_captured_call_outlives_the_growth_of_its_scratch(kind):
     rng = np.random.default_rng(len(kind))
     small, large = (make(rng) for make in KINDS[kind])
     with daq.Context(0) as ctx:
+        ctx.set_schedule(512, 8, 5, 0)  # launched plainly, whatever the environment says
         s = torch.cuda.Stream()
         with torch.cuda.stream(s):
             small.call(ctx)  # the scratch of a small call
